@@ -64,8 +64,8 @@ static void release(ck_matrix *M) {
     mat_free(*M, M->panel_col);
     mat_free(*M, M->panel_val);
     mat_free(*M, M->panel_val32);
-    mat_free(*M, M->merge_part);
-    mat_free(*M, M->panel_part);
+    mat_free(*M, M->merge_plan);
+    mat_free(*M, M->panel_plan);
     mat_free(*M, M->panel_row);
     mat_free(*M, M->devsel_scratch);
     mat_free(*M, M->panel_boff);
@@ -125,13 +125,14 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
         return CK_OK;
     std::lock_guard<std::mutex> lk(M.mu);
     if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_MERGE) {
-        // the merge-path partition of the matrix, searched once instead of by
-        // every workgroup of every product
-        if (M.has_merge_part.load())
+        // the merge-path plan of the matrix, made once instead of searched by
+        // every workgroup and thread of every product
+        if (M.has_merge_plan.load())
             return CK_OK;
-        CK_TRY(mat_alloc(M, &M.merge_part, merge_part_entries(M), s));
-        CK_TRY(launch_merge_partition(M, M.merge_part, s));
-        return mark_built(M.has_merge_part, s);
+        if (!M.merge_plan)
+            CK_TRY(mat_alloc(M, &M.merge_plan, merge_plan_ints(M.n, M.nnz), s));
+        CK_TRY(build_merge_plan(M.n, M.nnz, M.rp, M.merge_plan, &M.merge_cut, s));
+        return mark_built(M.has_merge_plan, s);
     }
     if (c.format == CK_FMT_CSR) {   // CSR-panel
         if (M.has_panel.load())
@@ -165,9 +166,13 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             st = panel_make_rows(M, tmp, s);   // only the non-empty panel rows, if that pays
         const int64_t R = M.panel_rows;
         if (st == CK_OK)
-            st = mat_alloc(M, &M.panel_part, merge_part_entries_rows(R, M.nnz), s);
+            st = mat_alloc(M, &M.panel_plan, merge_plan_ints(R, M.nnz), s);
         if (st == CK_OK)
-            st = launch_merge_partition_rows(R, M.nnz, M.panel_rp, M.panel_part, s);
+            st = build_merge_plan(R, M.nnz, M.panel_rp, M.panel_plan, &M.panel_cut, s);
+        if (st == CK_OK) {   // products read the plan, not the row pointers
+            mat_free(M, M.panel_rp);
+            M.panel_rp = nullptr;
+        }
         if (st == CK_OK)
             st = mark_built(M.has_panel, s);
         (void)hipStreamSynchronize(s);   // the conversion has finished with tmp
@@ -556,8 +561,10 @@ ck_status spmv_apply(ck_handle h, const ck_config *cfg, double alpha, const doub
 // GPU for the life of the process.  In host code `scratch` only names the
 // symbol; its device address on the current GPU comes from
 // hipGetSymbolAddress, looked up once per device and kept.
+// Calls are admitted by spmv_noalloc_bytes against the first 64 MiB; the
+// mebibyte after them holds what a panel product's carries take beyond that.
 constexpr int64_t kNoAllocScratchBytes = int64_t(64) << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + (1 << 20)];
 
 static std::mutex g_scratch_mu;
 static std::map<int, void *> g_scratch_ptr;   // device -> address of its `scratch`
@@ -594,7 +601,7 @@ ck_status spmv_apply_noalloc(ck_handle h, const ck_config *cfg, double alpha, co
                          (c.format == CK_FMT_CSR &&
                           (c.algorithm == CK_ALG_MERGE || c.algorithm == CK_ALG_PANEL));
     if (carries && h->n > 0) {
-        const int64_t need = spmv_carry_bytes(*h, c, false);
+        const int64_t need = spmv_noalloc_bytes(*h, c);
         if (need > kNoAllocScratchBytes)
             return fail(CK_E_UNSUPPORTED,
                         "spmv_apply_noalloc: %s needs %lld bytes of workspace for this matrix, "

@@ -152,6 +152,22 @@ __device__ __forceinline__ T wave_seg_scan(T v, int key) {
     return v;
 }
 
+// Inclusive sum of v over the lanes of a wave up to each lane, by the steps of
+// wave_seg_scan.
+template <int CTRL, int RM>
+__device__ __forceinline__ void scan_step(int &v) {
+    v += __builtin_amdgcn_update_dpp(0, v, CTRL, RM, 0xf, true);
+}
+__device__ __forceinline__ int wave_scan(int v) {
+    scan_step<0x111, 0xf>(v);
+    scan_step<0x112, 0xf>(v);
+    scan_step<0x114, 0xf>(v);
+    scan_step<0x118, 0xf>(v);
+    scan_step<0x142, 0xa>(v);
+    scan_step<0x143, 0xc>(v);
+    return v;
+}
+
 // Sum over groups of L consecutive lanes (L a power of two <= 64) by DPP
 // register moves, valid in lane L - 1 of each group (for L <= 16 in every
 // lane of the group): lanes exchange with lane ^ 1 and lane ^ 2 (quad

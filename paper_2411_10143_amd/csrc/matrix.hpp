@@ -44,12 +44,15 @@ struct ck_matrix {
     double *panel_val = nullptr;
     float *panel_val32 = nullptr;
     std::atomic<bool> has_panel{false};
-    // merge-path partition of the panel-major arrays read as one CSR of P*n rows
-    int32_t *panel_part = nullptr;
-    // merge-path partition (after conversion to CSR-merge): merge_part[q] =
-    // rows whose end lies among the first min(2048 q, n + nnz) merged items
-    int32_t *merge_part = nullptr;
-    std::atomic<bool> has_merge_part{false};
+    // merge-path plan of the panel-major arrays read as one CSR of panel_rows rows
+    int32_t *panel_plan = nullptr;
+    bool panel_cut = true;
+    // merge-path plan (after conversion to CSR-merge): where every workgroup
+    // starts and which merged items are row ends (merge_plan_ints); cut =
+    // some workgroup starts inside a row
+    int32_t *merge_plan = nullptr;
+    bool merge_cut = true;
+    std::atomic<bool> has_merge_plan{false};
     // DIA (after conversion): dia_nd offsets (col - row, ascending), values
     // diagonal-major: diagonal k of row i at k*dia_pitch + i, absent = +0.0
     int32_t *dia_off = nullptr;
@@ -118,13 +121,15 @@ bool spmv_fuses_dot(const ck_config &c);
 int64_t spmv_dot_blocks(const ck_matrix &M, const ck_config &c);
 // Bytes of carry workspace a launch needs (0 if none).
 int64_t spmv_carry_bytes(const ck_matrix &M, const ck_config &c, bool fp32);
-// Merge-path partition: entries of merge_part, and its launch (stream-ordered).
-int64_t merge_part_entries(const ck_matrix &M);
-ck_status launch_merge_partition(const ck_matrix &M, int32_t *part, hipStream_t s);
-// The same for any CSR of `rows` rows (used for the panel-major arrays).
-int64_t merge_part_entries_rows(int64_t rows, int64_t nnz);
-ck_status launch_merge_partition_rows(int64_t rows, int64_t nnz, const int32_t *rp,
-                                      int32_t *part, hipStream_t s);
+// The bytes spmv_apply_noalloc admits against its fixed array: the size with
+// 2048 merged items per panel-product workgroup.  A launch's carries take up
+// to 3.3 % more (its workgroups start up to 64 items early).
+int64_t spmv_noalloc_bytes(const ck_matrix &M, const ck_config &c);
+// Merge-path plan of a CSR of `rows` rows (the matrix, or the panel-major
+// arrays): its size in ints, and building it (returns when it is built).
+int64_t merge_plan_ints(int64_t rows, int64_t nnz);
+ck_status build_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
+                           bool *cut, hipStream_t s);
 
 template <typename T>
 ck_status launch_spmv(const ck_matrix &M, const ck_config &c, const SpmvArgs<T> &a,

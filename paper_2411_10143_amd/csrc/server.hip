@@ -130,8 +130,11 @@ int64_t handle_bytes(const ck_matrix &M) {
     if (M.has_hyb.load())
         b += 4 * M.hyb_nt + M.hyb_K * M.hyb_pitch * (12 + (M.hyb_val32 ? 4 : 0));
     if (M.has_panel.load())
-        b += 4 * (M.panel_rows + 1) + M.nnz * (12 + (M.panel_val32 ? 4 : 0)) +
-             (M.panel_row ? 4 * M.panel_rows + 4 * (int64_t)M.panel_P * (M.panel_B + 1) : 0);
+        b += M.nnz * (12 + (M.panel_val32 ? 4 : 0)) +
+             (M.panel_row ? 4 * M.panel_rows + 4 * (int64_t)M.panel_P * (M.panel_B + 1) : 0) +
+             4 * merge_plan_ints(M.panel_rows, M.nnz);
+    if (M.has_merge_plan.load())
+        b += 4 * merge_plan_ints(M.n, M.nnz);
     return b;
 }
 
@@ -160,7 +163,7 @@ int64_t converted_bytes(const ck_features &F, const ck_config &c, bool fp32) {
         return 4 * (P * n + 1) + nnz * (4 + vb) + 8 * (P * n + 1) + tmp;
     }
     if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_MERGE)
-        return 4 * ((n + nnz) / 1024 + 2) + tmp;
+        return 4 * merge_plan_ints(n, nnz) + tmp;
     return 0;
 }
 

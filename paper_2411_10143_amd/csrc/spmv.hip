@@ -24,13 +24,18 @@
 // contiguous slice of rows (its L2 then holds the x entries that slice uses).
 // Every reduction has a fixed order, so a configuration always returns the
 // same bits for the same input.
+#include <algorithm>
+
 #include "diahyb.hpp"
 #include "matrix.hpp"
 #include "panel.hpp"
+#include "solvers.hpp"
 
 using ck::ld_stream;
 
 constexpr int kMergeIPT = 8;   // merged items per thread  (2048 per workgroup)
+constexpr int kMergeSlack = 64;   // items a workgroup may start before its nominal start
+constexpr int kMergeSpan = 256 * kMergeIPT - kMergeSlack;   // merged items between nominal starts
 constexpr int kCooIPT = 8;     // entries per thread       (2048 per workgroup)
 constexpr int kScalarCap = 4096;  // products staged per LDS chunk (CSR-scalar)
 
@@ -250,7 +255,24 @@ __global__ __launch_bounds__(256) void spmv_hyb_ell(int n, int64_t G, int K, int
     ell_rows<T, BETA, false>(n, G, K, pitch, ecol, evl, alpha, x, beta, y, nullptr, nullptr);
 }
 
-// ---- carry completion shared by merge-path and COO -------------------------
+// Sum of the partials of the run of equal s_crow ending at thread p (s_cval
+// holds each wave's segmented scan): its wave's part, then the runs ending
+// each earlier wave while the run goes on.
+template <typename T>
+__device__ __forceinline__ T carry_run(const int *s_crow, const T *s_cval, int p) {
+    const int key = s_crow[p];
+    T tot = s_cval[p];
+    for (int u = (p >> 6) - 1; u >= 0; --u) {
+        if (s_crow[64 * u + 63] != key)
+            break;
+        tot += s_cval[64 * u + 63];
+        if (s_crow[64 * u] != key)
+            break;
+    }
+    return tot;
+}
+
+// ---- carry completion of COO -------------------------------------------------
 // Every thread passes the row it ended inside (crow, -1 if none) with its
 // partial (cval), and the first row it completed (frow, -1 if none) with its
 // own part of that row (fval).  Across the workgroup, equal crow values form
@@ -271,22 +293,10 @@ __device__ __forceinline__ void finish_carries(int *s_crow, T *s_cval, int crow,
     s_crow[tid] = crow;
     s_cval[tid] = ck::wave_seg_scan(cval, crow);
     __syncthreads();
-    // sum of the partials of the run ending at thread p: its wave's part,
-    // then the runs ending each earlier wave while the run goes on
-    auto run_to = [&](int p) {
-        const int key = s_crow[p];
-        T tot = s_cval[p];
-        for (int u = (p >> 6) - 1; u >= 0; --u) {
-            if (s_crow[64 * u + 63] != key)
-                break;
-            tot += s_cval[64 * u + 63];
-            if (s_crow[64 * u] != key)
-                break;
-        }
-        return tot;
-    };
     if (frow >= 0) {
-        T tot = tid > 0 && s_crow[tid - 1] == frow ? run_to(tid - 1) : T(0);
+        T tot = tid > 0 && s_crow[tid - 1] == frow
+                    ? carry_run(s_crow, s_cval, tid - 1)
+                    : T(0);
         tot += fval;
         T out = alpha * tot;
         if (BETA)
@@ -296,154 +306,241 @@ __device__ __forceinline__ void finish_carries(int *s_crow, T *s_cval, int crow,
     if (tid == 0) {
         const int R = last_active >= 0 ? s_crow[last_active] : -1;
         crow_g[b] = R;
-        cval_g[b] = R >= 0 ? run_to(last_active) : T(0);
+        cval_g[b] = R >= 0 ? carry_run(s_crow, s_cval, last_active) : T(0);
     }
 }
 
-// part[q] = merge-path row coordinate of item min(2048 q, n + nnz): the
-// number of row ends among those first items (binary search on the row ends).
-__global__ __launch_bounds__(256) void merge_partition(int n, int nnz, int64_t Q,
-                                                       const int *__restrict__ rp,
-                                                       int *__restrict__ part) {
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= Q)
-        return;
-    const int64_t d = min<int64_t>(q * 256 * kMergeIPT, (int64_t)n + nnz);
+// Merge-path coordinates (row ends, entries) where workgroup q starts.  The
+// nominal start is merged item kMergeSpan q; when the row it falls into has
+// at most kMergeSlack entries before it, the workgroup starts at that row
+// instead, so a matrix with no row longer than kMergeSlack has no row cut by
+// a workgroup boundary and needs no carry_fixup.  A workgroup covers at most
+// kMergeSpan + kMergeSlack = 256 kMergeIPT items.
+__device__ __forceinline__ int2 merge_start(int n, int nnz, const int *__restrict__ rp,
+                                            int64_t q) {
+    const int64_t d = min<int64_t>(q * kMergeSpan, (int64_t)n + nnz);
     int lo = (int)max<int64_t>(0, d - nnz), hi = (int)min<int64_t>(d, n);
-    while (lo < hi) {
+    while (lo < hi) {   // row ends among the first d items
         const int mid = (lo + hi) >> 1;
         if ((int64_t)rp[mid + 1] <= d - mid - 1)
             lo = mid + 1;
         else
             hi = mid;
     }
-    part[q] = lo;
+    int j = (int)(d - lo);
+    if (lo < n && j - rp[lo] <= kMergeSlack)
+        j = rp[lo];
+    return make_int2(lo, j);
 }
 
-// Merge-path CSR.  Workgroup b owns merged items [2048 b, 2048 (b+1)) of the
-// merge of the row ends rp[1..n] with the entries 0..nnz-1.  Its start and
-// end coordinates come from the matrix's cached partition (built by the
-// conversion to CSR-merge), else two threads search them; it then stages the
-// row ends it crosses and the products val[j] * x[col[j]] of the entries it
-// covers in LDS with coalesced loads (eight gathers per thread in flight), and
-// every thread walks its eight items from LDS after a local merge-path search.
-// Rows cut by thread boundaries are completed in LDS, rows cut by workgroup
-// boundaries by carry_fixup.
-template <typename T, bool BETA>
-__device__ __forceinline__ void merge_rows(int n, int nnz, int64_t G, const int *__restrict__ rp,
-                                           const int *__restrict__ col,
-                                           const T *__restrict__ val, T alpha,
-                                           const T *__restrict__ x, T beta, T *__restrict__ y,
-                                           int *__restrict__ crow_g, T *__restrict__ cval_g,
-                                           const int *__restrict__ part) {
-    constexpr int ITEMS = 256 * kMergeIPT;
-    __shared__ int s_crow[256];
-    __shared__ T s_cval[256];
-    __shared__ int s_rend[ITEMS + 1];   // ends of rows i0 .. i1 (local entry index + j0)
-    __shared__ T s_prod[ITEMS];         // products of entries j0 .. j1-1
-    __shared__ int s_coord[4];
-    const int64_t b = ck::xcd_block(G);
-    if (b < 0)
-        return;
-    const int tid = threadIdx.x;
-    const int64_t P = (int64_t)n + nnz;
-    const int64_t D0 = b * ITEMS;
-    const int64_t D1 = min(D0 + ITEMS, P);
-    if (tid < 2) {   // merge-path coordinates of D0 (thread 0) and D1 (thread 1)
-        const int64_t d = tid == 0 ? D0 : D1;
-        int i;
-        if (part != nullptr) {   // the matrix's cached partition
-            i = part[b + tid];
-        } else {
-            int lo = (int)max<int64_t>(0, d - nnz), hi = (int)min<int64_t>(d, n);
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if ((int64_t)rp[mid + 1] <= d - mid - 1)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            i = lo;
+// part[q] = the coordinates of workgroup q = 0 .. G (G: the end).
+__global__ __launch_bounds__(256) void merge_partition(int n, int nnz, int64_t G,
+                                                       const int *__restrict__ rp,
+                                                       int2 *__restrict__ part) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q <= G)
+        part[q] = merge_start(n, nnz, rp, q);
+}
+
+// The merged sequence as one bit per item, 1 = row end: byte t of workgroup
+// q holds thread t's items D0 + 8 t .. D0 + 8 t + 7, items past the
+// workgroup's end 0.  *cut = 1 if a workgroup starts inside a row.
+__global__ __launch_bounds__(256) void merge_bits(int n, int64_t G, const int *__restrict__ rp,
+                                                  const int2 *__restrict__ part,
+                                                  unsigned *__restrict__ bits,
+                                                  int *__restrict__ cut) {
+    static_assert(kMergeIPT == 8, "one byte of row-end bits per thread");
+    __shared__ unsigned w[64];
+    for (int64_t q = blockIdx.x; q < G; q += gridDim.x) {
+        if (threadIdx.x < 64)
+            w[threadIdx.x] = 0;
+        __syncthreads();
+        const int2 c0 = part[q], c1 = part[q + 1];
+        for (int r = c0.x + threadIdx.x; r < c1.x; r += 256) {
+            const int at = rp[r + 1] - c0.y + (r - c0.x);
+            atomicOr(&w[at >> 5], 1u << (at & 31));
         }
-        s_coord[2 * tid] = i;
-        s_coord[2 * tid + 1] = (int)(d - i);
+        __syncthreads();
+        if (threadIdx.x < 64)
+            bits[64 * q + threadIdx.x] = w[threadIdx.x];
+        if (threadIdx.x == 0 && c0.x < n && c0.y != rp[c0.x])
+            *cut = 1;
     }
-    __syncthreads();
-    const int i0 = s_coord[0], j0 = s_coord[1], i1 = s_coord[2], j1 = s_coord[3];
-    const int nrows = i1 - i0 + 1;   // rows i0 .. i1 (i1 may be n)
-    const int nents = j1 - j0;
-    for (int t = tid; t < nrows; t += 256)
-        s_rend[t] = i0 + t < n ? rp[i0 + t + 1] : nnz;
-    for (int t0 = 0; t0 < nents; t0 += 256 * kMergeIPT) {
-        int cc[kMergeIPT];
-        T vv[kMergeIPT], xv[kMergeIPT];
+}
+
+// LDS slot of staged product e: one slot of padding per eight, so the threads
+// of a wave, whose reads are about eight slots apart, use different banks.
+__device__ __forceinline__ int pad8(int e) { return e + (e >> 3); }
+
+// The products of the workgroup's entries j0 .. j0 + nents - 1 into LDS
+// (coalesced loads, eight gathers per thread in flight), zeros after them.
+template <typename T>
+__device__ __forceinline__ void stage_products(int j0, int nents, const int *__restrict__ col,
+                                               const T *__restrict__ val,
+                                               const T *__restrict__ x, T *s_prod) {
+    const int tid = threadIdx.x;
+    int cc[kMergeIPT];
+    T vv[kMergeIPT], xv[kMergeIPT];
+    if (nents > 0) {
+        const int *colb = col + j0;
+        const T *valb = val + j0;
 #pragma unroll
         for (int u = 0; u < kMergeIPT; ++u) {
-            const int t = min(t0 + u * 256 + tid, nents - 1);
-            cc[u] = ld_stream(&col[j0 + t]);
-            vv[u] = ld_stream(&val[j0 + t]);
+            const int t = min(u * 256 + tid, nents - 1);
+            cc[u] = ld_stream(&colb[t]);
+            vv[u] = ld_stream(&valb[t]);
         }
 #pragma unroll
         for (int u = 0; u < kMergeIPT; ++u)
             xv[u] = x[cc[u]];
         __builtin_amdgcn_sched_barrier(0);   // all gathers in flight before the first use
-#pragma unroll
-        for (int u = 0; u < kMergeIPT; ++u)
-            if (t0 + u * 256 + tid < nents)
-                s_prod[t0 + u * 256 + tid] = vv[u] * xv[u];
     }
-    __syncthreads();
-    int crow = -1, frow = -1;
-    T cval = 0, fval = 0;
-    const int dl = tid * kMergeIPT;   // this thread's first local item
-    if (D0 + dl < D1) {
-        const int dle = (int)min<int64_t>(dl + kMergeIPT, D1 - D0);
-        // local merge-path search: a = row ends among the block's first dl items
-        int lo = max(0, dl - nents), hi = min(dl, nrows - 1);
+#pragma unroll
+    for (int u = 0; u < kMergeIPT; ++u) {
+        const int t = u * 256 + tid;
+        s_prod[pad8(t)] = t < nents ? vv[u] * xv[u] : T(0);
+    }
+}
+
+// Merge-path CSR.  Workgroup b owns at most 2048 merged items: the merge of
+// the row ends rp[1..n] with the entries 0..nnz-1 between the coordinates of
+// merge_start.  It stages the products of its entries in LDS; every thread
+// then sums its eight items: entries add to the running row, row ends close
+// it.  Which items are row ends comes from the matrix's plan (part and bits,
+// built by the conversion), so a thread needs no search and no row pointers,
+// its eight products are read together, and its place in the rows is a
+// prefix sum of bit counts; without a plan (a product before any conversion)
+// two threads search the workgroup's coordinates and every thread searches
+// its own start in LDS, with the same items per thread and so the same bits.
+// Rows cut by thread boundaries are completed in LDS, rows cut by workgroup
+// boundaries by carry_fixup; the finished rows leave LDS in row order.
+//
+// Bound by the L2 requests of the x gathers (one line each, about 190 G/s).
+// Searching and walking the merged items in LDS, eight slots apart without
+// padding (16-way bank conflicts), and a carry_fixup per product cost on top
+// of them; whole products before -> now: FP32 uniform rows, n = 180K (all of
+// x in every L2): 40.7 -> 34.6 us; CSR-panel, uniform rows, n = 2M: 486 ->
+// 410 us; CSR-panel, power-law rows, n = 1.2M: 229 -> 205 us.
+template <typename T, bool BETA, bool PLAN>
+__device__ __forceinline__ void merge_rows(int n, int nnz, int64_t G, const int *__restrict__ rp,
+                                           const int *__restrict__ col,
+                                           const T *__restrict__ val, T alpha,
+                                           const T *__restrict__ x, T beta, T *__restrict__ y,
+                                           int *__restrict__ crow_g, T *__restrict__ cval_g,
+                                           const int2 *__restrict__ part,
+                                           const unsigned char *__restrict__ bits) {
+    constexpr int ITEMS = 256 * kMergeIPT;
+    __shared__ int s_crow[256];
+    __shared__ T s_cval[256];
+    __shared__ T s_prod[ITEMS + ITEMS / 8];   // the products, then the row sums
+    __shared__ int s_rend[PLAN ? 1 : ITEMS + 1];
+    __shared__ int s_wave[4];
+    __shared__ int2 s_coord[2];
+    const int64_t b = ck::xcd_block(G);
+    if (b < 0)
+        return;
+    const int tid = threadIdx.x;
+    int2 c0, c1;
+    unsigned mask = 0;   // this thread's row ends
+    if constexpr (PLAN) {
+        c0 = part[b];
+        c1 = part[b + 1];
+        mask = bits[b * 256 + tid];
+    } else {
+        if (tid < 2)
+            s_coord[tid] = merge_start(n, nnz, rp, b + tid);
+        __syncthreads();
+        c0 = s_coord[0];
+        c1 = s_coord[1];
+    }
+    const int i0 = c0.x, nends = c1.x - c0.x, nents = c1.y - c0.y;
+    const int items = nends + nents;
+    if constexpr (!PLAN)
+        for (int t = tid; t <= nends; t += 256)
+            s_rend[t] = i0 + t < n ? rp[i0 + t + 1] - c0.y : nents;
+    stage_products<T>(c0.y, nents, col, val, x, s_prod);
+    const int dl = tid * kMergeIPT;   // this thread's first item
+    int a;                            // row ends before it
+    if constexpr (PLAN) {
+        const int pc = __popc(mask);
+        const int sc = ck::wave_scan(pc);
+        if ((tid & 63) == 63)
+            s_wave[tid >> 6] = sc;
+        __syncthreads();
+        a = sc - pc;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+            a += w < wave ? s_wave[w] : 0;
+    } else {
+        __syncthreads();
+        int lo = max(0, dl - nents), hi = min(dl, nends);
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (s_rend[mid] - j0 <= dl - mid - 1)
+            if (s_rend[mid] <= dl - mid - 1)
                 lo = mid + 1;
             else
                 hi = mid;
         }
-        int a = lo;
+        a = lo;
         int e = dl - lo;
-        int rend = s_rend[a] - j0;
-        T acc = 0;
-        bool first = true;
-        for (int d = dl; d < dle; ++d) {
-            if (e < rend) {
-                acc += s_prod[e];
-                ++e;
+#pragma unroll
+        for (int d = 0, r = lo; d < kMergeIPT; ++d) {
+            if (r < nends && s_rend[r] <= e) {
+                mask |= 1u << d;
+                ++r;
             } else {
-                const int i = i0 + a;
-                if (first) {
-                    frow = i;
-                    fval = acc;
-                    first = false;
-                } else {
-                    T out = alpha * acc;
-                    if (BETA)
-                        out += beta * y[i];
-                    y[i] = out;
-                }
-                acc = 0;
-                ++a;
-                rend = s_rend[a] - j0;
+                ++e;
             }
         }
-        crow = i0 + a < n ? i0 + a : -1;
-        cval = acc;
     }
-    const int64_t first_d = b * 256 * kMergeIPT;
-    const int last_active =
-        (int)min<int64_t>(255, (P - first_d + kMergeIPT - 1) / kMergeIPT - 1);
-    finish_carries<T, BETA>(s_crow, s_cval, crow, cval, frow, fval, last_active, b, alpha, beta,
-                            y, crow_g, cval_g);
+    T v[kMergeIPT];   // item d: its product, or the sum of the row it ends
+#pragma unroll
+    for (int d = 0; d < kMergeIPT; ++d) {
+        const int e = dl - a + d - __popc(mask & ((1u << d) - 1));
+        v[d] = s_prod[pad8(e)];   // e < 2048: items are in order
+    }
+    T acc = 0;
+#pragma unroll
+    for (int d = 0; d < kMergeIPT; ++d) {
+        if (mask & (1u << d)) {
+            v[d] = acc;
+            acc = 0;
+        } else {
+            acc += v[d];
+        }
+    }
+    const int after = a + __popc(mask);   // the row this thread ends in
+    const int crow = dl < items && i0 + after < n ? i0 + after : -1;
+    s_crow[tid] = crow;
+    s_cval[tid] = ck::wave_seg_scan(acc, crow);
+    __syncthreads();   // also: every product has been read
+    bool first = true;
+    int r = a;
+#pragma unroll
+    for (int d = 0; d < kMergeIPT; ++d)
+        if (mask & (1u << d)) {
+            if (first && tid > 0 && s_crow[tid - 1] == i0 + a)
+                v[d] = carry_run(s_crow, s_cval, tid - 1) + v[d];
+            s_prod[r++] = v[d];
+            first = false;
+        }
+    if (tid == 0) {   // the row the workgroup ends in
+        const int last = (items + kMergeIPT - 1) / kMergeIPT - 1;
+        const int R = last >= 0 ? s_crow[last] : -1;
+        crow_g[b] = R;
+        cval_g[b] = R >= 0 ? carry_run(s_crow, s_cval, last) : T(0);
+    }
+    __syncthreads();
+    for (int t = tid; t < nends; t += 256) {
+        T out = alpha * s_prod[t];
+        if (BETA)
+            out += beta * y[i0 + t];
+        y[i0 + t] = out;
+    }
 }
 
-template <typename T, bool BETA>
+template <typename T, bool BETA, bool PLAN>
 __global__ __launch_bounds__(256) void spmv_merge(int n, int nnz, int64_t G,
                                                   const int *__restrict__ rp,
                                                   const int *__restrict__ col,
@@ -451,11 +548,13 @@ __global__ __launch_bounds__(256) void spmv_merge(int n, int nnz, int64_t G,
                                                   const T *__restrict__ x, T beta,
                                                   T *__restrict__ y, int *__restrict__ crow_g,
                                                   T *__restrict__ cval_g,
-                                                  const int *__restrict__ part,
+                                                  const int2 *__restrict__ part,
+                                                  const unsigned char *__restrict__ bits,
                                                   const int *__restrict__ skip) {
     if (skipped(skip))
         return;
-    merge_rows<T, BETA>(n, nnz, G, rp, col, val, alpha, x, beta, y, crow_g, cval_g, part);
+    merge_rows<T, BETA, PLAN>(n, nnz, G, rp, col, val, alpha, x, beta, y, crow_g, cval_g, part,
+                              bits);
 }
 
 // CSR-panel products: the merge path over the panel-major arrays read as one
@@ -463,19 +562,19 @@ __global__ __launch_bounds__(256) void spmv_merge(int n, int nnz, int64_t G,
 // it apart from CSR-merge).
 template <typename T>
 __global__ __launch_bounds__(256) void spmv_panel_merge(int rows, int nnz, int64_t G,
-                                                        const int *__restrict__ prp,
                                                         const int *__restrict__ pcol,
                                                         const T *__restrict__ pval,
                                                         const T *__restrict__ x,
                                                         T *__restrict__ ypart,
                                                         int *__restrict__ crow_g,
                                                         T *__restrict__ cval_g,
-                                                        const int *__restrict__ part,
+                                                        const int2 *__restrict__ part,
+                                                        const unsigned char *__restrict__ bits,
                                                         const int *__restrict__ skip) {
     if (skipped(skip))
         return;
-    merge_rows<T, false>(rows, nnz, G, prp, pcol, pval, T(1), x, T(0), ypart, crow_g, cval_g,
-                         part);
+    merge_rows<T, false, true>(rows, nnz, G, nullptr, pcol, pval, T(1), x, T(0), ypart, crow_g,
+                               cval_g, part, bits);
 }
 
 template <typename T, bool BETA>
@@ -658,8 +757,13 @@ static int64_t carry_blocks(const ck_matrix &M, const ck_config &c) {
     if (c.format == CK_FMT_COO)
         return ceil_div(M.nnz, 256 * kCooIPT);
     if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_MERGE)
-        return ceil_div(M.n + M.nnz, 256 * kMergeIPT);
+        return ceil_div(M.n + M.nnz, kMergeSpan);
     return 0;
+}
+
+// Carries of G workgroups, each array at a multiple of 256 bytes.
+static int64_t carry_array_bytes(int64_t G, bool fp32) {
+    return ((G * (int64_t)sizeof(int) + 255) / 256) * 256 + G * (fp32 ? 4 : 8) + 256;
 }
 
 int64_t spmv_carry_bytes(const ck_matrix &M, const ck_config &c, bool fp32) {
@@ -669,31 +773,52 @@ int64_t spmv_carry_bytes(const ck_matrix &M, const ck_config &c, bool fp32) {
         // bound: the row-list layout has fewer rows, and the size is also
         // needed before the conversion decides)
         const int64_t rows = (int64_t)panel_count_for(M.ncols, 8) * M.n;
-        const int64_t Gt = ceil_div(rows + M.nnz, 256 * kMergeIPT);
         return ((rows * (fp32 ? 4 : 8) + 255) / 256) * 256 +
-               ((Gt * (int64_t)sizeof(int) + 255) / 256) * 256 + Gt * (fp32 ? 4 : 8) + 256;
+               carry_array_bytes(ceil_div(rows + M.nnz, kMergeSpan), fp32);
     }
-    const int64_t G = carry_blocks(M, c);
-    return ((G * (int64_t)sizeof(int) + 255) / 256) * 256 + G * (fp32 ? 4 : 8) + 256;
+    return carry_array_bytes(carry_blocks(M, c), fp32);
 }
 
-int64_t merge_part_entries_rows(int64_t rows, int64_t nnz) {
-    return ceil_div(rows + nnz, 256 * kMergeIPT) + 1;
+int64_t spmv_noalloc_bytes(const ck_matrix &M, const ck_config &c) {
+    int64_t b = spmv_carry_bytes(M, c, false);
+    if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL) {
+        const int64_t items = (int64_t)panel_count_for(M.ncols, 8) * M.n + M.nnz;
+        b += carry_array_bytes(ceil_div(items, 256 * kMergeIPT), false) -
+             carry_array_bytes(ceil_div(items, kMergeSpan), false);
+    }
+    return b;
 }
 
-int64_t merge_part_entries(const ck_matrix &M) { return merge_part_entries_rows(M.n, M.nnz); }
+// ---- merge-path plan: G + 1 coordinate pairs, 64 words of row-end bits per
+// workgroup, and the cut flag --------------------------------------------------
+static int64_t plan_blocks(int64_t rows, int64_t nnz) { return ceil_div(rows + nnz, kMergeSpan); }
 
-ck_status launch_merge_partition_rows(int64_t rows, int64_t nnz, const int32_t *rp,
-                                      int32_t *part, hipStream_t s) {
-    const int64_t Q = merge_part_entries_rows(rows, nnz);
-    hipLaunchKernelGGL(merge_partition, dim3(ceil_div(Q, 256)), dim3(256), 0, s, (int)rows,
-                       (int)nnz, Q, rp, part);
+int64_t merge_plan_ints(int64_t rows, int64_t nnz) {
+    const int64_t G = plan_blocks(rows, nnz);
+    return 2 * (G + 1) + 64 * G + 1;
+}
+
+static const unsigned char *plan_bits(const int32_t *plan, int64_t G) {
+    return (const unsigned char *)(plan + 2 * (G + 1));
+}
+
+ck_status build_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
+                           bool *cut, hipStream_t s) {
+    const int64_t G = plan_blocks(rows, nnz);
+    int2 *part = (int2 *)plan;
+    int *flag = plan + 2 * (G + 1) + 64 * G;
+    CK_TRY(launch_fill<int>(1, flag, 0, s));
+    hipLaunchKernelGGL(merge_partition, dim3(ceil_div(G + 1, 256)), dim3(256), 0, s, (int)rows,
+                       (int)nnz, G, rp, part);
+    if (G > 0)
+        hipLaunchKernelGGL(merge_bits, dim3(std::min<int64_t>(G, 16384)), dim3(256), 0, s,
+                           (int)rows, G, rp, part, (unsigned *)(plan + 2 * (G + 1)), flag);
     CK_HIP(hipGetLastError());
+    int h = 0;
+    CK_HIP(hipMemcpyAsync(&h, flag, sizeof h, hipMemcpyDeviceToHost, s));
+    CK_HIP(hipStreamSynchronize(s));
+    *cut = h != 0;
     return CK_OK;
-}
-
-ck_status launch_merge_partition(const ck_matrix &M, int32_t *part, hipStream_t s) {
-    return launch_merge_partition_rows(M.n, M.nnz, M.rp, part, s);
 }
 
 ck_config default_config(int64_t n, int64_t nnz) {
@@ -728,7 +853,7 @@ const char *kernel_name(const ck_config &c, bool fp32) {
     if (c.algorithm == CK_ALG_SCALAR)
         return fp32 ? "spmv_csr_scalar<float, false, false>" : "spmv_csr_scalar<double, false, false>";
     if (c.algorithm == CK_ALG_MERGE)
-        return fp32 ? "spmv_merge<float, false>" : "spmv_merge<double, false>";
+        return fp32 ? "spmv_merge<float, false, true>" : "spmv_merge<double, false, true>";
     if (c.algorithm == CK_ALG_PANEL)
         return fp32 ? "spmv_panel_merge<float>" : "spmv_panel_merge<double>";
     int idx = 0;
@@ -830,17 +955,25 @@ static ck_status dispatch_carry(const ck_matrix &M, const ck_config &c, const Sp
     }
     int *crow = (int *)ws;
     T *cval = (T *)((char *)ws + ((G * (int64_t)sizeof(int) + 255) / 256) * 256);
-    if (c.format == CK_FMT_COO)
+    bool cut = true;   // rows may be cut by a workgroup boundary
+    if (c.format == CK_FMT_COO) {
         hipLaunchKernelGGL((spmv_coo<T, BETA>), dim3(xcd_grid(G)), dim3(256), 0, s, (int)M.n,
                            (int)M.nnz, G, M.coo_row, M.col, values<T>(M), a.alpha, a.x, a.beta,
                            a.y, crow, cval, a.skip);
-    else
-        hipLaunchKernelGGL((spmv_merge<T, BETA>), dim3(xcd_grid(G)), dim3(256), 0, s, (int)M.n,
-                           (int)M.nnz, G, M.rp, M.col, values<T>(M), a.alpha, a.x, a.beta, a.y,
-                           crow, cval, M.has_merge_part.load() ? M.merge_part : nullptr,
-                           a.skip);
-    hipLaunchKernelGGL((carry_fixup<T>), dim3(ceil_div(G, 256)), dim3(256), 0, s, G, crow, cval,
-                       a.alpha, a.y, a.skip);
+    } else if (M.has_merge_plan.load()) {
+        cut = M.merge_cut;
+        hipLaunchKernelGGL((spmv_merge<T, BETA, true>), dim3(xcd_grid(G)), dim3(256), 0, s,
+                           (int)M.n, (int)M.nnz, G, M.rp, M.col, values<T>(M), a.alpha, a.x,
+                           a.beta, a.y, crow, cval, (const int2 *)M.merge_plan,
+                           plan_bits(M.merge_plan, G), a.skip);
+    } else {
+        hipLaunchKernelGGL((spmv_merge<T, BETA, false>), dim3(xcd_grid(G)), dim3(256), 0, s,
+                           (int)M.n, (int)M.nnz, G, M.rp, M.col, values<T>(M), a.alpha, a.x,
+                           a.beta, a.y, crow, cval, nullptr, nullptr, a.skip);
+    }
+    if (cut)
+        hipLaunchKernelGGL((carry_fixup<T>), dim3(ceil_div(G, 256)), dim3(256), 0, s, G, crow,
+                           cval, a.alpha, a.y, a.skip);
     if (own)
         CK_HIP(hipFreeAsync(ws, s));
     return CK_OK;
@@ -863,16 +996,17 @@ static ck_status panel_merge_spmv(const ck_matrix &M, const SpmvArgs<T> &a, void
     else
         pv = M.panel_val;
     const int64_t rows = M.panel_rows;   // P*n, or the non-empty panel rows
-    const int64_t Gt = ceil_div(rows + M.nnz, 256 * kMergeIPT);
+    const int64_t Gt = plan_blocks(rows, M.nnz);
     T *ypart = (T *)ws;
     int *crow = (int *)((char *)ws + ((rows * (int64_t)sizeof(T) + 255) / 256) * 256);
     T *cval = (T *)((char *)crow + ((Gt * (int64_t)sizeof(int) + 255) / 256) * 256);
     if (Gt > 0) {   // no panel rows at all (no entries, row-list layout): combine only
         hipLaunchKernelGGL((spmv_panel_merge<T>), dim3(xcd_grid(Gt)), dim3(256), 0, s, (int)rows,
-                           (int)M.nnz, Gt, M.panel_rp, M.panel_col, pv, a.x, ypart, crow, cval,
-                           M.panel_part, a.skip);
-        hipLaunchKernelGGL((carry_fixup<T>), dim3(ceil_div(Gt, 256)), dim3(256), 0, s, Gt, crow,
-                           cval, T(1), ypart, a.skip);
+                           (int)M.nnz, Gt, M.panel_col, pv, a.x, ypart, crow, cval,
+                           (const int2 *)M.panel_plan, plan_bits(M.panel_plan, Gt), a.skip);
+        if (M.panel_cut)
+            hipLaunchKernelGGL((carry_fixup<T>), dim3(ceil_div(Gt, 256)), dim3(256), 0, s, Gt,
+                               crow, cval, T(1), ypart, a.skip);
     }
     CK_HIP(hipGetLastError());
     return launch_panel_combine<T>(M, a, ypart, G_dot, s);
