@@ -47,9 +47,29 @@ __device__ __forceinline__ T wg_sum(T v, T *lds) {
 // together.  The summation order is the plain one.
 constexpr int kVec = 4;   // vector elements in flight per thread
 
+// A value or pointer that is the same in every lane, in scalar registers, so
+// that a load from p[i] takes a scalar base and a 32-bit lane offset.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T *uni(T *p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (T *)(((unsigned long long)hi << 32) | lo);
+}
+
+// This thread's index, as a value the compiler cannot trace: what a loop
+// derives from it (clamped row indices, LDS addresses, bounds tests) is then
+// formed there, instead of being kept for the whole solve in registers that
+// at 1024 threads do not suffice.
+__device__ __forceinline__ int thread_index() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // rows in flight per thread in the workgroup SpMV
-template <int BS>
-constexpr int rows_in_flight() { return BS >= 1024 ? 8 : 4; }
+constexpr int kRowsInFlight = 4;
 
 // Sum over the L lanes of a row (L a run-time power of two, uniform over
 // the workgroup) by DPP moves, valid in lane L - 1 of each row's lanes.
@@ -70,23 +90,30 @@ __device__ __forceinline__ T lanes_sum(T a, int L) {
 // two).  Per row the lanes sum entries start + lane, start + lane + L, ...
 // in order, then a DPP sum over the L lanes.
 template <int BS, typename TV, typename TX, typename TA>
-__device__ void wg_spmv(int n, int L, const int *__restrict__ rp, const int *__restrict__ col,
-                        const TV *__restrict__ val, const TX *__restrict__ x, TA s1, TA s0,
-                        const TA *__restrict__ z, TA *__restrict__ y) {
-    constexpr int U = rows_in_flight<BS>();
-    const int lane = threadIdx.x & (L - 1);
-    const int rpp = BS / L;
+__device__ __forceinline__ void wg_spmv(int n, int L, const int *__restrict__ rp,
+                                        const int *__restrict__ col,
+                                        const TV *__restrict__ val, const TX *__restrict__ x,
+                                        TA s1, TA s0, const TA *__restrict__ z,
+                                        TA *__restrict__ y) {
+    constexpr int U = kRowsInFlight;
+    rp = uni(rp);
+    col = uni(col);
+    val = uni(val);
+    const int tid = thread_index();
+    const int lg = 31 - __clz(L);
+    const int lane = tid & (L - 1), sub = tid >> lg;
+    const int rpp = BS >> lg;
     for (int r0 = 0; r0 < n; r0 += U * rpp) {
         int kb[U], ke[U];
         TA acc[U];
         int trips = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int row = min(r0 + u * rpp + (int)threadIdx.x / L, n - 1);
-            kb[u] = rp[row] + lane;
-            ke[u] = r0 + u * rpp + (int)threadIdx.x / L < n ? rp[row + 1] : 0;
+            const int row = min(r0 + u * rpp + sub, n - 1);
+            kb[u] = rp[(unsigned)row] + lane;
+            ke[u] = r0 + u * rpp + sub < n ? rp[(unsigned)row + 1] : 0;
             acc[u] = 0;
-            trips = max(trips, (ke[u] - kb[u] + L - 1) / L);
+            trips = max(trips, (ke[u] - kb[u] + L - 1) >> lg);
         }
         // trips > 0 means some row here has entries, so entry 0 exists and
         // serves as the in-range index of finished rows
@@ -95,10 +122,10 @@ __device__ void wg_spmv(int n, int L, const int *__restrict__ rp, const int *__r
             TV vv[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int k = kb[u] + t * L;
+                const int k = kb[u] + (t << lg);
                 const int kk = k < ke[u] ? k : 0;
-                cc[u] = col[kk];
-                vv[u] = val[kk];
+                cc[u] = col[(unsigned)kk];
+                vv[u] = val[(unsigned)kk];
             }
             TX xv[U];
 #pragma unroll
@@ -107,13 +134,13 @@ __device__ void wg_spmv(int n, int L, const int *__restrict__ rp, const int *__r
             __builtin_amdgcn_sched_barrier(0);   // all gathers in flight before the first use
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (kb[u] + t * L < ke[u])
+                if (kb[u] + (t << lg) < ke[u])
                     acc[u] += (TA)vv[u] * (TA)xv[u];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const TA a = lanes_sum(acc[u], L);   // valid in lane L - 1 of the row's lanes
-            const int row = r0 + u * rpp + threadIdx.x / L;
+            const int row = r0 + u * rpp + sub;
             if (lane == L - 1 && row < n)
                 y[row] = z ? s1 * a + s0 * z[row] : s1 * a;
         }
@@ -125,22 +152,326 @@ __device__ __forceinline__ T *wsp(ck::BSlot *s, int which) {
     return (T *)s->work + (int64_t)which * s->ld;
 }
 
+// ---- inner loops of systems whose vectors fit the workgroup -------------------
+// Rows per thread of the inner loops below: thread t holds rows t, t + BS, ...
+// of the inner vectors in registers, and the vector being multiplied sits in
+// LDS, so between products nothing is read from memory but the matrix (and
+// the basis).
+template <int BS>
+constexpr int resident_rows() { return BS >= 1024 ? 8 : 4; }
+
+template <typename T, int BS>
+struct SlotLds {
+    T p[BS * resident_rows<BS>()];   // the vector multiplied
+    T q[BS * resident_rows<BS>()];   // its product
+    T red[2][BS / 64];
+    T wred[BS / 64][ck::kBMaxM + 1];
+    T h[ck::kBMaxM + 1], hsum[ck::kBMaxM + 1];
+    T cs[ck::kBMaxM], sn[ck::kBMaxM];
+    T inv;
+    int stop;
+};
+
+// wg_sum with one barrier: successive calls alternate between two buffers, so
+// a buffer is rewritten only after the barrier of the call in between, which
+// every thread reaches after reading it.
+template <int BS, typename T>
+__device__ __forceinline__ T wg_sum_alt(T v, T (&red)[2][BS / 64], int &parity) {
+    T *buf = red[parity];
+    parity ^= 1;
+    v = ck::wave_sum_last(v);   // valid in lane 63
+    if ((threadIdx.x & 63) == 63)
+        buf[threadIdx.x >> 6] = v;
+    __syncthreads();
+    T r = (buf[0] + buf[1]) + (buf[2] + buf[3]);
+#pragma unroll
+    for (int t = 4; t < BS / 64; t += 4)
+        r += (buf[t] + buf[t + 1]) + (buf[t + 2] + buf[t + 3]);
+    return r;
+}
+
+// CG steps of a slot in phase B_INNER until it leaves the phase or `budget`
+// steps are done; returns the steps, and the new phase in *phase.
+template <typename T, int BS>
+__device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> &lds, int *phase) {
+    constexpr int R = resident_rows<BS>();
+    const int tid = thread_index(), n = uni(s->n), L = uni(s->lanes);
+    T *r = wsp<T>(s, 0), *p = wsp<T>(s, 1), *d = wsp<T>(s, 3);
+    const T *val = sizeof(T) == 4 ? (const T *)s->val32 : (const T *)s->val64;
+    T rr[R], pr[R], dr[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = tid + u * BS, ii = min(i, n - 1);
+        rr[u] = r[ii];
+        pr[u] = p[ii];
+        dr[u] = d[ii];
+        if (i >= n)
+            rr[u] = pr[u] = dr[u] = 0;
+        else
+            lds.p[i] = pr[u];
+    }
+    T rho = (T)s->rho;
+    int inner = s->inner_iter, iter = s->iter, parity = 0, steps = 0, next = ck::B_INNER;
+    const int inner_cap = s->inner_cap, max_iter = s->max_iter;
+    const double inner_tol = s->inner_tol;
+    bool broken = false;
+    while (steps < budget && next == ck::B_INNER) {
+        const int tid = thread_index();
+        ++steps;
+        __syncthreads();   // lds.p is complete
+        wg_spmv<BS, T, T, T>(n, L, s->rp, s->col, val, lds.p, T(1), T(0), (const T *)nullptr,
+                             lds.q);
+        __syncthreads();
+        T q[R], pq = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int i = tid + u * BS;
+            q[u] = i < n ? lds.q[i] : T(0);
+            pq += pr[u] * q[u];
+        }
+        const T sigma = wg_sum_alt<BS>(pq, lds.red, parity);
+        if (!(sigma > T(0))) {
+            broken = inner == 0;
+            next = broken ? ck::B_DONE : ck::B_UPDATE;
+            break;
+        }
+        const T alpha = rho / sigma;
+        T rn = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            dr[u] += alpha * pr[u];
+            rr[u] -= alpha * q[u];
+            rn += rr[u] * rr[u];
+        }
+        const T rho_new = wg_sum_alt<BS>(rn, lds.red, parity);
+        ++inner;
+        const bool stop = sqrt((double)rho_new) <= inner_tol || inner >= inner_cap ||
+                          iter + 1 >= max_iter;
+        ++iter;
+        const T beta = rho_new / rho;
+        rho = rho_new;
+        if (stop) {
+            next = ck::B_UPDATE;
+        } else {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int i = tid + u * BS;
+                pr[u] = rr[u] + beta * pr[u];
+                if (i < n)
+                    lds.p[i] = pr[u];
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = tid + u * BS;
+        if (i < n) {
+            r[i] = rr[u];
+            p[i] = pr[u];
+            d[i] = dr[u];
+        }
+    }
+    if (tid == 0) {
+        s->rho = (double)rho;
+        s->inner_iter = inner;
+        s->iter = iter;
+        if (broken)
+            s->status = ck::BREAKDOWN;
+    }
+    *phase = next;
+    __syncthreads();
+    return steps;
+}
+
+// One sweep over basis columns 0 .. j of the thread's rows, eight columns at a
+// time: DOT adds V_c . w to lds.wred, else w -= h_c V_c.
+template <bool DOT, typename T, int BS>
+__device__ __forceinline__ void basis_sweep(int n, int j, const T *__restrict__ V, int64_t ld,
+                                            T (&w)[resident_rows<BS>()], SlotLds<T, BS> &lds) {
+    constexpr int R = resident_rows<BS>();
+    constexpr int U = sizeof(T) == 4 ? 4 : 2;   // rows in flight, 8 columns of each
+    const int tid = thread_index();
+    for (int g = 0; g <= j; g += 8) {
+        T acc[8], h[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            acc[c] = 0;
+            h[c] = !DOT && g + c <= j ? lds.h[min(g + c, j)] : T(0);
+        }
+#pragma unroll
+        for (int u0 = 0; u0 < R; u0 += U) {
+            if (u0 * BS < n) {
+                T vv[U][8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const T *Vc = V + (int64_t)min(g + c, j) * ld;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        vv[u][c] = Vc[(unsigned)min(tid + (u0 + u) * BS, n - 1)];
+                }
+                __builtin_amdgcn_sched_barrier(0);   // the loads are in flight together
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        if (DOT)
+                            acc[c] += vv[u][c] * w[u0 + u];   // w is 0 past the last row
+                        else
+                            w[u0 + u] -= h[c] * vv[u][c];
+                    }
+            }
+        }
+        if (DOT) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (g + c <= j) {
+                    const T v = ck::wave_sum_last(acc[c]);   // valid in lane 63
+                    if ((tid & 63) == 63)
+                        lds.wred[tid >> 6][g + c] = v;
+                }
+        }
+    }
+    if (!DOT) {
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (tid + u * BS >= n)
+                w[u] = 0;
+    }
+}
+
+// Arnoldi steps (classical Gram-Schmidt twice, Givens) of a slot in phase
+// B_INNER, as slot_cg.
+template <typename T, int BS>
+__device__ __forceinline__ int slot_gmres(ck::BSlot *s, int budget, SlotLds<T, BS> &lds, int *phase) {
+    constexpr int R = resident_rows<BS>(), NW = BS / 64;
+    const int tid = thread_index(), n = uni(s->n), L = uni(s->lanes), m = uni(s->m);
+    const int64_t ld = uni((int)s->ld);
+    T *V = uni(wsp<T>(s, 0));
+    const T *val = sizeof(T) == 4 ? (const T *)s->val32 : (const T *)s->val64;
+    int j = uni(s->j), iter = s->iter, parity = 0, steps = 0, next = ck::B_INNER;
+    const int max_iter = s->max_iter;
+    const double beta = s->beta, bnorm = s->bnorm, tol = s->tol;
+    for (int u = 0; u < R; ++u) {
+        const int i = tid + u * BS;
+        if (i < n)
+            lds.p[i] = V[(int64_t)j * ld + i];
+    }
+    if (tid < j) {
+        lds.cs[tid] = (T)s->cs[tid];
+        lds.sn[tid] = (T)s->sn[tid];
+    }
+    T gj = (T)s->g[j];   // every thread; thread 0 uses it
+    while (steps < budget && next == ck::B_INNER) {
+        const int tid = thread_index();
+        ++steps;
+        __syncthreads();   // lds.p is complete
+        wg_spmv<BS, T, T, T>(n, L, s->rp, s->col, val, lds.p, T(1), T(0), (const T *)nullptr,
+                             lds.q);
+        __syncthreads();
+        T w[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            w[u] = tid + u * BS < n ? lds.q[tid + u * BS] : T(0);
+        for (int pass = 0; pass < 2; ++pass) {
+            basis_sweep<true, T, BS>(n, j, V, ld, w, lds);
+            __syncthreads();
+            if (tid <= j) {
+                T h = 0;
+#pragma unroll
+                for (int t = 0; t < NW; t += 4)
+                    h += (lds.wred[t][tid] + lds.wred[t + 1][tid]) +
+                         (lds.wred[t + 2][tid] + lds.wred[t + 3][tid]);
+                lds.h[tid] = h;
+                lds.hsum[tid] = pass == 0 ? h : lds.hsum[tid] + h;
+            }
+            __syncthreads();
+            basis_sweep<false, T, BS>(n, j, V, ld, w, lds);
+        }
+        T nn = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            nn += w[u] * w[u];
+        const T hn = sqrt(wg_sum_alt<BS>(nn, lds.red, parity));
+        if (tid == 0) {
+            // Hessenberg column j in the inner precision (stored as double)
+            double *Hj = s->H + j * (m + 1);
+            T a = lds.hsum[0];
+            for (int i = 0; i < j; ++i) {
+                const T c2 = lds.hsum[i + 1], ci = lds.cs[i], si = lds.sn[i];
+                Hj[i] = (double)(ci * a + si * c2);
+                a = -si * a + ci * c2;
+            }
+            const T dd = sqrt(a * a + hn * hn);
+            int stop = 0;
+            if (dd == T(0)) {
+                stop = 2;           // singular least-squares problem
+            } else {
+                const T cj = a / dd, sj = hn / dd, g1 = -sj * gj;
+                lds.cs[j] = cj;
+                lds.sn[j] = sj;
+                s->cs[j] = (double)cj;
+                s->sn[j] = (double)sj;
+                Hj[j] = (double)dd;
+                Hj[j + 1] = 0;
+                s->g[j + 1] = (double)g1;
+                s->g[j] = (double)(cj * gj);
+                gj = g1;
+                const double est = fabs((double)g1) * beta / bnorm;
+                if (est <= tol || hn == T(0) || j + 1 == m || iter + 1 >= max_iter)
+                    stop = 1;
+            }
+            lds.stop = stop;
+            lds.inv = hn > T(0) ? T(1) / hn : T(0);
+        }
+        __syncthreads();
+        const int stop = uni(lds.stop);
+        if (stop == 2) {
+            next = j == 0 ? ck::B_DONE : ck::B_UPDATE;
+        } else {
+            ++j;
+            ++iter;
+            if (stop == 1) {
+                next = ck::B_UPDATE;
+            } else {
+                const T inv = lds.inv;
+                T *v = V + (int64_t)j * ld;
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    const int i = tid + u * BS;
+                    if (i < n) {
+                        v[i] = w[u] * inv;
+                        lds.p[i] = w[u] * inv;
+                    }
+                }
+            }
+        }
+    }
+    if (tid == 0) {
+        s->j = j;
+        s->iter = iter;
+        if (next == ck::B_DONE)
+            s->status = ck::BREAKDOWN;
+    }
+    *phase = next;
+    __syncthreads();
+    return steps;
+}
+
 }  // namespace
 
-// One launch: every listed slot advances by up to `budget` steps; BS threads
-// per slot (256 when many slots share the GPU, 1024 for a single system).
+// Slot `which` advances by up to `budget` steps on BS threads.
 template <typename T, int BS>
-__global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat *stat,
-                                                    const int *active, int budget) {
+__device__ __forceinline__ void run_slot(ck::BSlot *slots, ck::BStat *stat, int which,
+                                         int budget, SlotLds<T, BS> &resident) {
     constexpr int NW = BS / 64;
+    auto &hcol = resident.h, &hacc = resident.hsum;
+    auto &wred = resident.wred;
     __shared__ T lds[NW];
     __shared__ double lds64[NW];
-    __shared__ T hcol[ck::kBMaxM + 1];
-    __shared__ T hacc[ck::kBMaxM + 1];
-    __shared__ T wred[NW][ck::kBMaxM + 1];
-    ck::BSlot *s = slots + active[blockIdx.x];
+    ck::BSlot *s = slots + which;
     const int tid = threadIdx.x;
-    const int n = s->n, L = s->lanes;
+    const int n = uni(s->n), L = uni(s->lanes);
+    const bool fits = n <= BS * resident_rows<BS>();
     int phase = s->phase;
     if (phase == ck::B_DONE)
         return;
@@ -167,6 +498,12 @@ __global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat 
     }
     int steps = 0;
     while (steps < budget && phase != ck::B_DONE) {
+        const int tid = thread_index();
+        if (phase == ck::B_INNER && fits) {
+            steps += s->kind == ck::B_CG ? slot_cg<T, BS>(s, budget - steps, resident, &phase)
+                                         : slot_gmres<T, BS>(s, budget - steps, resident, &phase);
+            continue;
+        }
         ++steps;
         if (phase == ck::B_OUTER) {
             // r = b - A x in FP64; beta = ||r||
@@ -334,35 +671,30 @@ __global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat 
                              (const T *)nullptr, w);
             __syncthreads();
             for (int pass = 0; pass < 2; ++pass) {
-                T acc[ck::kBMaxM + 1];
+                for (int g = 0; g <= j; g += 8) {   // eight columns at a time
+                    T acc[8];
 #pragma unroll
-                for (int c = 0; c <= ck::kBMaxM; ++c)
-                    acc[c] = 0;
-                for (int i = tid; i < n; i += BS) {
-                    const T wi = w[i];
-                    // columns in groups of 8 loads in flight
+                    for (int c = 0; c < 8; ++c)
+                        acc[c] = 0;
+                    for (int i = tid; i < n; i += BS) {
+                        const T wi = w[i];
+                        T vv[8];
 #pragma unroll
-                    for (int g = 0; g <= ck::kBMaxM; g += 8) {
-                        if (g <= j) {
-                            T vv[8];
+                        for (int c = 0; c < 8; ++c)
+                            vv[c] = V[(int64_t)min(g + c, j) * ld + i];
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int c = 0; c < 8; ++c)
-                                vv[c] = V[(int64_t)min(g + c, j) * ld + i];
-                            __builtin_amdgcn_sched_barrier(0);
+                        for (int c = 0; c < 8; ++c)
+                            acc[c] += vv[c] * wi;
+                    }
 #pragma unroll
-                            for (int c = 0; c < 8; ++c)
-                                if (g + c <= ck::kBMaxM && g + c <= j)
-                                    acc[g + c] += vv[c] * wi;
+                    for (int c = 0; c < 8; ++c)
+                        if (g + c <= j) {
+                            const T v = ck::wave_sum_last(acc[c]);   // valid in lane 63
+                            if ((tid & 63) == 63)
+                                wred[tid >> 6][g + c] = v;
                         }
-                    }
                 }
-#pragma unroll
-                for (int c = 0; c <= ck::kBMaxM; ++c)
-                    if (c <= j) {
-                        const T v = ck::wave_sum_last(acc[c]);   // valid in lane 63
-                        if ((tid & 63) == 63)
-                            wred[tid >> 6][c] = v;
-                    }
                 __syncthreads();
                 if (tid <= j) {
                     T h = (wred[0][tid] + wred[1][tid]) + (wred[2][tid] + wred[3][tid]);
@@ -486,13 +818,36 @@ __global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat 
     if (tid == 0) {
         s->phase = phase;
         s->launches += 1;
-        ck::BStat &o = stat[active[blockIdx.x]];
+        ck::BStat &o = stat[which];
         o.phase = phase;
         o.status = s->status;
         o.iter = s->iter;
         o.outer = s->outer;
         o.relres = s->relres;
     }
+}
+
+// One launch: every listed slot advances by up to `budget` steps.  A slot of
+// at most narrow_n rows runs on 256 threads, a larger one on 1024: a slot's
+// step is a chain of L2 round trips, so more threads shorten it (n = 7,000,
+// FP32 CG: 103 us a step with 256 threads and the vectors in memory, 15 us
+// now), while a system of a thousand rows gains nothing from more than 256
+// and leaves the rest of the compute unit to other slots.  The width follows
+// from n alone, so a slot's bits do not depend on the launch it is in.
+template <typename T, int BS>
+__global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat *stat,
+                                                    const int *active, int budget, int narrow_n) {
+    __shared__ __align__(16) char raw[sizeof(SlotLds<T, BS>)];
+    const int which = active[blockIdx.x];
+    if constexpr (BS > 256) {
+        if (slots[which].n > narrow_n) {
+            run_slot<T, BS>(slots, stat, which, budget, *(SlotLds<T, BS> *)raw);
+            return;
+        }
+        if (threadIdx.x >= 256)
+            return;   // whole waves; barriers count the waves that remain
+    }
+    run_slot<T, 256>(slots, stat, which, budget, *(SlotLds<T, 256> *)raw);
 }
 
 namespace ck {
@@ -503,22 +858,23 @@ int64_t bslot_work_elems(int kind, int64_t n, int m) {
 }
 
 ck_status launch_batched_chunk(BSlot *slots, BStat *stat, const int *active, int nactive,
-                               int budget, bool fp32, hipStream_t s, bool wide) {
+                               int budget, bool fp32, hipStream_t s, int64_t max_n,
+                               int narrow_n) {
     if (nactive <= 0)
         return CK_OK;
-    if (wide) {
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(nactive), dim3(threads), 0, s, slots, stat, active, budget,
+                           narrow_n);
+    };
+    if (max_n > narrow_n) {
         if (fp32)
-            hipLaunchKernelGGL((batched_chunk<float, 1024>), dim3(nactive), dim3(1024), 0, s,
-                               slots, stat, active, budget);
+            go(batched_chunk<float, 1024>, 1024);
         else
-            hipLaunchKernelGGL((batched_chunk<double, 1024>), dim3(nactive), dim3(1024), 0, s,
-                               slots, stat, active, budget);
+            go(batched_chunk<double, 1024>, 1024);
     } else if (fp32) {
-        hipLaunchKernelGGL((batched_chunk<float, 256>), dim3(nactive), dim3(256), 0, s, slots,
-                           stat, active, budget);
+        go(batched_chunk<float, 256>, 256);
     } else {
-        hipLaunchKernelGGL((batched_chunk<double, 256>), dim3(nactive), dim3(256), 0, s, slots,
-                           stat, active, budget);
+        go(batched_chunk<double, 256>, 256);
     }
     CK_HIP(hipGetLastError());
     return CK_OK;

@@ -56,8 +56,11 @@ ck_status launch_cg_wg(int n, const int *rp, const int *col, const double *val, 
 
 // elements (of the inner type) of a slot's `work`
 int64_t bslot_work_elems(int kind, int64_t n, int m);
-// wide = 1024 threads per slot (single-system path), else 256
+// max_n = the most rows of a listed slot; slots of at most narrow_n rows run on
+// 256 threads, the others on 1024.  `stat` and `active` may be pinned host memory.
+constexpr int kNarrowN = 1024;   // the request loop's narrow_n
 ck_status launch_batched_chunk(BSlot *slots, BStat *stat, const int *active, int nactive,
-                               int budget, bool fp32, hipStream_t s, bool wide = false);
+                               int budget, bool fp32, hipStream_t s, int64_t max_n,
+                               int narrow_n);
 
 }  // namespace ck

@@ -85,10 +85,8 @@ struct ck_server {
     int device = 0;
     // batched slots
     BSlot *slots = nullptr;
-    BStat *stat = nullptr;
-    BStat *stat_host = nullptr;
-    int *active_dev = nullptr;
-    int *active_host = nullptr;
+    BStat *stat_host = nullptr;     // pinned; the kernel writes it
+    int *active_host = nullptr;     // pinned; the kernel reads it
     std::vector<Request *> slot_req;
     std::vector<BSlot> slot_init;
     // bookkeeping
@@ -434,17 +432,19 @@ void scheduler(ck_server *Sp) {
         });
         // one batched launch over the occupied slots
         int na = 0;
+        int64_t max_n = 0;
         for (int i = 0; i < S.o.max_slots; ++i)
-            if (S.slot_req[i])
+            if (S.slot_req[i]) {
                 S.active_host[na++] = i;
+                max_n = std::max<int64_t>(max_n, S.slot_init[i].n);
+            }
         stalled = moved == 0 && na == 0;
         if (na > 0) {
-            if (hipMemcpyAsync(S.active_dev, S.active_host, na * sizeof(int),
-                               hipMemcpyHostToDevice, S.stream) != hipSuccess ||
-                launch_batched_chunk(S.slots, S.stat, S.active_dev, na, S.o.chunk_iters, fp32,
-                                     S.stream) != CK_OK ||
-                hipMemcpyAsync(S.stat_host, S.stat, S.o.max_slots * sizeof(BStat),
-                               hipMemcpyDeviceToHost, S.stream) != hipSuccess ||
+            // the slot list is read, and the status records are written, in
+            // pinned host memory by the kernel itself: a launch is one command
+            // instead of three (each copy added about 4 us to every chunk)
+            if (launch_batched_chunk(S.slots, S.stat_host, S.active_host, na, S.o.chunk_iters,
+                                     fp32, S.stream, max_n, kNarrowN) != CK_OK ||
                 hipStreamSynchronize(S.stream) != hipSuccess) {
                 // a failed launch ends the occupied slots with an error
                 (void)hipGetLastError();
@@ -552,8 +552,6 @@ ck_status ck_server_create(const ck_server_opts *o, ck_server_t *out) {
     ck_status st = CK_OK;
     if (hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking) != hipSuccess ||
         hipMalloc((void **)&S->slots, sizeof(BSlot) * o->max_slots) != hipSuccess ||
-        hipMalloc((void **)&S->stat, sizeof(BStat) * o->max_slots) != hipSuccess ||
-        hipMalloc((void **)&S->active_dev, sizeof(int) * o->max_slots) != hipSuccess ||
         hipHostMalloc((void **)&S->stat_host, sizeof(BStat) * o->max_slots, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&S->active_host, sizeof(int) * o->max_slots, hipHostMallocDefault) != hipSuccess)
         st = fail(CK_E_HIP, "server allocation failed");
@@ -709,8 +707,6 @@ void ck_server_destroy(ck_server_t S) {
         if (kv.second.h)
             spmv_destroy(kv.second.h);
     (void)hipFree(S->slots);
-    (void)hipFree(S->stat);
-    (void)hipFree(S->active_dev);
     (void)hipHostFree(S->stat_host);
     (void)hipHostFree(S->active_host);
     if (S->stream)

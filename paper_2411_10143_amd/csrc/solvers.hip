@@ -809,7 +809,7 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool cg, int m) {
     std::free(h);
     CK_HIP(e);
     CK_TRY(launch_fill<int>(1, active, 0, c.s));
-    CK_TRY(launch_batched_chunk(slot, stat, active, 1, budget, fp32, c.s, true));
+    CK_TRY(launch_batched_chunk(slot, stat, active, 1, budget, fp32, c.s, M.n, 0));
     CK_HIP(hipMemcpyAsync(&hs, stat, sizeof hs, hipMemcpyDeviceToHost, c.s));
     CK_HIP(hipStreamSynchronize(c.s));
     c.res.iterations = hs.iter;
