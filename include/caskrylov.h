@@ -128,7 +128,8 @@ typedef struct {
                               + FP64 refinement; needs CK_KEEP_FP32)          */
     int32_t async;         /* CK_EXEC_DEFAULT, CK_EXEC_ASYNC or
                               CK_EXEC_SEQUENTIAL (see below)                  */
-    int32_t check_every;   /* iterations between host convergence polls       */
+    int32_t check_every;   /* iterations the host may issue ahead of the
+                              device (<= 0: 8; GMRES steps: at most 4)        */
     int32_t use_config;    /* 1: run every SpMV with `config` (async ignored) */
     ck_config config;
     int32_t overhead_aware; /* CK_EXEC_ASYNC, FP64 only: convert a decision's

@@ -95,7 +95,15 @@ template <typename T, int NC>
 __global__ __launch_bounds__(256) void gm_pass2(int64_t n, int64_t G, int ncols,
                                                 const T *__restrict__ V, int64_t ldv,
                                                 T *__restrict__ w, T *__restrict__ partials,
-                                                const GmDev<T> *st) {
+                                                const GmDev<T> *st,
+                                                unsigned long long *progress, unsigned seq) {
+    // Step seq opens its second sweep: the state is the one the steps before
+    // it left.  Reported here, where the store to the host's memory is hidden
+    // behind the sweep.
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        ck::report(progress, st->relres, seq,
+                   st->final_state != ck::RUN ? ck::kReportDone
+                   : st->halt ? ck::kReportStopped : ck::kReportRun);
     // A halted solve runs no rows (and leaves zero partials, which no later
     // kernel reads): the flag only sets the loop bound, so the coefficient
     // loads are issued with it rather than after an early exit.  h1 holds
@@ -462,7 +470,8 @@ ck_status launch_gm_cycle_start(int64_t n, const double *r64, T *v0, double *par
 
 template <typename T, int NC>
 static void arnoldi_nc(int64_t n, int64_t G, int j, T *V, int64_t ldv, T *w, T *partials,
-                       GmDev<T> *st, hipStream_t s) {
+                       GmDev<T> *st, unsigned long long *progress, unsigned seq,
+                       hipStream_t s) {
     const int ncols = j + 1;
     if (j == 0)
         hipLaunchKernelGGL((gm_pass1<T, NC>), dim3(G), dim3(256), 0, s, n, G, ncols, V, ldv, w,
@@ -472,7 +481,7 @@ static void arnoldi_nc(int64_t n, int64_t G, int j, T *V, int64_t ldv, T *w, T *
                            partials, st);
     hipLaunchKernelGGL((gm_finish_cols<T>), dim3(ncols), dim3(256), 0, s, G, partials, 1, st);
     hipLaunchKernelGGL((gm_pass2<T, NC>), dim3(G), dim3(256), 0, s, n, G, ncols, V, ldv, w,
-                       partials, st);
+                       partials, st, progress, seq);
     hipLaunchKernelGGL((gm_finish_givens<T>), dim3(1), dim3(1024), 0, s, G, partials, st);
 }
 
@@ -481,26 +490,26 @@ static void arnoldi_nc(int64_t n, int64_t G, int j, T *V, int64_t ldv, T *w, T *
 // w' of step j in column j+1 and h2, u, inv of step j in the state.
 template <typename T>
 ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, GmDev<T> *st,
-                            hipStream_t s) {
+                            unsigned long long *progress, unsigned seq, hipStream_t s) {
     const int64_t G = gm_blocks(n);
     const int ncols = j + 1;
     T *w = V + (int64_t)(j + 1) * ldv;
     if (ncols <= 8)
-        arnoldi_nc<T, 8>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 8>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 16)
-        arnoldi_nc<T, 16>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 16>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 24)
-        arnoldi_nc<T, 24>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 24>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 32)
-        arnoldi_nc<T, 32>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 32>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 40)
-        arnoldi_nc<T, 40>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 40>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 48)
-        arnoldi_nc<T, 48>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 48>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 56)
-        arnoldi_nc<T, 56>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 56>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else if (ncols <= 64)
-        arnoldi_nc<T, 64>(n, G, j, V, ldv, w, partials, st, s);
+        arnoldi_nc<T, 64>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
     else
         return fail(CK_E_INVALID, "restart length above %d", kMaxRestart);
     CK_HIP(hipGetLastError());
@@ -521,7 +530,7 @@ ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmD
     template ck_status launch_gm_cycle_start<T>(int64_t, const double *, T *, double *,        \
                                                 GmDev<T> *, hipStream_t);                      \
     template ck_status launch_gm_arnoldi<T>(int64_t, int, T *, int64_t, T *, GmDev<T> *,       \
-                                            hipStream_t);                                      \
+                                            unsigned long long *, unsigned, hipStream_t);      \
     template ck_status launch_gm_cycle_end<T>(int64_t, double *, const T *, int64_t,           \
                                               GmDev<T> *, hipStream_t);
 CK_GM_INST(double)

@@ -18,7 +18,7 @@ template <typename T>
 ck_status launch_cg_sigma_finish(int64_t G, T *partials, CgDev<T> *cg, hipStream_t s);
 template <typename T>
 ck_status launch_cg_update(int64_t n, T *x, T *r, T *p, const T *q, T *partials, CgDev<T> *cg,
-                           hipStream_t s);
+                           unsigned long long *progress, unsigned seq, hipStream_t s);
 template <typename D, typename S>
 ck_status launch_copy(int64_t n, D *dst, const S *src, const int *skip, hipStream_t s);
 template <typename D>
@@ -37,7 +37,7 @@ ck_status launch_gm_cycle_start(int64_t n, const double *r64, T *v0, double *par
                                 GmDev<T> *st, hipStream_t s);
 template <typename T>
 ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, GmDev<T> *st,
-                            hipStream_t s);
+                            unsigned long long *progress, unsigned seq, hipStream_t s);
 template <typename T>
 ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmDev<T> *st,
                               hipStream_t s);

@@ -157,17 +157,23 @@ __global__ __launch_bounds__(256) void cg_update_r(int64_t n, int64_t G, T *__re
 // beta = rho'/rho_prev; it adds alpha p to its share of x and, unless
 // converged, sets p = r + beta p there.  Block 0 alone stores the scalars.
 // No block reads a field that block 0 stores: `go`, rho_prev and alpha were
-// set by the sigma finish.
+// set by the sigma finish.  Block 0 reports the iteration's outcome to the
+// host, also when the solve had stopped before it.
 template <typename T>
 __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
                                                         const T *__restrict__ partials,
                                                         T *__restrict__ x, T *__restrict__ p,
-                                                        const T *__restrict__ r, CgDev<T> *cg) {
+                                                        const T *__restrict__ r, CgDev<T> *cg,
+                                                        unsigned long long *progress,
+                                                        unsigned seq) {
     __shared__ T lds[4];
     __shared__ T beta_s;
     __shared__ int run_s;
-    if (!cg->go)
+    if (!cg->go) {
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            ck::report(progress, cg->relres, seq, ck::kReportDone);
         return;
+    }
     const T alpha = cg->alpha;
     const T rho_new = ck::sum_partials(partials, G, lds);
     if (threadIdx.x == 0) {
@@ -186,6 +192,8 @@ __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
                 cg->state = ck::CONVERGED;
             else if (iter >= cg->max_iter)
                 cg->state = ck::BUDGET;
+            ck::report(progress, relres, seq,
+                       converged || iter >= cg->max_iter ? ck::kReportDone : ck::kReportRun);
         }
     }
     __syncthreads();
@@ -296,11 +304,11 @@ ck_status launch_cg_sigma_finish(int64_t G, T *partials, CgDev<T> *cg, hipStream
 
 template <typename T>
 ck_status launch_cg_update(int64_t n, T *x, T *r, T *p, const T *q, T *partials, CgDev<T> *cg,
-                           hipStream_t s) {
+                           unsigned long long *progress, unsigned seq, hipStream_t s) {
     const int64_t G = dot_blocks<T>(n);
     hipLaunchKernelGGL((cg_update_r<T>), dim3(G), dim3(256), 0, s, n, G, r, q, partials, cg);
     hipLaunchKernelGGL((cg_rho_update_xp<T>), dim3(G), dim3(256), 0, s, n, G, partials, x, p, r,
-                       cg);
+                       cg, progress, seq);
     CK_HIP(hipGetLastError());
     return CK_OK;
 }
@@ -347,7 +355,8 @@ ck_status launch_fill(int64_t n, T *dst, T v, hipStream_t s) {
                                           hipStream_t);                                     \
     template ck_status launch_cg_sigma_finish<T>(int64_t, T *, CgDev<T> *, hipStream_t);    \
     template ck_status launch_cg_update<T>(int64_t, T *, T *, T *, const T *, T *,          \
-                                           CgDev<T> *, hipStream_t);                        \
+                                           CgDev<T> *, unsigned long long *, unsigned,      \
+                                           hipStream_t);                                    \
     template ck_status launch_scale_cast<T>(int64_t, T *, const double *, const double *,   \
                                             const int *, hipStream_t);                      \
     template ck_status launch_axpy_promote<T>(int64_t, double *, const T *, const double *, \
