@@ -403,18 +403,33 @@ __global__ __launch_bounds__(256) void gm_start_v0(int64_t n, T *__restrict__ v0
         v0[i] = (T)(r[i] * inv);
 }
 
-// Cycle end: back substitution R y = g over the k = j columns formed.
+// Cycle end: back substitution R y = g over the k = j columns formed.  The
+// columns are copied to LDS; lane i of one wave then holds g_i, and for t = k -
+// 1 .. 0 the wave takes y_t = g_t / R_tt from lane t and subtracts y_t times
+// column t.  A chain of k divisions (one thread reading R from memory took
+// 38 us for 30 FP64 columns, each subtraction waiting for its loads; 7 us now).
 template <typename T>
-__global__ void gm_solve_y(GmDev<T> *st) {
-    if (st->final_state != ck::RUN || threadIdx.x != 0)
+__global__ __launch_bounds__(256) void gm_solve_y(GmDev<T> *st) {
+    __shared__ T R[ck::kMaxRestart * (ck::kMaxRestart + 1)];
+    if (st->final_state != ck::RUN)
         return;
-    const int m = st->m, k = st->j;
-    for (int i = k - 1; i >= 0; --i) {
-        T s = st->g[i];
-        for (int t = i + 1; t < k; ++t)
-            s -= st->H[(int64_t)t * (m + 1) + i] * st->y[t];
-        st->y[i] = s / st->H[(int64_t)i * (m + 1) + i];
+    const int tid = threadIdx.x, ld = st->m + 1, k = st->j;
+    T g = tid < k ? st->g[tid] : T(0);
+    for (int t = tid; t < k * ld; t += 256)
+        R[t] = st->H[t];
+    __syncthreads();
+    if (tid >= 64)
+        return;
+    T y = 0;
+    for (int t = k - 1; t >= 0; --t) {
+        const T yt = __shfl(g / R[t * ld + t], t, 64);
+        if (tid < t)
+            g -= R[t * ld + tid] * yt;
+        if (tid == t)
+            y = yt;
     }
+    if (tid < k)
+        st->y[tid] = y;
 }
 
 // x += V_k y, accumulated in FP64 (the basis may be FP32).
@@ -519,7 +534,7 @@ ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, Gm
 template <typename T>
 ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmDev<T> *st,
                               hipStream_t s) {
-    hipLaunchKernelGGL((gm_solve_y<T>), dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL((gm_solve_y<T>), dim3(1), dim3(256), 0, s, st);
     hipLaunchKernelGGL((gm_update_x<T>), dim3(gm_stream_grid(n)), dim3(256), 0, s, n, x, V, ldv,
                        st);
     CK_HIP(hipGetLastError());
