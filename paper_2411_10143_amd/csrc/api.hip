@@ -56,6 +56,9 @@ static void release(ck_matrix *M) {
     mat_free(*M, M->dia_off);
     mat_free(*M, M->dia_val);
     mat_free(*M, M->dia_val32);
+    mat_free(*M, M->dia_coef);
+    mat_free(*M, M->dia_coef32);
+    mat_free(*M, M->dia_mask);
     mat_free(*M, M->hyb_col);
     mat_free(*M, M->hyb_val);
     mat_free(*M, M->hyb_val32);
@@ -131,7 +134,8 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             return CK_OK;
         if (!M.merge_plan)
             CK_TRY(mat_alloc(M, &M.merge_plan, merge_plan_ints(M.n, M.nnz), s));
-        CK_TRY(build_merge_plan(M.n, M.nnz, M.rp, M.merge_plan, &M.merge_cut, s));
+        M.merge_cut = merge_cuts_rows(M.max_row);
+        CK_TRY(launch_merge_plan(M.n, M.nnz, M.rp, M.merge_plan, s));
         return mark_built(M.has_merge_plan, s);
     }
     if (c.format == CK_FMT_CSR) {   // CSR-panel
@@ -168,15 +172,16 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
         if (st == CK_OK)
             st = mat_alloc(M, &M.panel_plan, merge_plan_ints(R, M.nnz), s);
         if (st == CK_OK)
-            st = build_merge_plan(R, M.nnz, M.panel_rp, M.panel_plan, &M.panel_cut, s);
-        if (st == CK_OK) {   // products read the plan, not the row pointers
-            mat_free(M, M.panel_rp);
-            M.panel_rp = nullptr;
-        }
+            st = launch_merge_plan(R, M.nnz, M.panel_rp, M.panel_plan, s);
+        M.panel_cut = merge_cuts_rows(M.max_row);
         if (st == CK_OK)
             st = mark_built(M.has_panel, s);
         (void)hipStreamSynchronize(s);   // the conversion has finished with tmp
         mat_free(M, tmp);
+        if (st == CK_OK) {   // products read the plan, not the row pointers
+            mat_free(M, M.panel_rp);
+            M.panel_rp = nullptr;
+        }
         return st;
     }
     if (c.format == CK_FMT_DIA) {
@@ -188,6 +193,12 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             mat_free(M, M.dia_off);
             mat_free(M, M.dia_val);
             mat_free(M, M.dia_val32);
+            mat_free(M, M.dia_coef);
+            mat_free(M, M.dia_coef32);
+            mat_free(M, M.dia_mask);
+            M.dia_coef = nullptr;
+            M.dia_coef32 = nullptr;
+            M.dia_mask = nullptr;
             M.dia_off = nullptr;
             M.dia_val = nullptr;
             M.dia_val32 = nullptr;
@@ -654,8 +665,7 @@ ck_status ck_export_dia(ck_handle h, int32_t *d_off, double *d_val, int64_t *ndi
         CK_HIP(hipMemcpyAsync(d_off, h->dia_off, h->dia_nd * sizeof(int32_t),
                               hipMemcpyDeviceToDevice, s));
     if (d_val && h->dia_nd > 0)
-        CK_HIP(hipMemcpyAsync(d_val, h->dia_val, h->dia_nd * h->dia_pitch * sizeof(double),
-                              hipMemcpyDeviceToDevice, s));
+        return export_dia_values(*h, d_val, s);
     return CK_OK;
 }
 

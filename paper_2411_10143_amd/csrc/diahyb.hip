@@ -6,7 +6,10 @@
 // k of row i at k*pitch + i, absent entries +0.0.  A product reads no column
 // index at all: lane i reads value k*pitch + i (coalesced) and x[i + d]
 // (coalesced, and shared by neighbouring diagonals through the cache), so a
-// banded matrix moves 8 bytes per stored entry instead of CSR's 12.
+// banded matrix moves 8 bytes per stored entry instead of CSR's 12.  When
+// every diagonal's entries are equal (stencils with constant coefficients)
+// only one value per diagonal and a bit per slot are kept, and a product
+// moves little more than its vectors.
 //
 // HYB is ELL of width K plus the remainder of the rows longer than K.  K is
 // Bell and Garland's rule: the largest K such that at least a third of the
@@ -30,12 +33,15 @@ using ck::ld_stream;
 
 // ---- conversions -----------------------------------------------------------
 
-// flags[d + n - 1] = 1 for every offset d = col - row that holds an entry.
+// flags[d + n - 1] = 1 for every offset d = col - row that holds an entry, and
+// rep[d + n - 1] = the value of one of its entries.
 // Eight lanes per row; a flag is read before it is written, so a diagonal
 // crossed by every row is stored once per cache copy instead of per entry.
 __global__ __launch_bounds__(256) void dia_mark(int64_t n, const int *__restrict__ rp,
                                                 const int *__restrict__ col,
-                                                int *__restrict__ flags) {
+                                                const double *__restrict__ val,
+                                                int *__restrict__ flags,
+                                                double *__restrict__ rep) {
     constexpr int L = 8;
     const int lane = threadIdx.x & (L - 1);
     const int64_t i = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
@@ -44,8 +50,81 @@ __global__ __launch_bounds__(256) void dia_mark(int64_t n, const int *__restrict
     const int k1 = rp[i + 1];
     for (int k = rp[i] + lane; k < k1; k += L) {
         const int64_t t = (int64_t)col[k] - i + n - 1;
-        if (flags[t] == 0)
+        if (flags[t] == 0) {
             flags[t] = 1;
+            rep[t] = val[k];   // racing stores: any one of them will do
+        }
+    }
+}
+
+// The constant form's row masks, and *varies = 1 if an entry differs (in its
+// bits) from its diagonal's rep or there are more than 32 diagonals; blocks
+// that start after that do nothing.  Eight lanes per row.
+__global__ __launch_bounds__(256) void dia_masks(int64_t n, int64_t N, const int *__restrict__ rp,
+                                                 const int *__restrict__ col,
+                                                 const double *__restrict__ val,
+                                                 const int *__restrict__ pos,
+                                                 const double *__restrict__ rep,
+                                                 void *__restrict__ mask, int *varies) {
+    constexpr int L = 8;
+    const int lane = threadIdx.x & (L - 1);
+    const int64_t i = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int nd = pos[N];
+    if (nd > 32) {
+        if (i == 0 && lane == 0)
+            *varies = 1;
+        return;
+    }
+    if (__hip_atomic_load(varies, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        return;
+    unsigned m = 0;
+    bool differs = false;
+    if (i < n) {
+        const int k1 = rp[i + 1];
+        for (int k = rp[i] + lane; k < k1; k += L) {
+            const int64_t t = (int64_t)col[k] - i + n - 1;
+            m |= 1u << pos[t];
+            differs |= __double_as_longlong(val[k]) != __double_as_longlong(rep[t]);
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1)
+        m |= __shfl_xor(m, off, L);
+    if (i < n && lane == 0) {
+        if (nd <= 8)
+            ((unsigned char *)mask)[i] = (unsigned char)m;
+        else
+            ((unsigned *)mask)[i] = m;
+    }
+    if (__any(differs) && (threadIdx.x & 63) == 0)
+        atomicOr(varies, 1);
+}
+
+// coef[pos[t]] = rep[t] for every flagged t
+__global__ __launch_bounds__(256) void dia_coefs(int64_t N, const int *__restrict__ flags,
+                                                 const int *__restrict__ pos,
+                                                 const double *__restrict__ rep,
+                                                 double *__restrict__ coef,
+                                                 float *__restrict__ coef32) {
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < N;
+         t += (int64_t)gridDim.x * 256)
+        if (flags[t] != 0) {
+            coef[pos[t]] = rep[t];
+            if (coef32)
+                coef32[pos[t]] = (float)rep[t];
+        }
+}
+
+// The dense values of the constant form (rows past n: +0.0).
+template <typename MT>
+__global__ __launch_bounds__(256) void dia_expand(int64_t n, int64_t pitch, int64_t nd,
+                                                  const double *__restrict__ coef,
+                                                  const MT *__restrict__ mask,
+                                                  double *__restrict__ dv) {
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < nd * pitch;
+         t += (int64_t)gridDim.x * 256) {
+        const int64_t k = t / pitch, i = t - k * pitch;
+        dv[t] = i < n && ((mask[i] >> k) & 1) ? coef[k] : 0.0;
     }
 }
 
@@ -190,6 +269,86 @@ __global__ __launch_bounds__(256) void spmv_dia(int n, int ncols, int64_t G, int
     }
 }
 
+// DIA in the constant form: one lane per row, the same sums as spmv_dia (an
+// absent slot is the value +0.0), with the values in scalar registers and one
+// mask per row read instead of nd values.  A wave whose rows store every
+// diagonal (the inside of a stencil) needs no test per slot.  Bound by the
+// vectors: 7 diagonals, n = 2,097,152, FP64: 27.9 us reading dense values, 11.5
+// now (FP32 14.9, 7.6); 5 diagonals, n = 1,048,576, FP64: 13.0 and 6.0.
+template <typename T, bool BETA, bool DOT, int ND, typename MT>
+__global__ __launch_bounds__(256) void spmv_dia_const(
+    int n, int ncols, int64_t G, int nd, const int *__restrict__ off,
+    const T *__restrict__ coef, const MT *__restrict__ mask, T alpha, const T *__restrict__ x,
+    T beta, T *__restrict__ y, const int *__restrict__ skip, T *__restrict__ partials) {
+    if (skip != nullptr && *skip != 0)
+        return;
+    const int64_t b = ck::xcd_block(G);
+    if (b < 0)
+        return;
+    const int64_t groups = ((int64_t)n + 255) / 256;
+    const int tid = threadIdx.x;
+    T mine = 0;
+    for (int64_t g = b; g < groups; g += G) {
+        const int64_t row = g * 256 + tid;
+        if (row < n) {
+            const unsigned m = mask[row];
+            T sum = 0;
+            // every column of the group's rows in range: the x loads need no
+            // test and do not wait for the masks
+            const bool inside = ND > 0 && g * 256 + off[0] >= 0 &&
+                                g * 256 + 255 + off[ND > 0 ? ND - 1 : 0] < ncols;
+            if (inside) {
+                T xv[ND > 0 ? ND : 1];
+#pragma unroll
+                for (int u = 0; u < ND; ++u)
+                    xv[u] = (x + (g * 256 + off[u]))[tid];
+                __builtin_amdgcn_sched_barrier(0);
+                if (__all(m == (1u << ND) - 1)) {
+#pragma unroll
+                    for (int u = 0; u < ND; ++u)
+                        sum += coef[u] * xv[u];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < ND; ++u)
+                        sum += ((m >> u) & 1 ? coef[u] : T(0)) * xv[u];
+                }
+            } else {
+                constexpr int S = ND > 0 ? ND : 8;
+                const int steps = ND > 0 ? ND : nd;
+                for (int d0 = 0; d0 < steps; d0 += S) {
+                    T v[S], xv[S];
+                    bool ok[S];
+#pragma unroll
+                    for (int u = 0; u < S; ++u) {
+                        const int d = ND > 0 ? u : min(d0 + u, nd - 1);
+                        const int64_t j = row + off[d];
+                        ok[u] = (ND > 0 || d0 + u < nd) && j >= 0 && j < ncols;
+                        v[u] = (m >> d) & 1 ? coef[d] : T(0);
+                        xv[u] = x[ok[u] ? j : 0];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < S; ++u)
+                        if (ok[u])
+                            sum += v[u] * xv[u];
+                }
+            }
+            T out = alpha * sum;
+            if (BETA)
+                out += beta * y[row];
+            y[row] = out;
+            if (DOT)
+                mine += out * x[row];
+        }
+    }
+    if constexpr (DOT) {
+        __shared__ T lds[4];
+        const T d = ck::block_sum(mine, lds);
+        if (threadIdx.x == 0)
+            partials[b] = d;
+    }
+}
+
 // HYB remainder: L lanes per long row t, entries rp[i] + K .. rp[i+1] - 1 of
 // row i = rows[t], two accumulators per lane, a DPP sum over the L lanes;
 // y[i] += alpha * sum (the ELL pass has already written y[i]).
@@ -269,46 +428,90 @@ int lanes_for_mean(int64_t total, int64_t rows) {
 ck_status convert_to_dia(ck_matrix &M, hipStream_t s) {
     const int64_t n = M.n, pitch = ceil_div(n, 64) * 64;
     int64_t nd = 0;
-    Tmp tmp(M, s);
+    bool constant = false;
+    Tmp tmp(M, s), mask(M, s);
     int *flags = nullptr, *pos = nullptr;
+    double *rep = nullptr;
     const int64_t N = n + M.ncols - 1;   // offsets -(n-1) .. ncols-1
     if (n > 0 && M.nnz > 0) {
-        const int64_t scan_tmp = panel_scan_tmp_elems(N);
-        CK_TRY(tmp.get((size_t)(2 * N + 1 + scan_tmp) * sizeof(int)));
-        flags = (int *)tmp.p;
+        const int64_t ints = 2 * N + 1 + panel_scan_tmp_elems(N);
+        CK_TRY(tmp.get((size_t)(8 * N + (ints + 1) * (int64_t)sizeof(int))));
+        CK_TRY(mask.get((size_t)(4 * n)));
+        rep = (double *)tmp.p;
+        flags = (int *)(rep + N);
         pos = flags + N;
+        int *varies = pos + N + 1 + panel_scan_tmp_elems(N);
         CK_TRY(launch_fill<int>(N, flags, 0, s));
+        CK_TRY(launch_fill<int>(1, varies, 0, s));
         hipLaunchKernelGGL(dia_mark, dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s, n, M.rp, M.col,
-                           flags);
+                           M.val, flags, rep);
         CK_TRY(launch_scan_exclusive(N, flags, pos, pos + N + 1, s));
-        int total = 0;
+        // the first rows alone settle most matrices with varying values: the
+        // blocks of the second launch then end at once
+        for (const int64_t blocks : {(int64_t)1, ceil_div(n, 256 / 8)})
+            hipLaunchKernelGGL(dia_masks, dim3(blocks), dim3(256), 0, s, n, N, M.rp, M.col, M.val,
+                               pos, rep, mask.p, varies);
+        int total = 0, var = 1;
         CK_HIP(hipMemcpyAsync(&total, pos + N, sizeof total, hipMemcpyDeviceToHost, s));
+        CK_HIP(hipMemcpyAsync(&var, varies, sizeof var, hipMemcpyDeviceToHost, s));
         CK_HIP(hipStreamSynchronize(s));
         nd = total;
+        constant = var == 0;
     }
     if (nd * pitch > 8 * M.nnz)
         return fail(CK_E_UNSUPPORTED, "DIA refused: %lld diagonals x %lld rows for %lld entries",
                     (long long)nd, (long long)pitch, (long long)M.nnz);
     CK_TRY(mat_alloc(M, &M.dia_off, nd, s));
-    CK_TRY(mat_alloc(M, &M.dia_val, nd * pitch, s));
-    if (M.val32)
-        CK_TRY(mat_alloc(M, &M.dia_val32, nd * pitch, s));
-    if (nd > 0) {
-        hipLaunchKernelGGL(dia_offsets, dim3(std::min<int64_t>(ceil_div(N, 256), 8192)), dim3(256),
-                           0, s, N, n, flags, pos, M.dia_off);
-        CK_TRY(launch_fill<double>(nd * pitch, M.dia_val, 0.0, s));
-        if (M.val32) {
-            CK_TRY(launch_fill<float>(nd * pitch, M.dia_val32, 0.0f, s));
-            hipLaunchKernelGGL((dia_fill<true>), dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s, n,
-                               pitch, M.rp, M.col, M.val, pos, M.dia_val, M.dia_val32);
-        } else {
-            hipLaunchKernelGGL((dia_fill<false>), dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s, n,
-                               pitch, M.rp, M.col, M.val, pos, M.dia_val, M.dia_val32);
+    const int64_t Gn = std::min<int64_t>(ceil_div(std::max<int64_t>(N, 1), 256), 8192);
+    if (nd > 0)
+        hipLaunchKernelGGL(dia_offsets, dim3(Gn), dim3(256), 0, s, N, n, flags, pos, M.dia_off);
+    if (constant) {
+        CK_TRY(mat_alloc(M, &M.dia_coef, nd, s));
+        if (M.val32)
+            CK_TRY(mat_alloc(M, &M.dia_coef32, nd, s));
+        char *rows = nullptr;
+        const int64_t bytes = n * dia_mask_bytes(nd);
+        CK_TRY(mat_alloc(M, &rows, bytes, s));
+        M.dia_mask = rows;
+        CK_HIP(hipMemcpyAsync(rows, mask.p, (size_t)bytes, hipMemcpyDeviceToDevice, s));
+        hipLaunchKernelGGL(dia_coefs, dim3(Gn), dim3(256), 0, s, N, flags, pos, rep, M.dia_coef,
+                           M.dia_coef32);
+    } else {
+        CK_TRY(mat_alloc(M, &M.dia_val, nd * pitch, s));
+        if (M.val32)
+            CK_TRY(mat_alloc(M, &M.dia_val32, nd * pitch, s));
+        if (nd > 0) {
+            CK_TRY(launch_fill<double>(nd * pitch, M.dia_val, 0.0, s));
+            if (M.val32) {
+                CK_TRY(launch_fill<float>(nd * pitch, M.dia_val32, 0.0f, s));
+                hipLaunchKernelGGL((dia_fill<true>), dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s,
+                                   n, pitch, M.rp, M.col, M.val, pos, M.dia_val, M.dia_val32);
+            } else {
+                hipLaunchKernelGGL((dia_fill<false>), dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s,
+                                   n, pitch, M.rp, M.col, M.val, pos, M.dia_val, M.dia_val32);
+            }
         }
     }
     CK_HIP(hipGetLastError());
     M.dia_nd = nd;
     M.dia_pitch = pitch;
+    return CK_OK;
+}
+
+ck_status export_dia_values(const ck_matrix &M, double *dv, hipStream_t s) {
+    const int64_t total = M.dia_nd * M.dia_pitch;
+    if (M.dia_coef == nullptr) {
+        CK_HIP(hipMemcpyAsync(dv, M.dia_val, total * sizeof(double), hipMemcpyDeviceToDevice, s));
+        return CK_OK;
+    }
+    const dim3 grid(std::min<int64_t>(ceil_div(std::max<int64_t>(total, 1), 256), 65536));
+    if (dia_mask_bytes(M.dia_nd) == 1)
+        hipLaunchKernelGGL((dia_expand<unsigned char>), grid, dim3(256), 0, s, M.n, M.dia_pitch,
+                           M.dia_nd, M.dia_coef, (const unsigned char *)M.dia_mask, dv);
+    else
+        hipLaunchKernelGGL((dia_expand<unsigned>), grid, dim3(256), 0, s, M.n, M.dia_pitch,
+                           M.dia_nd, M.dia_coef, (const unsigned *)M.dia_mask, dv);
+    CK_HIP(hipGetLastError());
     return CK_OK;
 }
 
@@ -375,6 +578,36 @@ template <typename T, bool BETA, bool DOT>
 void launch_dia_spmv(const ck_matrix &M, int64_t G, const T *dv, const SpmvArgs<T> &a,
                      hipStream_t s) {
     const int nd = (int)M.dia_nd;
+    if (M.dia_coef != nullptr) {
+        const T *coef;
+        if constexpr (sizeof(T) == 4)
+            coef = M.dia_coef32;
+        else
+            coef = M.dia_coef;
+        auto go = [&](auto kernel, auto *mask) {
+            hipLaunchKernelGGL(kernel, dim3(xcd_grid(G)), dim3(256), 0, s, (int)M.n, (int)M.ncols,
+                               G, nd, M.dia_off, coef, mask, a.alpha, a.x, a.beta, a.y, a.skip,
+                               a.dot_partials);
+        };
+        const unsigned char *m8 = (const unsigned char *)M.dia_mask;
+        const unsigned *m32 = (const unsigned *)M.dia_mask;
+        switch (nd) {
+        case 3: go(spmv_dia_const<T, BETA, DOT, 3, unsigned char>, m8); break;
+        case 5: go(spmv_dia_const<T, BETA, DOT, 5, unsigned char>, m8); break;
+        case 7: go(spmv_dia_const<T, BETA, DOT, 7, unsigned char>, m8); break;
+        case 9: go(spmv_dia_const<T, BETA, DOT, 9, unsigned>, m32); break;
+        case 13: go(spmv_dia_const<T, BETA, DOT, 13, unsigned>, m32); break;
+        case 15: go(spmv_dia_const<T, BETA, DOT, 15, unsigned>, m32); break;
+        case 19: go(spmv_dia_const<T, BETA, DOT, 19, unsigned>, m32); break;
+        case 27: go(spmv_dia_const<T, BETA, DOT, 27, unsigned>, m32); break;
+        default:
+            if (dia_mask_bytes(nd) == 1)
+                go(spmv_dia_const<T, BETA, DOT, 0, unsigned char>, m8);
+            else
+                go(spmv_dia_const<T, BETA, DOT, 0, unsigned>, m32);
+        }
+        return;
+    }
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(xcd_grid(G)), dim3(256), 0, s, (int)M.n, (int)M.ncols, G,
                            nd, M.dia_pitch, M.dia_off, dv, a.alpha, a.x, a.beta, a.y, a.skip,

@@ -15,6 +15,9 @@ constexpr int kMaxRestart = 64;    // largest GMRES restart length m
 // ever finishes.
 constexpr int kMaxPartials = 8192;
 constexpr int kRowBlocks = kMaxPartials;
+// Up to this many partials a following kernel sums in each of its blocks, so
+// that no one-block finish is launched between the two.
+constexpr int kFoldPartials = 2048;
 // GMRES Gram-Schmidt passes: at most this many blocks, one partial per
 // block and basis column.
 constexpr int kGmMaxBlocks = 2048;

@@ -46,10 +46,10 @@ struct ck_matrix {
     std::atomic<bool> has_panel{false};
     // merge-path plan of the panel-major arrays read as one CSR of panel_rows rows
     int32_t *panel_plan = nullptr;
-    bool panel_cut = true;
+    bool panel_cut = true;            // a workgroup may start inside a panel row
     // merge-path plan (after conversion to CSR-merge): where every workgroup
     // starts and which merged items are row ends (merge_plan_ints); cut =
-    // some workgroup starts inside a row
+    // a workgroup may start inside a row
     int32_t *merge_plan = nullptr;
     bool merge_cut = true;
     std::atomic<bool> has_merge_plan{false};
@@ -59,6 +59,13 @@ struct ck_matrix {
     double *dia_val = nullptr;
     float *dia_val32 = nullptr;
     int64_t dia_nd = 0, dia_pitch = 0;
+    // Constant form (dia_coef != nullptr, dia_val not kept): the entries of
+    // every diagonal have the same bits; dia_coef[k] is diagonal k's value and
+    // bit k of dia_mask's row i says whether row i stores it (one byte a row
+    // for at most 8 diagonals, else four, for at most 32)
+    double *dia_coef = nullptr;
+    float *dia_coef32 = nullptr;
+    void *dia_mask = nullptr;
     std::atomic<bool> has_dia{false};
     // HYB (after conversion): ELL part of width hyb_K (layout as ELL) and the
     // hyb_nt rows longer than hyb_K, ascending; their entries hyb_K.. stay in
@@ -126,10 +133,12 @@ int64_t spmv_carry_bytes(const ck_matrix &M, const ck_config &c, bool fp32);
 // to 3.3 % more (its workgroups start up to 64 items early).
 int64_t spmv_noalloc_bytes(const ck_matrix &M, const ck_config &c);
 // Merge-path plan of a CSR of `rows` rows (the matrix, or the panel-major
-// arrays): its size in ints, and building it (returns when it is built).
+// arrays): its size in ints, and the launches that build it.
 int64_t merge_plan_ints(int64_t rows, int64_t nnz);
-ck_status build_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
-                           bool *cut, hipStream_t s);
+ck_status launch_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
+                            hipStream_t s);
+// Whether a workgroup may start inside a row, from the longest row (-1: not known).
+bool merge_cuts_rows(int64_t max_row);
 
 template <typename T>
 ck_status launch_spmv(const ck_matrix &M, const ck_config &c, const SpmvArgs<T> &a,

@@ -32,6 +32,7 @@
 #include "admit.hpp"
 #include "batched.hpp"
 #include "matrix.hpp"
+#include "diahyb.hpp"
 #include "panel.hpp"
 #include "predictor.hpp"
 #include "solvers.hpp"
@@ -124,7 +125,9 @@ int64_t handle_bytes(const ck_matrix &M) {
     if (M.has_coo.load())
         b += 4 * M.nnz;
     if (M.has_dia.load())
-        b += 4 * M.dia_nd + M.dia_nd * M.dia_pitch * (8 + (M.dia_val32 ? 4 : 0));
+        b += M.dia_coef ? M.dia_nd * (12 + (M.dia_coef32 ? 4 : 0)) +
+                              M.n * dia_mask_bytes(M.dia_nd)
+                        : 4 * M.dia_nd + M.dia_nd * M.dia_pitch * (8 + (M.dia_val32 ? 4 : 0));
     if (M.has_hyb.load())
         b += 4 * M.hyb_nt + M.hyb_K * M.hyb_pitch * (12 + (M.hyb_val32 ? 4 : 0));
     if (M.has_panel.load())

@@ -344,11 +344,10 @@ __global__ __launch_bounds__(256) void merge_partition(int n, int nnz, int64_t G
 
 // The merged sequence as one bit per item, 1 = row end: byte t of workgroup
 // q holds thread t's items D0 + 8 t .. D0 + 8 t + 7, items past the
-// workgroup's end 0.  *cut = 1 if a workgroup starts inside a row.
-__global__ __launch_bounds__(256) void merge_bits(int n, int64_t G, const int *__restrict__ rp,
+// workgroup's end 0.
+__global__ __launch_bounds__(256) void merge_bits(int64_t G, const int *__restrict__ rp,
                                                   const int2 *__restrict__ part,
-                                                  unsigned *__restrict__ bits,
-                                                  int *__restrict__ cut) {
+                                                  unsigned *__restrict__ bits) {
     static_assert(kMergeIPT == 8, "one byte of row-end bits per thread");
     __shared__ unsigned w[64];
     for (int64_t q = blockIdx.x; q < G; q += gridDim.x) {
@@ -363,8 +362,6 @@ __global__ __launch_bounds__(256) void merge_bits(int n, int64_t G, const int *_
         __syncthreads();
         if (threadIdx.x < 64)
             bits[64 * q + threadIdx.x] = w[threadIdx.x];
-        if (threadIdx.x == 0 && c0.x < n && c0.y != rp[c0.x])
-            *cut = 1;
     }
 }
 
@@ -749,8 +746,11 @@ static int64_t row_groups(const ck_matrix &M, const ck_config &c) {
 int64_t spmv_dot_blocks(const ck_matrix &M, const ck_config &c) {
     if (!spmv_fuses_dot(c))
         return 0;
-    const int64_t g = row_groups(M, c);
-    return g < kMaxPartials ? (g > 0 ? g : 1) : kMaxPartials;
+    const int64_t g = std::max<int64_t>(row_groups(M, c), 1);
+    if (c.format == CK_FMT_DIA)
+        return dia_blocks(M, g);
+    return std::min<int64_t>(g, c.algorithm == CK_ALG_PANEL && c.format == CK_FMT_CSR
+                                    ? kFoldPartials : kMaxPartials);
 }
 
 static int64_t carry_blocks(const ck_matrix &M, const ck_config &c) {
@@ -789,37 +789,33 @@ int64_t spmv_noalloc_bytes(const ck_matrix &M, const ck_config &c) {
     return b;
 }
 
-// ---- merge-path plan: G + 1 coordinate pairs, 64 words of row-end bits per
-// workgroup, and the cut flag --------------------------------------------------
+// ---- merge-path plan: G + 1 coordinate pairs and 64 words of row-end bits per
+// workgroup ---------------------------------------------------------------------
 static int64_t plan_blocks(int64_t rows, int64_t nnz) { return ceil_div(rows + nnz, kMergeSpan); }
 
 int64_t merge_plan_ints(int64_t rows, int64_t nnz) {
     const int64_t G = plan_blocks(rows, nnz);
-    return 2 * (G + 1) + 64 * G + 1;
+    return 2 * (G + 1) + 64 * G;
 }
 
 static const unsigned char *plan_bits(const int32_t *plan, int64_t G) {
     return (const unsigned char *)(plan + 2 * (G + 1));
 }
 
-ck_status build_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
-                           bool *cut, hipStream_t s) {
+ck_status launch_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_t *plan,
+                            hipStream_t s) {
     const int64_t G = plan_blocks(rows, nnz);
     int2 *part = (int2 *)plan;
-    int *flag = plan + 2 * (G + 1) + 64 * G;
-    CK_TRY(launch_fill<int>(1, flag, 0, s));
     hipLaunchKernelGGL(merge_partition, dim3(ceil_div(G + 1, 256)), dim3(256), 0, s, (int)rows,
                        (int)nnz, G, rp, part);
     if (G > 0)
-        hipLaunchKernelGGL(merge_bits, dim3(std::min<int64_t>(G, 16384)), dim3(256), 0, s,
-                           (int)rows, G, rp, part, (unsigned *)(plan + 2 * (G + 1)), flag);
+        hipLaunchKernelGGL(merge_bits, dim3(std::min<int64_t>(G, 16384)), dim3(256), 0, s, G, rp,
+                           part, (unsigned *)(plan + 2 * (G + 1)));
     CK_HIP(hipGetLastError());
-    int h = 0;
-    CK_HIP(hipMemcpyAsync(&h, flag, sizeof h, hipMemcpyDeviceToHost, s));
-    CK_HIP(hipStreamSynchronize(s));
-    *cut = h != 0;
     return CK_OK;
 }
+
+bool merge_cuts_rows(int64_t max_row) { return max_row < 0 || max_row > kMergeSlack; }
 
 ck_config default_config(int64_t n, int64_t nnz) {
     const int64_t mean = n > 0 ? nnz / n : 0;   // floor(nnz/n) has the same floor(log2)
@@ -906,7 +902,7 @@ static ck_status dispatch_rows(const ck_matrix &M, const ck_config &c, const Spm
                                hipStream_t s) {
     const int64_t G = std::min<int64_t>(std::max<int64_t>(row_groups(M, c), 1), kRowBlocks);
     if (c.format == CK_FMT_DIA) {
-        launch_dia_spmv<T, BETA, DOT>(M, G, dia_values<T>(M), a, s);
+        launch_dia_spmv<T, BETA, DOT>(M, dia_blocks(M, row_groups(M, c)), dia_values<T>(M), a, s);
         return CK_OK;
     }
     if (c.format == CK_FMT_HYB) {   // ELL part for every row, then the long rows' remainder
