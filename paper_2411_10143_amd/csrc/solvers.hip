@@ -530,15 +530,17 @@ ck_status cg_core(SolveCtx &c, T *x, T *r, T *p, T *q, T *partials, CgDev<T> *de
     while (true) {
         c.poll(iter0 + issued);
         const bool fused = spmv_fuses_dot(c.cfg);
+        T *sigma = partials + kMaxPartials;
+        int64_t Gs = spmv_dot_blocks(c.M, c.cfg);
         if (fused) {
-            CK_TRY(spmv<T>(c, T(1), p, T(0), q, state_ptr, dev, partials));
-            CK_TRY(launch_cg_sigma_finish<T>(spmv_dot_blocks(c.M, c.cfg), partials, dev, c.s));
+            CK_TRY(spmv<T>(c, T(1), p, T(0), q, state_ptr, dev, sigma));
         } else {
             CK_TRY(spmv<T>(c, T(1), p, T(0), q, state_ptr));
-            CK_TRY(launch_cg_sigma<T>(c.M.n, p, q, partials, dev, c.s));
+            CK_TRY(launch_cg_sigma<T>(c.M.n, p, q, sigma, dev, c.s, &Gs));
         }
         ++issued;
-        CK_TRY(launch_cg_update<T>(c.M.n, x, r, p, q, partials, dev, pin.progress(), issued, c.s));
+        CK_TRY(launch_cg_update<T>(c.M.n, x, r, p, q, partials, dev, Gs, sigma, pin.progress(),
+                                   issued, c.s));
         // run at most `every` iterations ahead of the device's reports; two
         // while a cascade decision may still arrive, so that it reaches the
         // device within a few iterations
@@ -569,7 +571,7 @@ ck_status cg_fp64(SolveCtx &c, const double *b, double *x) {
     CK_TRY(ws.get(&r, M.n));
     CK_TRY(ws.get(&p, M.n));
     CK_TRY(ws.get(&q, M.n));
-    CK_TRY(ws.get(&partials, kMaxPartials));
+    CK_TRY(ws.get(&partials, 2 * kMaxPartials));   // r.r, then p.Ap
     CK_TRY(ws.get(&dev, 1));
     CK_TRY(f.init(ws, c.s));
     double bnorm = 0;
@@ -622,7 +624,7 @@ ck_status cg_mixed(SolveCtx &c, const double *b, double *x) {
     CK_TRY(ws.get(&p, M.n));
     CK_TRY(ws.get(&q, M.n));
     CK_TRY(ws.get(&d, M.n));
-    CK_TRY(ws.get(&partials, kMaxPartials));
+    CK_TRY(ws.get(&partials, 2 * kMaxPartials));   // r.r, then p.Ap
     CK_TRY(ws.get(&dev, 1));
     CK_TRY(f.init(ws, c.s));
     double bnorm = 0;

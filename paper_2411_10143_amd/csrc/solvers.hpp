@@ -10,15 +10,16 @@ ck_status launch_dot(int64_t n, const double *x, const double *y, double *partia
                      double *out, hipStream_t s);
 template <typename T>
 ck_status launch_cg_start(int64_t n, const T *r, T *p, T *partials, CgDev<T> *cg, hipStream_t s);
+// partials of p.q (for configurations whose SpMV does not fuse the dot); *Gs of them
 template <typename T>
 ck_status launch_cg_sigma(int64_t n, const T *p, const T *q, T *partials, CgDev<T> *cg,
-                          hipStream_t s);
-// finishes sigma/alpha from the G partials a fused SpMV launch wrote
-template <typename T>
-ck_status launch_cg_sigma_finish(int64_t G, T *partials, CgDev<T> *cg, hipStream_t s);
+                          hipStream_t s, int64_t *Gs);
+// sigma and alpha from the Gs partials of p.q, then the r, x and p updates;
+// `partials` (of r.r) and sigma_partials are different arrays
 template <typename T>
 ck_status launch_cg_update(int64_t n, T *x, T *r, T *p, const T *q, T *partials, CgDev<T> *cg,
-                           unsigned long long *progress, unsigned seq, hipStream_t s);
+                           int64_t Gs, const T *sigma_partials, unsigned long long *progress,
+                           unsigned seq, hipStream_t s);
 template <typename D, typename S>
 ck_status launch_copy(int64_t n, D *dst, const S *src, const int *skip, hipStream_t s);
 template <typename D>

@@ -2,16 +2,46 @@
 // (the "vector inner product and other kernels" beside SpMV in CG and GMRES,
 // Introduction).  All are HBM-bound streams.  Reductions are two-stage with a
 // fixed order: grid-stride sum per thread -> wave butterfly -> 4 waves ->
-// one partial per block; a one-block finish kernel then sums the partials in
-// block order and updates the device-resident scalars.
+// one partial per block; the kernel that needs the sum, or a one-block finish
+// kernel, then sums the partials in block order and updates the
+// device-resident scalars.
 #include "matrix.hpp"
 #include "solvers.hpp"
+
+// Elements a thread of the vector kernels takes at a time, their loads issued
+// together, and so the rows of a block (256 threads, as few as keep the number
+// of partials at most 1024).  At n = 2,097,152 the kernels run at the rate of
+// the last-level cache either way (x and p update 14.9 -> 14.3 us, 5.9 TB/s);
+// with one element at a time and eight per thread a small system waited for
+// eight round trips (n = 27,000: 17.2 -> 13.7 us an iteration, together with
+// the sigma finish folded into the r update).
+constexpr int kVecUnroll = 4;
+
+// f(i, in) for the block's share of n elements, kVecUnroll of them at a time:
+// `load` first for each (index clamped), then `use` for each that exists.
+template <typename L, typename U>
+__device__ __forceinline__ void batched(int64_t n, int64_t b, int64_t G, L load, U use) {
+    for (int64_t i0 = (b * kVecUnroll) * 256 + threadIdx.x; i0 < n; i0 += G * kVecUnroll * 256) {
+#pragma unroll
+        for (int u = 0; u < kVecUnroll; ++u) {
+            const int64_t i = i0 + u * 256;
+            load(u, i < n ? i : n - 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kVecUnroll; ++u) {
+            const int64_t i = i0 + u * 256;
+            if (i < n)
+                use(u, i);
+        }
+    }
+}
 
 namespace ck {
 
 template <typename T>
 int64_t dot_blocks(int64_t n) {
-    int64_t g = ceil_div(n, 2048);
+    int64_t g = ceil_div(n, 256 * kVecUnroll);
     if (g < 1)
         g = 1;
     return g < 1024 ? g : 1024;
@@ -32,9 +62,14 @@ __global__ __launch_bounds__(256) void dot_partial(int64_t n, int64_t G,
                                                    double *__restrict__ partials) {
     __shared__ double lds[4];
     const int64_t b = blockIdx.x;
-    double s = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256)
-        s += x[i] * y[i];
+    double s = 0, xv[kVecUnroll], yv[kVecUnroll];
+    batched(
+        n, b, G,
+        [&](int u, int64_t i) {
+            xv[u] = x[i];
+            yv[u] = y[i];
+        },
+        [&](int u, int64_t) { s += xv[u] * yv[u]; });
     s = ck::block_sum(s, lds);
     if (threadIdx.x == 0)
         partials[b] = s;
@@ -57,12 +92,13 @@ __global__ __launch_bounds__(256) void cg_start(int64_t n, int64_t G, const T *_
     if (cg->state != ck::RUN)
         return;
     const int64_t b = blockIdx.x;
-    T s = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256) {
-        const T ri = r[i];
-        p[i] = ri;
-        s += ri * ri;
-    }
+    T s = 0, rv[kVecUnroll];
+    batched(
+        n, b, G, [&](int u, int64_t i) { rv[u] = r[i]; },
+        [&](int u, int64_t i) {
+            p[i] = rv[u];
+            s += rv[u] * rv[u];
+        });
     s = ck::block_sum(s, lds);
     if (threadIdx.x == 0)
         partials[b] = s;
@@ -95,9 +131,14 @@ __global__ __launch_bounds__(256) void cg_sigma(int64_t n, int64_t G, const T *_
     if (cg->state != ck::RUN)
         return;
     const int64_t b = blockIdx.x;
-    T s = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256)
-        s += p[i] * q[i];
+    T s = 0, pv[kVecUnroll], qv[kVecUnroll];
+    batched(
+        n, b, G,
+        [&](int u, int64_t i) {
+            pv[u] = p[i];
+            qv[u] = q[i];
+        },
+        [&](int u, int64_t) { s += pv[u] * qv[u]; });
     s = ck::block_sum(s, lds);
     if (threadIdx.x == 0)
         partials[b] = s;
@@ -129,22 +170,61 @@ __global__ __launch_bounds__(256) void cg_sigma_finish(int64_t G, const T *__res
 }
 
 // r -= alpha q; partials of r.r (x is updated with p in cg_rho_update_xp,
-// which reads p anyway)
-template <typename T>
+// which reads p anyway).  FOLD: the sigma finish happens here: every block
+// sums the Gs sigma partials in the same order and forms alpha = rho / sigma
+// itself, and block 0 alone stores the scalars (no block reads a field that
+// block 0 stores, but `state`, and a block that finds it changed to BREAKDOWN
+// only leaves a little earlier).  The sum takes about 1.3 us of every block; the
+// finish kernel took 4.2 us and the gap of one more launch.
+template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void cg_update_r(int64_t n, int64_t G, T *__restrict__ r,
                                                    const T *__restrict__ q,
-                                                   T *__restrict__ partials, const CgDev<T> *cg) {
+                                                   T *__restrict__ partials, int64_t Gs,
+                                                   const T *__restrict__ sigma_partials,
+                                                   CgDev<T> *cg) {
     __shared__ T lds[4];
-    if (cg->state != ck::RUN)
+    __shared__ T alpha_s;
+    if (cg->state != ck::RUN) {
+        if (FOLD && blockIdx.x == 0 && threadIdx.x == 0)
+            cg->go = 0;
         return;
-    const T alpha = cg->alpha;
-    const int64_t b = blockIdx.x;
-    T s = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256) {
-        const T ri = r[i] - alpha * q[i];
-        r[i] = ri;
-        s += ri * ri;
     }
+    T alpha;
+    if constexpr (FOLD) {
+        const T rho = cg->rho;
+        const T sigma = ck::sum_partials(sigma_partials, Gs, lds);
+        if (threadIdx.x == 0) {
+            const bool ok = sigma > T(0);
+            const T a = ok ? rho / sigma : T(0);
+            alpha_s = a;
+            if (blockIdx.x == 0) {
+                cg->sigma = sigma;
+                cg->rho_prev = rho;
+                cg->go = ok;
+                if (ok)
+                    cg->alpha = a;
+                else
+                    cg->state = ck::BREAKDOWN;
+            }
+        }
+        __syncthreads();
+        alpha = alpha_s;
+    } else {
+        alpha = cg->alpha;
+    }
+    const int64_t b = blockIdx.x;
+    T s = 0, rv[kVecUnroll], qv[kVecUnroll];
+    batched(
+        n, b, G,
+        [&](int u, int64_t i) {
+            rv[u] = r[i];
+            qv[u] = q[i];
+        },
+        [&](int u, int64_t i) {
+            const T ri = rv[u] - alpha * qv[u];
+            r[i] = ri;
+            s += ri * ri;
+        });
     s = ck::block_sum(s, lds);
     if (threadIdx.x == 0)
         partials[b] = s;
@@ -198,16 +278,20 @@ __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
     }
     __syncthreads();
     const T beta = beta_s;
-    if (run_s) {
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += G * 256) {
-            const T pi = p[i];
-            x[i] += alpha * pi;
-            p[i] = r[i] + beta * pi;
-        }
-    } else {
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += G * 256)
-            x[i] += alpha * p[i];
-    }
+    const bool run = run_s;
+    T xv[kVecUnroll], pv[kVecUnroll], rv[kVecUnroll];
+    batched(
+        n, blockIdx.x, G,
+        [&](int u, int64_t i) {
+            xv[u] = x[i];
+            pv[u] = p[i];
+            rv[u] = r[i];
+        },
+        [&](int u, int64_t i) {
+            x[i] = xv[u] + alpha * pv[u];
+            if (run)
+                p[i] = rv[u] + beta * pv[u];
+        });
 }
 
 // ---- small elementwise helpers -----------------------------------------------
@@ -287,26 +371,26 @@ ck_status launch_cg_start(int64_t n, const T *r, T *p, T *partials, CgDev<T> *cg
 
 template <typename T>
 ck_status launch_cg_sigma(int64_t n, const T *p, const T *q, T *partials, CgDev<T> *cg,
-                          hipStream_t s) {
-    const int64_t G = dot_blocks<T>(n);
-    hipLaunchKernelGGL((cg_sigma<T>), dim3(G), dim3(256), 0, s, n, G, p, q, partials, cg);
-    hipLaunchKernelGGL((cg_sigma_finish<T>), dim3(1), dim3(256), 0, s, G, partials, cg);
-    CK_HIP(hipGetLastError());
-    return CK_OK;
-}
-
-template <typename T>
-ck_status launch_cg_sigma_finish(int64_t G, T *partials, CgDev<T> *cg, hipStream_t s) {
-    hipLaunchKernelGGL((cg_sigma_finish<T>), dim3(1), dim3(256), 0, s, G, partials, cg);
+                          hipStream_t s, int64_t *Gs) {
+    *Gs = dot_blocks<T>(n);
+    hipLaunchKernelGGL((cg_sigma<T>), dim3(*Gs), dim3(256), 0, s, n, *Gs, p, q, partials, cg);
     CK_HIP(hipGetLastError());
     return CK_OK;
 }
 
 template <typename T>
 ck_status launch_cg_update(int64_t n, T *x, T *r, T *p, const T *q, T *partials, CgDev<T> *cg,
-                           unsigned long long *progress, unsigned seq, hipStream_t s) {
+                           int64_t Gs, const T *sigma_partials, unsigned long long *progress,
+                           unsigned seq, hipStream_t s) {
     const int64_t G = dot_blocks<T>(n);
-    hipLaunchKernelGGL((cg_update_r<T>), dim3(G), dim3(256), 0, s, n, G, r, q, partials, cg);
+    if (Gs <= kFoldPartials) {
+        hipLaunchKernelGGL((cg_update_r<T, true>), dim3(G), dim3(256), 0, s, n, G, r, q, partials,
+                           Gs, sigma_partials, cg);
+    } else {
+        hipLaunchKernelGGL((cg_sigma_finish<T>), dim3(1), dim3(256), 0, s, Gs, sigma_partials, cg);
+        hipLaunchKernelGGL((cg_update_r<T, false>), dim3(G), dim3(256), 0, s, n, G, r, q, partials,
+                           Gs, sigma_partials, cg);
+    }
     hipLaunchKernelGGL((cg_rho_update_xp<T>), dim3(G), dim3(256), 0, s, n, G, partials, x, p, r,
                        cg, progress, seq);
     CK_HIP(hipGetLastError());
@@ -352,11 +436,10 @@ ck_status launch_fill(int64_t n, T *dst, T v, hipStream_t s) {
     template ck_status launch_cg_start<T>(int64_t, const T *, T *, T *, CgDev<T> *,         \
                                           hipStream_t);                                     \
     template ck_status launch_cg_sigma<T>(int64_t, const T *, const T *, T *, CgDev<T> *,   \
-                                          hipStream_t);                                     \
-    template ck_status launch_cg_sigma_finish<T>(int64_t, T *, CgDev<T> *, hipStream_t);    \
+                                          hipStream_t, int64_t *);                          \
     template ck_status launch_cg_update<T>(int64_t, T *, T *, T *, const T *, T *,          \
-                                           CgDev<T> *, unsigned long long *, unsigned,      \
-                                           hipStream_t);                                    \
+                                           CgDev<T> *, int64_t, const T *,                  \
+                                           unsigned long long *, unsigned, hipStream_t);    \
     template ck_status launch_scale_cast<T>(int64_t, T *, const double *, const double *,   \
                                             const int *, hipStream_t);                      \
     template ck_status launch_axpy_promote<T>(int64_t, double *, const T *, const double *, \
