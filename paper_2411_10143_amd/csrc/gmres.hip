@@ -11,14 +11,23 @@
 // v_{j+1} = (w' - V_j h2) / h and A v_{j+1} = (z - V_{j+1} u) / h, where
 // u = Hbar_j h2 is A (V_j h2) expressed in the basis through the Arnoldi
 // relation A V_j = V_{j+1} Hbar_j, and that also sums the partials of
-// V_{j+1}^T A v_{j+1}.  So each step streams the basis twice:
-//   step 0:  pass 1 (partials of V_0^T w)               -> finish: h1
-//   step j:  pass 3+1 (v_j, A v_j in place, partials of V_j^T A v_j) -> h1
-//   then     pass 2: w' = w - V_j h1, partials of V_j^T w' (h2) and ||w'||^2
-//            givens: one workgroup sums the pass-2 partials, forms h_{j+1,j},
-//            H column j (kept unrotated for u, and rotated), the previous
-//            Givens rotations, rotation j, residual estimate |g_{j+1}|, the
-//            cycle stop decision, and u = Hbar_j h2 for the next step.
+// V_{j+1}^T A v_{j+1}.  So each step streams the basis twice, in two kernels
+// after its SpMV:
+//   step 0:  pass 1 (partials of V_0^T w)
+//   step j:  pass 3+1: every block sums the previous step's pass-2 partials
+//            (h2, ||w'||^2) and forms h_{j,j-1} and u itself, then v_j, A v_j in
+//            place and the partials of V_j^T A v_j; one more block does the
+//            previous step's Givens work (H column, rotations, residual estimate
+//            |g|, the cycle stop decision)
+//   then     pass 2: every block sums the first-pass partials (h1) itself,
+//            then w' = w - V_j h1, partials of V_j^T w' (h2) and ||w'||^2.
+// (One-block kernels between the passes took 4.6 and 5.3 us and two launch
+// gaps a step; summed in every block they take about 1.5 and 2.5 us, with at
+// most 256 partials a column.  A step of FP64 GMRES(30) with DIA: n = 22,500
+// 34.4 -> 21.2 us, 160,000 36.1 -> 25.0, 1,048,576 74.3 -> 69.8, of which the
+// two sweeps run at 6.2 TB/s.)
+// The Givens work of a cycle's last step opens the back substitution.  A
+// step issued after the stop decision forms a column that is not used.
 // After the first projection h2 is of rounding size relative to w', so the
 // corrections through h2 and u change w' and z by rounding-size amounts.
 // The last step of a cycle needs no v_{j+1}: the update x += V_k y uses
@@ -26,6 +35,8 @@
 // butterfly, 4 waves, then block order), so results are deterministic.  The
 // least-squares solve and the solution update close the cycle on the
 // device; nothing returns to the host inside a cycle.
+#include <algorithm>
+
 #include "solvers.hpp"
 
 using ck::GmDev;
@@ -40,13 +51,15 @@ namespace {
 // before it.
 __device__ __forceinline__ int64_t clampc(int c, int ncols) { return c < ncols ? c : ncols - 1; }
 
-// partials[c*G + b] = block b's sum of acc[c]  (c < ncols).  The NC wave
-// sums run back to back at the end of the pass, so they use register-to-
-// register (DPP) moves, valid in lane 63.
-template <typename T, int NC>
-__device__ __forceinline__ void block_cols(const T (&acc)[NC], int ncols, T *partials, int64_t b,
-                                           int64_t G) {
-    __shared__ T lds[4][NC];
+constexpr int kGmWaves = ck::kGmThreads / 64;
+
+// partials[c*G + b] = block b's sum of acc[c]  (c < ncols), and of `extra` as
+// column ncols if EXTRA.  The wave sums run back to back at the end of the
+// pass, so they use register-to-register (DPP) moves, valid in lane 63.
+template <bool EXTRA, typename T, int NC>
+__device__ __forceinline__ void block_cols(const T (&acc)[NC], T extra, int ncols, T *partials,
+                                           int64_t b, int64_t G) {
+    __shared__ T lds[kGmWaves][NC + 1];
     const int w = threadIdx.x / 64, lane = threadIdx.x & 63;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -56,17 +69,171 @@ __device__ __forceinline__ void block_cols(const T (&acc)[NC], int ncols, T *par
                 lds[w][c] = v;
         }
     }
-    __syncthreads();
-    if ((int)threadIdx.x < ncols) {
-        const int c = threadIdx.x;
-        partials[c * G + b] = (lds[0][c] + lds[1][c]) + (lds[2][c] + lds[3][c]);
+    if constexpr (EXTRA) {
+        const T v = ck::wave_sum_last(extra);
+        if (lane == 63)
+            lds[w][ncols] = v;
     }
+    __syncthreads();
+    const int cols = ncols + (EXTRA ? 1 : 0);
+    if ((int)threadIdx.x < cols) {
+        const int c = threadIdx.x;
+        T t = 0;
+#pragma unroll
+        for (int v = 0; v < kGmWaves; v += 4)
+            t += (lds[v][c] + lds[v + 1][c]) + (lds[v + 2][c] + lds[v + 3][c]);
+        partials[c * G + b] = t;
+    }
+}
+
+// out[c] = sum over the G blocks of partials[c*G + b], c < ncols, by the waves
+// of a block: wave w takes columns w, w + kGmWaves, ..., four at a time, its
+// lanes striding the blocks (up to four loads of each column in flight), then
+// a wave sum.  Fixed order.  `out` is in LDS; a barrier must follow.
+template <typename T>
+__device__ __forceinline__ void sum_cols(int ncols, int64_t G, const T *__restrict__ partials,
+                                         T *out) {
+    constexpr int U = 4, C = 4;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int c0 = w; c0 < ncols; c0 += C * kGmWaves) {
+        T sum[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+            sum[k] = 0;
+        for (int64_t b0 = lane; b0 < G; b0 += 64 * U) {
+            T v[C][U];
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const int c = min(c0 + k * kGmWaves, ncols - 1);
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    v[k][t] = partials[c * G + (b0 + 64 * t < G ? b0 + 64 * t : G - 1)];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < C; ++k)
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (b0 + 64 * t < G)
+                        sum[k] += v[k][t];
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const T t = ck::wave_sum_last(sum[k]);   // valid in lane 63
+            if (lane == 63 && c0 + k * kGmWaves < ncols)
+                out[c0 + k * kGmWaves] = t;
+        }
+    }
+}
+
+// What the end of step s leaves for the next kernel, formed by a block from
+// the step's pass-2 partials: h2 (column s + 1: ||w'||^2), the unrotated
+// column s of H, h_{s+1,s} and u = Hbar_s h2.
+template <typename T>
+struct StepEnd {
+    __align__(16) T h2[ck::kMaxRestart + 2];
+    __align__(16) T u[ck::kMaxRestart + 2];
+    T col[ck::kMaxRestart + 1];
+    T hr[ck::kMaxRestart * (ck::kMaxRestart + 1)];   // Hraw columns 0 .. s-1
+    T cs[ck::kMaxRestart], sn[ck::kMaxRestart];
+    T hn;
+};
+
+template <typename T>
+__device__ __forceinline__ void step_end(int s, int m, int64_t G, const T *__restrict__ partials,
+                                         const GmDev<T> *st, StepEnd<T> &e) {
+    const int t = threadIdx.x;
+    // loads that do not depend on the sums are issued before them
+    const T h1 = t <= s ? st->h1[t] : T(0);
+    for (int k = t; k < s * (m + 1); k += ck::kGmThreads)
+        e.hr[k] = st->Hraw[k];
+    sum_cols(s + 2, G, partials, e.h2);
+    __syncthreads();
+    if (t <= s)
+        e.col[t] = h1 + e.h2[t];
+    if (t < 64) {   // s < 64 columns: one wave sums h2^2
+        const T h = t <= s ? e.h2[t] : T(0);
+        const T proj = ck::wave_sum_last(h * h);   // valid in lane 63
+        if (t == 63) {
+            const T nrm2 = e.h2[s + 1] - proj;
+            e.hn = nrm2 > T(0) ? sqrt(nrm2) : T(0);
+        }
+    }
+    __syncthreads();
+    // u_i sums columns c >= i - 1
+    for (int i = t; i <= s + 1; i += ck::kGmThreads) {
+        T acc = 0;
+        for (int c = i > 0 ? i - 1 : 0; c < s; ++c)
+            acc += e.hr[c * (m + 1) + i] * e.h2[c];
+        e.u[i] = acc + (i <= s ? e.col[i] : e.hn) * e.h2[s];
+    }
+    __syncthreads();
+}
+
+// Givens step s from what step_end formed: Hessenberg column s, previous
+// rotations, new rotation, residual estimate and the cycle stop decision.  No
+// field that other blocks of the same kernel read is changed, except `halt`
+// (a block that sees it set only leaves out rows nothing will use).
+template <typename T>
+__device__ __forceinline__ void givens_step(int s, int m, GmDev<T> *st, StepEnd<T> &e) {
+    const int t = threadIdx.x;
+    T *Rs = st->Hraw + (int64_t)s * (m + 1);
+    if (t < s) {
+        e.cs[t] = st->cs[t];
+        e.sn[t] = st->sn[t];
+    }
+    if (t <= s)
+        Rs[t] = e.col[t];
+    __syncthreads();
+    if (t != 0)
+        return;
+    const T hn = e.hn;
+    Rs[s + 1] = hn;
+    T *Hs = st->H + (int64_t)s * (m + 1);
+    // previous rotations applied to (h_0s, ..., h_ss, hn); `a` carries entry i
+    T a = e.col[0];
+    for (int i = 0; i < s; ++i) {
+        const T c2 = e.col[i + 1];
+        Hs[i] = e.cs[i] * a + e.sn[i] * c2;
+        a = -e.sn[i] * a + e.cs[i] * c2;
+    }
+    const T d = sqrt(a * a + hn * hn);
+    if (d == T(0)) {
+        st->final_state = ck::BREAKDOWN;
+        st->cycle_stop = ck::BREAKDOWN;
+        st->halt = 1;
+        return;
+    }
+    const T cj = a / d, sj = hn / d;
+    const T gj = st->res[s], g1 = -sj * gj;
+    const int iter = st->iter0 + s + 1;
+    st->cs[s] = cj;
+    st->sn[s] = sj;
+    Hs[s] = d;
+    Hs[s + 1] = 0;
+    st->g[s] = cj * gj;
+    st->res[s + 1] = g1;
+    st->j = s + 1;
+    st->iter = iter;
+    const double relres = fabs((double)g1) / st->bnorm;
+    st->relres = relres;
+    int stop = ck::RUN;
+    if (relres <= st->tol)
+        stop = ck::CONVERGED;
+    else if (hn == T(0))
+        stop = ck::BREAKDOWN;
+    else if (iter >= st->max_iter)
+        stop = ck::BUDGET;
+    else if (s + 1 == m)
+        stop = ck::FULL;
+    st->cycle_stop = stop;
+    st->halt = stop != ck::RUN;
 }
 
 }  // namespace
 
 template <typename T, int NC>
-__global__ __launch_bounds__(256) void gm_pass1(int64_t n, int64_t G, int ncols,
+__global__ __launch_bounds__(ck::kGmThreads) void gm_pass1(int64_t n, int64_t G, int ncols,
                                                 const T *__restrict__ V, int64_t ldv,
                                                 const T *__restrict__ w,
                                                 T *__restrict__ partials, const GmDev<T> *st) {
@@ -77,7 +244,7 @@ __global__ __launch_bounds__(256) void gm_pass1(int64_t n, int64_t G, int ncols,
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         acc[c] = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256) {
+    for (int64_t i = b * ck::kGmThreads + threadIdx.x; i < n; i += G * ck::kGmThreads) {
         const T wi = w[i];
         T vv[NC];
 #pragma unroll
@@ -88,15 +255,17 @@ __global__ __launch_bounds__(256) void gm_pass1(int64_t n, int64_t G, int ncols,
         for (int c = 0; c < NC; ++c)
             acc[c] += vv[c] * wi;
     }
-    block_cols<T, NC>(acc, ncols, partials, b, G);
+    block_cols<false, T, NC>(acc, T(0), ncols, partials, b, G);
 }
 
 template <typename T, int NC>
-__global__ __launch_bounds__(256) void gm_pass2(int64_t n, int64_t G, int ncols,
+__global__ __launch_bounds__(ck::kGmThreads) void gm_pass2(int64_t n, int64_t G, int ncols,
                                                 const T *__restrict__ V, int64_t ldv,
-                                                T *__restrict__ w, T *__restrict__ partials,
-                                                const GmDev<T> *st,
+                                                T *__restrict__ w,
+                                                const T *__restrict__ partials1,
+                                                T *__restrict__ partials, GmDev<T> *st,
                                                 unsigned long long *progress, unsigned seq) {
+    __shared__ __align__(16) T h1[NC];
     // Step seq opens its second sweep: the state is the one the steps before
     // it left.  Reported here, where the store to the host's memory is hidden
     // behind the sweep.
@@ -105,77 +274,115 @@ __global__ __launch_bounds__(256) void gm_pass2(int64_t n, int64_t G, int ncols,
                    st->final_state != ck::RUN ? ck::kReportDone
                    : st->halt ? ck::kReportStopped : ck::kReportRun);
     // A halted solve runs no rows (and leaves zero partials, which no later
-    // kernel reads): the flag only sets the loop bound, so the coefficient
-    // loads are issued with it rather than after an early exit.  h1 holds
-    // kMaxRestart + 1 >= NC entries.
+    // kernel reads): the flag only sets the loop bound, so the loads of the
+    // first pass's partials are issued with it rather than after an early exit.
     const int64_t nl = st->halt ? 0 : n;
-    T h[NC], acc[NC], nn = 0;
+    sum_cols(ncols, G, partials1, h1);
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < ncols && nl > 0)
+        st->h1[threadIdx.x] = h1[threadIdx.x];
+    constexpr bool HREG = NC * sizeof(T) <= 256;   // as in gm_pass31
+    if ((int)threadIdx.x >= ncols && threadIdx.x < NC)
+        h1[threadIdx.x] = 0;
+    __syncthreads();
+    T h[HREG ? NC : 1], acc[NC], nn = 0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const T hc = st->h1[c];   // unconditional: the loads merge
-        h[c] = c < ncols ? hc : T(0);
+        if constexpr (HREG)
+            h[c] = h1[c];
         acc[c] = 0;
     }
     const int64_t b = blockIdx.x;
-    for (int64_t i = b * 256 + threadIdx.x; i < nl; i += G * 256) {
+    for (int64_t i = b * ck::kGmThreads + threadIdx.x; i < nl; i += G * ck::kGmThreads) {
         T vv[NC];
         T wi = w[i];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             vv[c] = V[clampc(c, ncols) * ldv + i];
         __builtin_amdgcn_sched_barrier(0);   // every load issued before the first use
+        int o = 0;
+        if constexpr (!HREG)
+            asm volatile("" : "+v"(o));
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            wi -= h[c] * vv[c];
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (HREG)
+                wi -= h[c] * vv[c];
+            else
+                wi -= h1[c + o] * vv[c];
+        }
         w[i] = wi;
         nn += wi * wi;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             acc[c] += vv[c] * wi;
     }
-    block_cols<T, NC>(acc, ncols, partials, b, G);
-    __shared__ T lds[4];
-    nn = ck::block_sum(nn, lds);
-    if (threadIdx.x == 0)
-        partials[ncols * G + b] = nn;
+    block_cols<true, T, NC>(acc, nn, ncols, partials, b, G);
 }
 
 // Step j >= 1 opens here: column j holds w' of step j - 1 (after its first
 // projection, not yet corrected by h2 nor normalised) and column j + 1 holds
 // z = A w'.  One sweep over V_{j-1} forms, in place, v_j = (w' - V_{j-1} h2)
 // * inv and A v_j = (z - V_{j-1} u_{0..j-1} - u_j v_j) * inv, and the
-// partials of V_j^T A v_j (columns 0..j).  h2, u and inv are step j - 1's.
+// partials of V_j^T A v_j (columns 0..j).  h2, u and inv = 1 / h_{j,j-1} are step
+// j - 1's, formed by every block; block G does that step's Givens work.
 template <typename T, int NC>
-__global__ __launch_bounds__(256) void gm_pass31(int64_t n, int64_t G, int j,
+__global__ __launch_bounds__(ck::kGmThreads) void gm_pass31(int64_t n, int64_t G, int j, int m,
                                                  T *__restrict__ V, int64_t ldv,
-                                                 T *__restrict__ partials, const GmDev<T> *st) {
+                                                 const T *__restrict__ partials2,
+                                                 T *__restrict__ partials, GmDev<T> *st) {
+    __shared__ StepEnd<T> e;
     const int nold = j;   // finished columns 0 .. j-1, read from memory (NC >= j + 1)
-    T h2[NC], u[NC], acc[NC];
+    const int halt = st->halt;
+    step_end(j - 1, m, G, partials2, st, e);
+    if (blockIdx.x == G) {
+        if (!halt)
+            givens_step(j - 1, m, st, e);
+        return;
+    }
+    // The coefficients of the swept columns stay in registers where there is
+    // room for two waves per SIMD (the grid has no more), else they are read
+    // from LDS for every row.
+    constexpr bool HREG = NC * sizeof(T) <= 256, UREG = NC * sizeof(T) <= 192;
+    const T uj = e.u[j];
+    const T inv = e.hn > T(0) ? T(1) / e.hn : T(0);
+    __syncthreads();
+    if ((int)threadIdx.x >= nold && threadIdx.x < NC)
+        e.h2[threadIdx.x] = e.u[threadIdx.x] = 0;
+    __syncthreads();
+    T h2[HREG ? NC : 1], u[UREG ? NC : 1], acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const T hc = st->h2[c], uc = st->u[c];   // unconditional: the loads merge
-        h2[c] = c < nold ? hc : T(0);
-        u[c] = c < nold ? uc : T(0);
+        if constexpr (HREG)
+            h2[c] = e.h2[c];
+        if constexpr (UREG)
+            u[c] = e.u[c];
         acc[c] = 0;
     }
-    const T uj = st->u[j];
-    const T inv = st->inv;
-    const int64_t nl = st->halt ? 0 : n;   // as in gm_pass2: no rows once halted
+    const int64_t nl = halt ? 0 : n;   // as in gm_pass2: no rows once halted
     const int64_t b = blockIdx.x;
     T *wv = V + (int64_t)j * ldv;         // w' in, v_j out
     T *zw = V + (int64_t)(j + 1) * ldv;   // z in, A v_j out
     T accj = 0;
-    for (int64_t i = b * 256 + threadIdx.x; i < nl; i += G * 256) {
+    for (int64_t i = b * ck::kGmThreads + threadIdx.x; i < nl; i += G * ck::kGmThreads) {
         T a = wv[i], zz = zw[i];
         T vv[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             vv[c] = V[clampc(c, nold) * ldv + i];
         __builtin_amdgcn_sched_barrier(0);   // every load issued before the first use
+        int o = 0;
+        if constexpr (!UREG)
+            asm volatile("" : "+v"(o));   // read for this row: not kept in registers
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            a -= h2[c] * vv[c];
-            zz -= u[c] * vv[c];
+            if constexpr (HREG)
+                a -= h2[c] * vv[c];
+            else
+                a -= e.h2[c + o] * vv[c];
+            if constexpr (UREG)
+                zz -= u[c] * vv[c];
+            else
+                zz -= e.u[c + o] * vv[c];
         }
         const T vj = a * inv;
         zz -= uj * vj;
@@ -191,152 +398,7 @@ __global__ __launch_bounds__(256) void gm_pass31(int64_t n, int64_t G, int j,
     for (int c = 0; c < NC; ++c)
         if (c == j)
             acc[c] = accj;   // column j is v_j itself (the loop's acc[j] saw a reloaded column)
-    block_cols<T, NC>(acc, j + 1, partials, b, G);
-}
-
-// out[c] = sum_b partials[c*G + b]; block c reduces column c in block order
-template <typename T>
-__global__ __launch_bounds__(256) void gm_finish_cols(int64_t G, const T *__restrict__ partials,
-                                                      int which, GmDev<T> *st) {
-    __shared__ T lds[4];
-    // the partials are read whether or not the solve has halted (they are
-    // always allocated); only the store depends on the flag
-    const int halt = st->halt;
-    const int c = blockIdx.x;
-    const T s = ck::sum_partials(partials + c * G, G, lds);
-    if (!halt && threadIdx.x == 0)
-        (which == 1 ? st->h1 : st->h2)[c] = s;
-}
-
-// Pass-2 finish and Givens step in one 1024-thread workgroup:
-//  1. wave w sums the G block partials of columns w, w + 16, ... (h2[c] for
-//     c <= j, and ||w'||^2 as column j + 1), lanes striding the blocks, then a
-//     wave butterfly (fixed order);
-//  2. h_{j+1,j} = sqrt(||w'||^2 - ||h2||^2), Hessenberg column j (h1 + h2),
-//     previous rotations, new rotation, residual estimate -- one thread, from
-//     LDS, with no global-memory round trip per rotation.
-template <typename T>
-__global__ __launch_bounds__(1024) void gm_finish_givens(int64_t G, const T *__restrict__ partials,
-                                                         GmDev<T> *st) {
-    constexpr int U = 8;
-    __shared__ T col[ck::kMaxRestart], h2[ck::kMaxRestart + 1], cs[ck::kMaxRestart],
-        sn[ck::kMaxRestart];
-    __shared__ T hr[ck::kMaxRestart * (ck::kMaxRestart + 1)];   // Hraw columns 0 .. j-1
-    const int halt = st->halt, m = st->m, j = st->j;   // one round trip
-    if (halt)
-        return;
-    // Loads that do not depend on the partial sums are issued first, into
-    // registers, so that their latency overlaps the sums': the unrotated
-    // columns 0 .. j-1 (for u below; one entry per thread up to m = 31),
-    // the previous rotations and this column's first-pass coefficients.
-    const int t = threadIdx.x;
-    const int nh = j * (m + 1);
-    const T hr0 = t < nh ? st->Hraw[t] : T(0);
-    const T cs0 = t < j ? st->cs[t] : T(0), sn0 = t < j ? st->sn[t] : T(0);
-    const T h10 = t <= j ? st->h1[t] : T(0);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int c = w; c <= j + 1; c += 16) {
-        const T *pc = partials + (int64_t)c * G;
-        T acc = 0;
-        for (int64_t b0 = lane; b0 < G; b0 += 64 * U) {
-            T v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t b = b0 + 64 * u;
-                v[u] = __builtin_nontemporal_load(&pc[b < G ? b : G - 1]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (b0 + 64 * u < G)
-                    acc += v[u];
-        }
-        acc = ck::wave_sum_last(acc);   // valid in lane 63
-        if (lane == 63) {
-            h2[c] = acc;
-            st->h2[c] = acc;   // pass 3 subtracts V h2
-        }
-    }
-    if (t < nh)
-        hr[t] = hr0;
-    for (int k = t + 1024; k < nh; k += 1024)   // m > 31 only
-        hr[k] = st->Hraw[k];
-    if (t < j) {   // j < kMaxRestart <= 1024
-        cs[t] = cs0;
-        sn[t] = sn0;
-    }
-    __syncthreads();
-    if (t <= j)
-        col[t] = h10 + h2[t];
-    __shared__ T hn_s;
-    if (threadIdx.x == 0) {
-        T proj = 0;
-        for (int c = 0; c <= j; ++c)
-            proj += h2[c] * h2[c];
-        const T nrm2 = h2[j + 1] - proj;
-        hn_s = nrm2 > T(0) ? sqrt(nrm2) : T(0);
-    }
-    __syncthreads();
-    const T hn = hn_s;
-    // unrotated column j, then u = Hbar_j h2 (row i sums columns c >= i - 1)
-    T *Rj = st->Hraw + (int64_t)j * (m + 1);
-    for (int c = threadIdx.x; c <= j; c += 1024)
-        Rj[c] = col[c];
-    if (threadIdx.x == 0)
-        Rj[j + 1] = hn;
-    for (int i = threadIdx.x; i <= j + 1; i += 1024) {
-        T acc = 0;
-        for (int c = i > 0 ? i - 1 : 0; c < j; ++c)
-            acc += hr[c * (m + 1) + i] * h2[c];
-        acc += (i <= j ? col[i] : hn) * h2[j];
-        st->u[i] = acc;
-    }
-    if (threadIdx.x != 0)
-        return;
-    T *Hj = st->H + (int64_t)j * (m + 1);
-    // previous rotations applied to (h_0j, ..., h_jj, hn); `a` carries entry i
-    T a = col[0];
-    for (int i = 0; i < j; ++i) {
-        const T c2 = col[i + 1];
-        Hj[i] = cs[i] * a + sn[i] * c2;
-        a = -sn[i] * a + cs[i] * c2;
-    }
-    const T c2 = hn;
-    Hj[j] = a;
-    Hj[j + 1] = c2;
-    const T d = sqrt(a * a + c2 * c2);
-    if (d == T(0)) {
-        st->final_state = ck::BREAKDOWN;
-        st->cycle_stop = ck::BREAKDOWN;
-        st->halt = 1;
-        return;
-    }
-    const T cj = a / d, sj = c2 / d;
-    const T gj = st->g[j];
-    const double bnorm = st->bnorm, tol = st->tol;
-    const int iter = st->iter + 1, max_iter = st->max_iter;
-    st->cs[j] = cj;
-    st->sn[j] = sj;
-    Hj[j] = d;
-    Hj[j + 1] = 0;
-    const T gj1 = -sj * gj;
-    st->g[j + 1] = gj1;
-    st->g[j] = cj * gj;
-    st->j = j + 1;
-    st->iter = iter;
-    const double relres = fabs((double)gj1) / bnorm;
-    st->relres = relres;
-    int stop = ck::RUN;
-    if (relres <= tol)
-        stop = ck::CONVERGED;
-    else if (hn == T(0))
-        stop = ck::BREAKDOWN;
-    else if (iter >= max_iter)
-        stop = ck::BUDGET;
-    else if (j + 1 == m)
-        stop = ck::FULL;
-    st->cycle_stop = stop;
-    st->halt = stop != ck::RUN;
-    st->inv = hn > T(0) ? T(1) / hn : T(0);
+    block_cols<false, T, NC>(acc, T(0), j + 1, partials, b, G);
 }
 
 // Cycle start: partials of ||r||^2 (FP64)
@@ -386,9 +448,8 @@ __global__ __launch_bounds__(256) void gm_start_finish(int64_t G,
     st->cycle_stop = ck::RUN;
     st->halt = 0;
     st->cycles += 1;
-    st->g[0] = (T)beta;
-    for (int t = 1; t <= st->m; ++t)
-        st->g[t] = 0;
+    st->iter0 = st->iter;
+    st->res[0] = (T)beta;
 }
 
 template <typename T>
@@ -403,19 +464,32 @@ __global__ __launch_bounds__(256) void gm_start_v0(int64_t n, T *__restrict__ v0
         v0[i] = (T)(r[i] * inv);
 }
 
-// Cycle end: back substitution R y = g over the k = j columns formed.  The
-// columns are copied to LDS; lane i of one wave then holds g_i, and for t = k -
+// Cycle end: the Givens work of the last step, unless the cycle has stopped
+// before (its work was done by the next step's pass 3+1 then), and the back
+// substitution R y = g over the k = j columns formed.  The columns are copied to LDS; lane i of one wave then holds g_i, and for t = k -
 // 1 .. 0 the wave takes y_t = g_t / R_tt from lane t and subtracts y_t times
 // column t.  A chain of k divisions (one thread reading R from memory took
 // 38 us for 30 FP64 columns, each subtraction waiting for its loads; 7 us now).
 template <typename T>
-__global__ __launch_bounds__(256) void gm_solve_y(GmDev<T> *st) {
-    __shared__ T R[ck::kMaxRestart * (ck::kMaxRestart + 1)];
+__global__ __launch_bounds__(ck::kGmThreads) void gm_solve_y(int64_t G, const T *__restrict__ partials2,
+                                                  GmDev<T> *st) {
+    __shared__ StepEnd<T> e;
     if (st->final_state != ck::RUN)
         return;
-    const int tid = threadIdx.x, ld = st->m + 1, k = st->j;
+    const int tid = threadIdx.x, m = st->m, ld = m + 1;
+    if (!st->halt) {
+        const int s = st->j;   // every thread reads it before thread 0 moves it on
+        step_end(s, m, G, partials2, st, e);
+        givens_step(s, m, st, e);
+        __threadfence_block();
+        __syncthreads();
+        if (st->final_state != ck::RUN)
+            return;
+    }
+    T *R = e.hr;
+    const int k = st->j;
     T g = tid < k ? st->g[tid] : T(0);
-    for (int t = tid; t < k * ld; t += 256)
+    for (int t = tid; t < k * ld; t += ck::kGmThreads)
         R[t] = st->H[t];
     __syncthreads();
     if (tid >= 64)
@@ -455,15 +529,16 @@ __global__ __launch_bounds__(256) void gm_update_x(int64_t n, double *__restrict
 
 namespace ck {
 
-// Blocks of the Gram-Schmidt passes: 2048 rows each (eight per thread),
-// which keeps the passes at full bandwidth while halving the partials the
-// finish kernels sum (1024 rows per block measured the same pass times).
+// Blocks of the Gram-Schmidt passes: as few rows per thread as kGmMaxBlocks
+// allow, the same for every block.
 int64_t gm_blocks(int64_t n) {
-    int64_t g = ceil_div(n, 2048);
-    if (g < 1)
-        g = 1;
-    return g < kGmMaxBlocks ? g : kGmMaxBlocks;
+    const int64_t rows = std::max<int64_t>(ceil_div(n, (int64_t)kGmThreads * kGmMaxBlocks), 1);
+    return std::max<int64_t>(ceil_div(n, kGmThreads * rows), 1);
 }
+
+// Values of the two partial arrays: one column per basis column and ||w'||^2.
+static int64_t gm_partials1() { return (int64_t)(kMaxRestart + 2) * kGmMaxBlocks; }
+int64_t gm_partials() { return 2 * gm_partials1(); }
 
 static int64_t gm_stream_grid(int64_t n) {
     int64_t g = ceil_div(n, 1024);
@@ -475,7 +550,7 @@ static int64_t gm_stream_grid(int64_t n) {
 template <typename T>
 ck_status launch_gm_cycle_start(int64_t n, const double *r64, T *v0, double *partials64,
                                 GmDev<T> *st, hipStream_t s) {
-    const int64_t G = gm_blocks(n);
+    const int64_t G = dot_blocks<double>(n);
     hipLaunchKernelGGL((gm_start_norm<T>), dim3(G), dim3(256), 0, s, n, G, r64, partials64, st);
     hipLaunchKernelGGL((gm_start_finish<T>), dim3(1), dim3(256), 0, s, G, partials64, st);
     hipLaunchKernelGGL((gm_start_v0<T>), dim3(gm_stream_grid(n)), dim3(256), 0, s, n, v0, r64, st);
@@ -485,46 +560,46 @@ ck_status launch_gm_cycle_start(int64_t n, const double *r64, T *v0, double *par
 
 template <typename T, int NC>
 static void arnoldi_nc(int64_t n, int64_t G, int j, T *V, int64_t ldv, T *w, T *partials,
-                       GmDev<T> *st, unsigned long long *progress, unsigned seq,
+                       int m, GmDev<T> *st, unsigned long long *progress, unsigned seq,
                        hipStream_t s) {
     const int ncols = j + 1;
+    T *partials2 = partials + gm_partials1();
     if (j == 0)
-        hipLaunchKernelGGL((gm_pass1<T, NC>), dim3(G), dim3(256), 0, s, n, G, ncols, V, ldv, w,
+        hipLaunchKernelGGL((gm_pass1<T, NC>), dim3(G), dim3(kGmThreads), 0, s, n, G, ncols, V, ldv, w,
                            partials, st);
     else
-        hipLaunchKernelGGL((gm_pass31<T, NC>), dim3(G), dim3(256), 0, s, n, G, j, V, ldv,
-                           partials, st);
-    hipLaunchKernelGGL((gm_finish_cols<T>), dim3(ncols), dim3(256), 0, s, G, partials, 1, st);
-    hipLaunchKernelGGL((gm_pass2<T, NC>), dim3(G), dim3(256), 0, s, n, G, ncols, V, ldv, w,
-                       partials, st, progress, seq);
-    hipLaunchKernelGGL((gm_finish_givens<T>), dim3(1), dim3(1024), 0, s, G, partials, st);
+        hipLaunchKernelGGL((gm_pass31<T, NC>), dim3(G + 1), dim3(kGmThreads), 0, s, n, G, j, m, V, ldv,
+                           partials2, partials, st);
+    hipLaunchKernelGGL((gm_pass2<T, NC>), dim3(G), dim3(kGmThreads), 0, s, n, G, ncols, V, ldv, w,
+                       partials, partials2, st, progress, seq);
 }
 
 // Step j after the SpMV of column j into column j+1 (column j is v_0 for
 // j = 0, else the previous step's w', see the file comment): ends with
-// w' of step j in column j+1 and h2, u, inv of step j in the state.
+// w' of step j in column j+1 and the partials of its second pass.  partials:
+// gm_partials() values, the first pass's, then the second's.
 template <typename T>
-ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, GmDev<T> *st,
+ck_status launch_gm_arnoldi(int64_t n, int j, int m, T *V, int64_t ldv, T *partials, GmDev<T> *st,
                             unsigned long long *progress, unsigned seq, hipStream_t s) {
     const int64_t G = gm_blocks(n);
     const int ncols = j + 1;
     T *w = V + (int64_t)(j + 1) * ldv;
     if (ncols <= 8)
-        arnoldi_nc<T, 8>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 8>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 16)
-        arnoldi_nc<T, 16>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 16>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 24)
-        arnoldi_nc<T, 24>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 24>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 32)
-        arnoldi_nc<T, 32>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 32>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 40)
-        arnoldi_nc<T, 40>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 40>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 48)
-        arnoldi_nc<T, 48>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 48>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 56)
-        arnoldi_nc<T, 56>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 56>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else if (ncols <= 64)
-        arnoldi_nc<T, 64>(n, G, j, V, ldv, w, partials, st, progress, seq, s);
+        arnoldi_nc<T, 64>(n, G, j, V, ldv, w, partials, m, st, progress, seq, s);
     else
         return fail(CK_E_INVALID, "restart length above %d", kMaxRestart);
     CK_HIP(hipGetLastError());
@@ -532,9 +607,10 @@ ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, Gm
 }
 
 template <typename T>
-ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmDev<T> *st,
-                              hipStream_t s) {
-    hipLaunchKernelGGL((gm_solve_y<T>), dim3(1), dim3(256), 0, s, st);
+ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, const T *partials,
+                              GmDev<T> *st, hipStream_t s) {
+    hipLaunchKernelGGL((gm_solve_y<T>), dim3(1), dim3(kGmThreads), 0, s, gm_blocks(n),
+                       partials + gm_partials1(), st);
     hipLaunchKernelGGL((gm_update_x<T>), dim3(gm_stream_grid(n)), dim3(256), 0, s, n, x, V, ldv,
                        st);
     CK_HIP(hipGetLastError());
@@ -544,10 +620,10 @@ ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmD
 #define CK_GM_INST(T)                                                                          \
     template ck_status launch_gm_cycle_start<T>(int64_t, const double *, T *, double *,        \
                                                 GmDev<T> *, hipStream_t);                      \
-    template ck_status launch_gm_arnoldi<T>(int64_t, int, T *, int64_t, T *, GmDev<T> *,       \
+    template ck_status launch_gm_arnoldi<T>(int64_t, int, int, T *, int64_t, T *, GmDev<T> *,  \
                                             unsigned long long *, unsigned, hipStream_t);      \
     template ck_status launch_gm_cycle_end<T>(int64_t, double *, const T *, int64_t,           \
-                                              GmDev<T> *, hipStream_t);
+                                              const T *, GmDev<T> *, hipStream_t);
 CK_GM_INST(double)
 CK_GM_INST(float)
 

@@ -18,9 +18,12 @@ constexpr int kRowBlocks = kMaxPartials;
 // Up to this many partials a following kernel sums in each of its blocks, so
 // that no one-block finish is launched between the two.
 constexpr int kFoldPartials = 2048;
-// GMRES Gram-Schmidt passes: at most this many blocks, one partial per
-// block and basis column.
-constexpr int kGmMaxBlocks = 2048;
+// GMRES Gram-Schmidt passes: blocks of kGmThreads, at most one per compute
+// unit (eight waves there, each with a load of every column in flight, keep
+// the memory busy), one partial per block and basis column.  Every block of
+// the next pass sums them all, so they are kept few.
+constexpr int kGmThreads = 512;
+constexpr int kGmMaxBlocks = 256;
 
 // Run states shared by the solvers
 enum : int { RUN = 0, CONVERGED = 1, BREAKDOWN = 2, BUDGET = 3 };
@@ -51,19 +54,18 @@ template <typename T>
 struct GmDev {
     T H[(kMaxRestart + 1) * kMaxRestart];
     T cs[kMaxRestart], sn[kMaxRestart];
-    T g[kMaxRestart + 1];
+    T res[kMaxRestart + 1];     // res[j]: residual component before rotation j
+    T g[kMaxRestart];           // the rotated right-hand side
     T y[kMaxRestart];
     T Hraw[(kMaxRestart + 1) * kMaxRestart];   // H before the rotations
-    T h1[kMaxRestart + 1];      // first Gram-Schmidt pass
-    T h2[kMaxRestart + 1];      // second pass
-    T u[kMaxRestart + 2];       // Hbar_j h2: A (V_j h2) = V_{j+1} u
-    T inv;                      // 1 / h_{j+1,j}
+    T h1[kMaxRestart + 1];      // first Gram-Schmidt pass of the last step
     double beta;                // ||r|| at the cycle start (FP64 true residual)
     double inv_beta;            // 1 / beta
     double bnorm, tol, relres;  // relres: last estimate or true value
     int m;
     int j;                      // Arnoldi steps done in this cycle
     int iter;                   // total Arnoldi steps
+    int iter0;                  // of them before this cycle
     int max_iter;
     int cycle_stop;             // RUN, CONVERGED (estimate), BREAKDOWN (happy), BUDGET
     int final_state;            // RUN, CONVERGED, BREAKDOWN (singular), BUDGET

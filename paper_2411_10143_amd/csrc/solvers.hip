@@ -690,7 +690,7 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
     GmDev<T> *st;
     Fp64Scratch f;
     CK_TRY(ws.get(&V, ldv * (m + 1)));
-    CK_TRY(ws.get(&partials, (int64_t)(kMaxRestart + 1) * kGmMaxBlocks));
+    CK_TRY(ws.get(&partials, gm_partials()));
     CK_TRY(ws.get(&r64, M.n));
     CK_TRY(ws.get(&st, 1));
     CK_TRY(f.init(ws, c.s));
@@ -743,7 +743,7 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
             CK_TRY(spmv<T>(c, T(1), V + (int64_t)j * ldv, T(0), V + (int64_t)(j + 1) * ldv,
                            halt_ptr));
             ++issued;
-            CK_TRY(launch_gm_arnoldi<T>(M.n, j, V, ldv, partials, st, pin.progress(), issued,
+            CK_TRY(launch_gm_arnoldi<T>(M.n, j, m, V, ldv, partials, st, pin.progress(), issued,
                                         c.s));
             Report rep = read_report(pin.progress());
             if (issued - ahead > 0)
@@ -757,7 +757,7 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
         }
         if (ended)
             break;
-        CK_TRY(launch_gm_cycle_end<T>(M.n, x, V, ldv, st, c.s));
+        CK_TRY(launch_gm_cycle_end<T>(M.n, x, V, ldv, partials, st, c.s));
         // a cycle that ends on the budget is followed by at most one more start
         if (issued > h->max_iter + 2 * m)
             break;

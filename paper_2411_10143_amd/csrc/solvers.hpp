@@ -33,14 +33,15 @@ ck_status launch_fill(int64_t n, T *dst, T v, hipStream_t s);
 
 // GMRES(m) pieces; V holds m+1 basis columns of length ldv.
 int64_t gm_blocks(int64_t n);
+int64_t gm_partials();   // values of the Gram-Schmidt passes' partials
 template <typename T>
 ck_status launch_gm_cycle_start(int64_t n, const double *r64, T *v0, double *partials64,
                                 GmDev<T> *st, hipStream_t s);
 template <typename T>
-ck_status launch_gm_arnoldi(int64_t n, int j, T *V, int64_t ldv, T *partials, GmDev<T> *st,
+ck_status launch_gm_arnoldi(int64_t n, int j, int m, T *V, int64_t ldv, T *partials, GmDev<T> *st,
                             unsigned long long *progress, unsigned seq, hipStream_t s);
 template <typename T>
-ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, GmDev<T> *st,
-                              hipStream_t s);
+ck_status launch_gm_cycle_end(int64_t n, double *x, const T *V, int64_t ldv, const T *partials,
+                              GmDev<T> *st, hipStream_t s);
 
 }  // namespace ck
