@@ -8,6 +8,7 @@
 #include "matrix.hpp"
 #include "devcache.hpp"
 #include "diahyb.hpp"
+#include "batched.hpp"
 #include "panel.hpp"
 #include "predictor.hpp"
 #include "solvers.hpp"
@@ -70,6 +71,8 @@ static void release(ck_matrix *M) {
     mat_free(*M, M->merge_plan);
     mat_free(*M, M->panel_plan);
     mat_free(*M, M->panel_row);
+    mat_free(*M, M->slot_mem[0]);
+    mat_free(*M, M->slot_mem[1]);
     mat_free(*M, M->devsel_scratch);
     mat_free(*M, M->panel_boff);
     for (auto &kv : M->carry)
@@ -119,6 +122,48 @@ static ck_status mark_built(std::atomic<bool> &flag, hipStream_t s) {
     return CK_OK;
 }
 
+ck_status ensure_max_row(ck_matrix &M, hipStream_t s) {
+    if (M.max_row >= 0)
+        return CK_OK;
+    if (M.n == 0) {
+        M.max_row = 0;
+        return CK_OK;
+    }
+    unsigned long long *d = nullptr;
+    unsigned long long h = 0;
+    CK_TRY(mat_alloc(M, &d, 1, s));
+    ck_status st = launch_fill<int>(2, (int *)d, 0, s);
+    if (st == CK_OK)
+        st = launch_row_max(M.n, M.rp, d, s);
+    if (st == CK_OK && hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess)
+        st = fail(CK_E_HIP, "row-length read-back failed");
+    if (hipStreamSynchronize(s) != hipSuccess && st == CK_OK)
+        st = fail(CK_E_HIP, "row-length pass failed");
+    mat_free(M, d);
+    CK_TRY(st);
+    M.max_row = (int64_t)h;
+    return CK_OK;
+}
+
+ck_status build_slot_copy(ck_matrix &M, bool fp32, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(M.mu);
+    if (M.has_slot[fp32].load())
+        return CK_OK;
+    CK_TRY(ensure_max_row(M, s));
+    M.slot_max_row = M.max_row;
+    const int vb = fp32 ? 4 : 8;
+    CK_TRY(mat_alloc(M, &M.slot_mem[fp32], slot_copy_bytes(M.n, M.nnz, M.slot_max_row, vb), s));
+    const ck_status st = launch_slot_copy(
+        M.n, M.rp, M.col, M.val, fp32 ? M.val32 : nullptr,
+        slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.slot_max_row, vb), s);
+    if (st != CK_OK) {
+        mat_free(M, M.slot_mem[fp32]);
+        M.slot_mem[fp32] = nullptr;
+        return st;
+    }
+    return mark_built(M.has_slot[fp32], s);
+}
+
 // Builds the ELL, COO, DIA, HYB or CSR-panel copy (or the merge-path
 // partition) a configuration needs (idempotent); returns when it is built.
 ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
@@ -134,6 +179,7 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             return CK_OK;
         if (!M.merge_plan)
             CK_TRY(mat_alloc(M, &M.merge_plan, merge_plan_ints(M.n, M.nnz), s));
+        CK_TRY(ensure_max_row(M, s));
         M.merge_cut = merge_cuts_rows(M.max_row);
         CK_TRY(launch_merge_plan(M.n, M.nnz, M.rp, M.merge_plan, s));
         return mark_built(M.has_merge_plan, s);
@@ -145,6 +191,7 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
         const int64_t N8 = (int64_t)P8 * M.n;   // the most panel rows P can give
         if (N8 + 1 > (int64_t)std::numeric_limits<int32_t>::max())
             return fail(CK_E_UNSUPPORTED, "too many panel rows");
+        CK_TRY(ensure_max_row(M, s));
         int *tmp = nullptr;
         CK_TRY(mat_alloc(M, &tmp, N8 + 2 + panel_scan_tmp_elems(N8), s));
         int P = P8;
@@ -233,21 +280,7 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
     }
     if (M.has_ell.load())
         return CK_OK;
-    if (M.max_row < 0) {
-        unsigned long long *d = nullptr;
-        unsigned long long h = 0;
-        CK_TRY(mat_alloc(M, &d, 1, s));
-        ck_status st = launch_fill<int>(2, (int *)d, 0, s);
-        if (st == CK_OK)
-            st = launch_row_max(M.n, M.rp, d, s);
-        if (st == CK_OK && hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess)
-            st = fail(CK_E_HIP, "row-length read-back failed");
-        if (hipStreamSynchronize(s) != hipSuccess && st == CK_OK)
-            st = fail(CK_E_HIP, "row-length pass failed");
-        mat_free(M, d);
-        CK_TRY(st);
-        M.max_row = (int64_t)h;
-    }
+    CK_TRY(ensure_max_row(M, s));
     const int64_t K = M.max_row;
     const int64_t pitch = ceil_div(M.n, 64) * 64;
     if (K * pitch > 8 * M.nnz)

@@ -162,8 +162,8 @@ constexpr int resident_rows() { return BS >= 1024 ? 8 : 4; }
 
 template <typename T, int BS>
 struct SlotLds {
-    T p[BS * resident_rows<BS>()];   // the vector multiplied
-    T q[BS * resident_rows<BS>()];   // its product
+    T p[BS * resident_rows<BS>() + 1];   // the vector multiplied, then one zero
+    T q[BS * resident_rows<BS>()];       // its product
     T red[2][BS / 64];
     T wred[BS / 64][ck::kBMaxM + 1];
     T h[ck::kBMaxM + 1], hsum[ck::kBMaxM + 1];
@@ -190,12 +190,80 @@ __device__ __forceinline__ T wg_sum_alt(T v, T (&red)[2][BS / 64], int &parity) 
     return r;
 }
 
+// lds.q = A lds.p from the slot copy: a wave takes slices w, w + BS / 64, ...,
+// a lane one row, its entries summed in ascending order (the bits of wg_spmv
+// with one lane per row).  Eight entries of a row are loaded while the eight
+// before them are gathered and multiplied.  One workgroup's products are bound
+// by the instructions it issues: a slot costs two loads, an LDS gather and two
+// vector instructions here, where lanes sharing CSR rows need about 25 an
+// entry (n = 7,000, 19 entries a row, FP32: 28 us a product before, @P@ us now).
+template <typename T, int BS>
+__device__ __forceinline__ void slot_product(int n, const ck::SlotCopy &c, SlotLds<T, BS> &lds) {
+    constexpr int U = 8;
+    const int tid = thread_index(), lane = tid & 63;
+    const int *base = uni(c.base);
+    const unsigned short *col = uni(c.col);
+    const T *val = uni((const T *)c.val);
+    const int slices = (n + 63) / 64;
+    for (int sl = uni(tid >> 6); sl < slices; sl += BS / 64) {
+        const int k0 = uni(base[sl]), K = uni((base[sl + 1] - base[sl]) >> 6);
+        const unsigned short *cp = col + k0;
+        const T *vp = val + k0;
+        const int at = sl * 64 + lane;
+        const int row = at < n ? uni(c.perm)[(unsigned)at] : 0;
+        T acc = 0, v[U];
+        unsigned short cc[U];
+        auto fetch = [&](int t) {   // entries t .. t + 7 of the lane's row; K >= 1 here
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int o = 64 * min(t + u, K - 1);
+                cc[u] = (cp + o)[(unsigned)lane];
+                v[u] = (vp + o)[(unsigned)lane];
+            }
+        };
+        if (K > 0)
+            fetch(0);
+        for (int t = 0; t < K; t += U) {
+            T vv[U];
+            int ci[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                vv[u] = v[u];
+                ci[u] = cc[u];
+            }
+            if (t + U < K)
+                fetch(t + U);
+            T g[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                g[u] = lds.p[ci[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t + u < K)   // uniform over the wave
+                    acc += vv[u] * g[u];
+        }
+        if (at < n)
+            lds.q[row] = acc;
+    }
+}
+
+// lds.q = A lds.p in the inner type
+template <typename T, int BS>
+__device__ __forceinline__ void inner_product(const ck::BSlot *s, int n, const T *val,
+                                              SlotLds<T, BS> &lds) {
+    if (s->sell.base != nullptr)
+        slot_product<T, BS>(n, s->sell, lds);
+    else   // no room for the copy: the same sums from the CSR arrays
+        wg_spmv<BS, T, T, T>(n, 1, s->rp, s->col, val, lds.p, T(1), T(0), (const T *)nullptr,
+                             lds.q);
+}
+
 // CG steps of a slot in phase B_INNER until it leaves the phase or `budget`
 // steps are done; returns the steps, and the new phase in *phase.
 template <typename T, int BS>
 __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> &lds, int *phase) {
     constexpr int R = resident_rows<BS>();
-    const int tid = thread_index(), n = uni(s->n), L = uni(s->lanes);
+    const int tid = thread_index(), n = uni(s->n);
     T *r = wsp<T>(s, 0), *p = wsp<T>(s, 1), *d = wsp<T>(s, 3);
     const T *val = sizeof(T) == 4 ? (const T *)s->val32 : (const T *)s->val64;
     T rr[R], pr[R], dr[R];
@@ -210,6 +278,8 @@ __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> 
         else
             lds.p[i] = pr[u];
     }
+    if (tid == 0)
+        lds.p[n] = 0;
     T rho = (T)s->rho;
     int inner = s->inner_iter, iter = s->iter, parity = 0, steps = 0, next = ck::B_INNER;
     const int inner_cap = s->inner_cap, max_iter = s->max_iter;
@@ -219,8 +289,7 @@ __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> 
         const int tid = thread_index();
         ++steps;
         __syncthreads();   // lds.p is complete
-        wg_spmv<BS, T, T, T>(n, L, s->rp, s->col, val, lds.p, T(1), T(0), (const T *)nullptr,
-                             lds.q);
+        inner_product<T, BS>(s, n, val, lds);
         __syncthreads();
         T q[R], pq = 0;
 #pragma unroll
@@ -344,7 +413,7 @@ __device__ __forceinline__ void basis_sweep(int n, int j, const T *__restrict__ 
 template <typename T, int BS>
 __device__ __forceinline__ int slot_gmres(ck::BSlot *s, int budget, SlotLds<T, BS> &lds, int *phase) {
     constexpr int R = resident_rows<BS>(), NW = BS / 64;
-    const int tid = thread_index(), n = uni(s->n), L = uni(s->lanes), m = uni(s->m);
+    const int tid = thread_index(), n = uni(s->n), m = uni(s->m);
     const int64_t ld = uni((int)s->ld);
     T *V = uni(wsp<T>(s, 0));
     const T *val = sizeof(T) == 4 ? (const T *)s->val32 : (const T *)s->val64;
@@ -356,6 +425,8 @@ __device__ __forceinline__ int slot_gmres(ck::BSlot *s, int budget, SlotLds<T, B
         if (i < n)
             lds.p[i] = V[(int64_t)j * ld + i];
     }
+    if (tid == 0)
+        lds.p[n] = 0;
     if (tid < j) {
         lds.cs[tid] = (T)s->cs[tid];
         lds.sn[tid] = (T)s->sn[tid];
@@ -365,8 +436,7 @@ __device__ __forceinline__ int slot_gmres(ck::BSlot *s, int budget, SlotLds<T, B
         const int tid = thread_index();
         ++steps;
         __syncthreads();   // lds.p is complete
-        wg_spmv<BS, T, T, T>(n, L, s->rp, s->col, val, lds.p, T(1), T(0), (const T *)nullptr,
-                             lds.q);
+        inner_product<T, BS>(s, n, val, lds);
         __syncthreads();
         T w[R];
 #pragma unroll
@@ -850,7 +920,107 @@ __global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat 
     run_slot<T, 256>(slots, stat, which, budget, *(SlotLds<T, 256> *)raw);
 }
 
+// Builds a slot copy in one workgroup: the rows sorted by length with a bitonic
+// sort of (8192 - length, row) in LDS, the slice offsets, then the entries,
+// slice by slice and slot-major (coalesced stores).
+template <typename T>
+__global__ __launch_bounds__(1024) void slot_sell(int n, const int *__restrict__ rp,
+                                                  const int *__restrict__ col,
+                                                  const T *__restrict__ val,
+                                                  int *__restrict__ base,
+                                                  unsigned short *__restrict__ perm,
+                                                  unsigned short *__restrict__ scol,
+                                                  T *__restrict__ sval) {
+    static_assert(ck::kSlotRows == 8192, "13 bits of row in a key");
+    __shared__ unsigned key[ck::kSlotRows];
+    __shared__ int sb[ck::kSlotRows / 64 + 1];
+    const int tid = threadIdx.x;
+    int n2 = 64;
+    while (n2 < n)
+        n2 <<= 1;
+    for (int i = tid; i < n2; i += 1024)   // a row has at most n <= 8192 entries
+        key[i] = i < n ? (unsigned)(ck::kSlotRows - (rp[i + 1] - rp[i])) << 13 | i : ~0u;
+    __syncthreads();
+    for (int k = 2; k <= n2; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = tid; t < n2 / 2; t += 1024) {
+                const int a = 2 * t - (t & (j - 1)), b = a + j;
+                const unsigned x = key[a], y = key[b];
+                if ((x > y) == ((a & k) == 0)) {
+                    key[a] = y;
+                    key[b] = x;
+                }
+            }
+            __syncthreads();
+        }
+    const int slices = (n + 63) / 64;
+    if (tid == 0) {
+        int at = 0;
+        for (int sl = 0; sl < slices; ++sl) {
+            sb[sl] = at;
+            at += 64 * (ck::kSlotRows - (int)(key[64 * sl] >> 13));
+        }
+        sb[slices] = at;
+    }
+    __syncthreads();
+    for (int i = tid; i <= slices; i += 1024)
+        base[i] = sb[i];
+    for (int i = tid; i < n; i += 1024)
+        perm[i] = (unsigned short)(key[i] & (ck::kSlotRows - 1));
+    const int lane = tid & 63;
+    for (int sl = tid >> 6; sl < slices; sl += 16) {
+        const int at = 64 * sl + lane;
+        const int row = at < n ? (int)(key[at] & (ck::kSlotRows - 1)) : 0;
+        const int k0 = at < n ? rp[row] : 0, len = at < n ? rp[row + 1] - k0 : 0;
+        const int K = (sb[sl + 1] - sb[sl]) / 64;
+        for (int t = 0; t < K; ++t) {
+            const bool in = t < len;
+            scol[sb[sl] + 64 * t + lane] = (unsigned short)(in ? col[k0 + t] : n);
+            sval[sb[sl] + 64 * t + lane] = in ? val[k0 + t] : T(0);
+        }
+    }
+}
+
 namespace ck {
+
+static int64_t slot_capacity(int64_t nnz, int64_t max_row) { return nnz + 64 * max_row; }
+static int64_t up256(int64_t b) { return (b + 255) / 256 * 256; }
+
+int64_t slot_copy_bytes(int64_t n, int64_t nnz, int64_t max_row, int value_bytes) {
+    const int64_t cap = slot_capacity(nnz, max_row);
+    return up256(4 * (n / 64 + 2)) + up256(2 * n) + up256(2 * cap) + cap * value_bytes;
+}
+
+SlotCopy slot_copy_at(void *mem, int64_t n, int64_t nnz, int64_t max_row, int value_bytes) {
+    char *p = (char *)mem;
+    SlotCopy c;
+    c.base = (const int *)p;
+    p += up256(4 * (n / 64 + 2));
+    c.perm = (const unsigned short *)p;
+    p += up256(2 * n);
+    c.col = (const unsigned short *)p;
+    p += up256(2 * slot_capacity(nnz, max_row));
+    c.val = p;
+    return c;
+}
+
+ck_status launch_slot_copy(int64_t n, const int *rp, const int *col, const double *val64,
+                           const float *val32, const SlotCopy &c, hipStream_t s) {
+    if (n < 1 || n > kSlotRows)
+        return fail(CK_E_INVALID, "a slot copy takes 1..%d rows", kSlotRows);
+    auto go = [&](auto *val) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(val)>>;
+        hipLaunchKernelGGL((slot_sell<T>), dim3(1), dim3(1024), 0, s, (int)n, rp, col, val,
+                           (int *)c.base, (unsigned short *)c.perm, (unsigned short *)c.col,
+                           (T *)c.val);
+    };
+    if (val32)
+        go(val32);
+    else
+        go(val64);
+    CK_HIP(hipGetLastError());
+    return CK_OK;
+}
 
 int64_t bslot_work_elems(int kind, int64_t n, int m) {
     const int64_t ld = ceil_div(std::max<int64_t>(n, 1), 64) * 64;

@@ -9,6 +9,26 @@ constexpr int kBMaxM = 32;            // largest GMRES restart in the batched pa
 enum : int { B_CG = 0, B_GMRES = 1 };
 enum : int { B_OUTER = 0, B_INNER = 1, B_UPDATE = 2, B_DONE = 3 };
 
+// Slot copy of a small matrix (at most kSlotRows rows), read by the inner
+// products: sliced ELLPACK with the rows sorted by length, longest first (ties
+// by row), 64 to a slice, one lane per row.  Slice s holds slots base[s] ..
+// base[s + 1] - 1, slot-major (64 lanes of entry 0, of entry 1, ...), K_s = its
+// first row's length; columns are 16 bits, padding has column n (a zero kept
+// behind the vector in LDS) and value 0; perm[64 s + lane] = the row.  The
+// entries and their padding take at most nnz + 64 * (longest row) slots.
+constexpr int kSlotRows = 8192;
+struct SlotCopy {
+    const int *base = nullptr;              // ceil(n / 64) + 1; null: no copy
+    const unsigned short *perm = nullptr;   // n, in slice order
+    const unsigned short *col = nullptr;
+    const void *val = nullptr;              // inner type
+};
+// Bytes of a copy, its pieces within a block, and building it on s.
+int64_t slot_copy_bytes(int64_t n, int64_t nnz, int64_t max_row, int value_bytes);
+SlotCopy slot_copy_at(void *mem, int64_t n, int64_t nnz, int64_t max_row, int value_bytes);
+ck_status launch_slot_copy(int64_t n, const int *rp, const int *col, const double *val64,
+                           const float *val32, const SlotCopy &c, hipStream_t s);
+
 struct BSlot {
     // problem, set at admission
     int kind, n, lanes, m;
@@ -16,6 +36,7 @@ struct BSlot {
     const int *col;
     const double *val64;
     const float *val32;
+    SlotCopy sell;        // of val32 (FP32 inner solves) or val64; base null: none
     const double *b;
     double *x;            // caller's solution vector (holds x0 on admission)
     double *r64;          // FP64 residual

@@ -78,6 +78,10 @@ struct ck_matrix {
     int hyb_L = 1;
     std::atomic<bool> has_hyb{false};
     int64_t max_row = -1;             // longest row, once known
+    // slot copies (batched.hpp) of a small matrix, FP64 and FP32 values
+    char *slot_mem[2] = {nullptr, nullptr};
+    int64_t slot_max_row = 0;         // the longest row their layout assumes
+    std::atomic<bool> has_slot[2] = {false, false};
     // feature scratch of the device-resident cascade (kept with the handle)
     char *devsel_scratch = nullptr;
     int64_t *devsel_ints = nullptr;
@@ -121,6 +125,12 @@ struct SpmvArgs {
     T *dot_partials = nullptr;
     void *carry = nullptr;
 };
+
+// The longest row of M, counted (and remembered) if it is not known yet.
+ck_status ensure_max_row(ck_matrix &M, hipStream_t s);
+// Builds M's slot copy (of the FP32 values if fp32; M.n <= kSlotRows) if it is
+// not there yet; returns when it is built.  Its bytes: slot_bytes_of.
+ck_status build_slot_copy(ck_matrix &M, bool fp32, hipStream_t s);
 
 bool config_valid(const ck_config &c);
 bool spmv_fuses_dot(const ck_config &c);

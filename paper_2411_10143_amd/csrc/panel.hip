@@ -307,8 +307,6 @@ int panel_count_for(int64_t ncols, int value_bytes) {
 // 4 MB slice: 465 -> 483 us).
 constexpr int64_t kSliceP4 = 5 * (int64_t(1) << 19);   // 2.5 MB
 
-ck_status launch_row_max(int64_t n, const int *rp, unsigned long long *out, hipStream_t s);
-
 ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
                              bool *counted) {
     const int P8 = panel_count_for(M.ncols, 8);
@@ -316,18 +314,7 @@ ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P
     *counted = false;
     if (P8 != 8 || M.n == 0 || M.ncols * 8 > 4 * kSliceP4)
         return CK_OK;
-    // the longest row (known after the feature pass; else one pass over rowptr)
-    int64_t max_r = M.max_row;
-    if (max_r < 0) {
-        unsigned long long *d = (unsigned long long *)tmp;
-        unsigned long long h = 0;
-        CK_TRY(launch_fill<int>(2, (int *)d, 0, s));
-        CK_TRY(launch_row_max(M.n, M.rp, d, s));
-        CK_HIP(hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, s));
-        CK_HIP(hipStreamSynchronize(s));
-        max_r = (int64_t)h;
-    }
-    if (max_r > 4 * ceil_div(M.nnz, M.n))
+    if (M.max_row > 4 * ceil_div(M.nnz, M.n))
         return CK_OK;
     const int64_t N4 = 4 * M.n;
     const int64_t W4 = ceil_div(std::max<int64_t>(M.ncols, 1), 4);

@@ -10,7 +10,7 @@ namespace ck {
 int panel_count_for(int64_t ncols, int value_bytes);
 int64_t panel_scan_tmp_elems(int64_t N);
 // The panel count of M's CSR-panel copy: panel_count_for(ncols, 8), or 4
-// (see panel.hip).  tmp: scratch of at least panel_count_for(ncols, 8) * n
+// (see panel.hip); M.max_row is known.  tmp: scratch of at least panel_count_for(ncols, 8) * n
 // + 2 ints; returns when decided.  *counted: tmp[0 .. P n) already holds the
 // chosen P's per-row panel counts (true when P = 4 was chosen).
 ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
