@@ -170,6 +170,7 @@ struct SlotLds {
     T cs[ck::kBMaxM], sn[ck::kBMaxM];
     T inv;
     int stop;
+    int base[BS * resident_rows<BS>() / 64 + 1];   // slice offsets of the slot copy
 };
 
 // wg_sum with one barrier: successive calls alternate between two buffers, so
@@ -192,54 +193,69 @@ __device__ __forceinline__ T wg_sum_alt(T v, T (&red)[2][BS / 64], int &parity) 
 
 // lds.q = A lds.p from the slot copy: a wave takes slices w, w + BS / 64, ...,
 // a lane one row, its entries summed in ascending order (the bits of wg_spmv
-// with one lane per row).  Eight entries of a row are loaded while the eight
-// before them are gathered and multiplied.  One workgroup's products are bound
-// by the instructions it issues: a slot costs two loads, an LDS gather and two
-// vector instructions here, where lanes sharing CSR rows need about 25 an
-// entry (n = 7,000, 19 entries a row, FP32: 28 us a product before, @P@ us now).
+// with one lane per row).  The next eight entries (FP64: four) of the slice,
+// or of the wave's next slice, are loaded while those before them are gathered
+// and multiplied.  One
+// workgroup's products are bound by the instructions it issues: a slot costs
+// two loads, an LDS gather and two vector instructions here, where lanes
+// sharing CSR rows need about 25 an entry (n = 7,000, 19 entries a row, mixed
+// GMRES: 82 us a step before, 45 with the copy).
 template <typename T, int BS>
 __device__ __forceinline__ void slot_product(int n, const ck::SlotCopy &c, SlotLds<T, BS> &lds) {
-    constexpr int U = 8;
+    constexpr int U = sizeof(T) == 4 ? 8 : 4, NW = BS / 64;
     const int tid = thread_index(), lane = tid & 63;
-    const int *base = uni(c.base);
-    const unsigned short *col = uni(c.col);
+    const unsigned short *col = uni(c.col), *perm = uni(c.perm);
     const T *val = uni((const T *)c.val);
     const int slices = (n + 63) / 64;
-    for (int sl = uni(tid >> 6); sl < slices; sl += BS / 64) {
-        const int k0 = uni(base[sl]), K = uni((base[sl + 1] - base[sl]) >> 6);
+    T v[U];
+    unsigned short cc[U];
+    int row = 0, nrow = 0;
+    // entries t .. t + 7 (as far as there are) of the lane's row of slots k0 ..
+    // k0 + 64 K - 1, K >= 1
+    auto fetch = [&](int k0, int K, int t) {
         const unsigned short *cp = col + k0;
         const T *vp = val + k0;
-        const int at = sl * 64 + lane;
-        const int row = at < n ? uni(c.perm)[(unsigned)at] : 0;
-        T acc = 0, v[U];
-        unsigned short cc[U];
-        auto fetch = [&](int t) {   // entries t .. t + 7 of the lane's row; K >= 1 here
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int o = 64 * min(t + u, K - 1);
-                cc[u] = (cp + o)[(unsigned)lane];
-                v[u] = (vp + o)[(unsigned)lane];
+        for (int u = 0; u < U; ++u)
+            if (t + u < K) {   // uniform over the wave
+                cc[u] = (cp + 64 * (t + u))[(unsigned)lane];
+                v[u] = (vp + 64 * (t + u))[(unsigned)lane];
             }
-        };
+    };
+    int sl = uni(tid >> 6);
+    int k0 = 0, K = 0;
+    auto open = [&](int s) {   // slice s: its extent, the lane's row, its first entries
+        k0 = uni(lds.base[s]);
+        K = (uni(lds.base[s + 1]) - k0) >> 6;
+        nrow = perm[(unsigned)min(s * 64 + lane, n - 1)];
         if (K > 0)
-            fetch(0);
-        for (int t = 0; t < K; t += U) {
-            T vv[U];
-            int ci[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                vv[u] = v[u];
-                ci[u] = cc[u];
-            }
-            if (t + U < K)
-                fetch(t + U);
-            T g[U];
+            fetch(k0, K, 0);
+    };
+    if (sl < slices)
+        open(sl);
+    while (sl < slices) {
+        const int at = sl * 64 + lane, K0 = K, first = k0;
+        row = nrow;
+        sl += NW;
+        T acc = 0;
+        if (K0 == 0 && sl < slices)
+            open(sl);
+        for (int t = 0; t < K0; t += U) {
+            T vv[U], g[U];
+            const int left = K0 - t;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                g[u] = lds.p[ci[u]];
+                if (u < left) {
+                    vv[u] = v[u];
+                    g[u] = lds.p[cc[u]];
+                }
+            if (t + U < K0)
+                fetch(first, K0, t + U);
+            else if (sl < slices)
+                open(sl);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (t + u < K)   // uniform over the wave
+                if (u < left)
                     acc += vv[u] * g[u];
         }
         if (at < n)
@@ -280,10 +296,12 @@ __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> 
     }
     if (tid == 0)
         lds.p[n] = 0;
+    if (s->sell.base != nullptr && tid <= (n + 63) / 64)
+        lds.base[tid] = s->sell.base[tid];
     T rho = (T)s->rho;
     int inner = s->inner_iter, iter = s->iter, parity = 0, steps = 0, next = ck::B_INNER;
     const int inner_cap = s->inner_cap, max_iter = s->max_iter;
-    const double inner_tol = s->inner_tol;
+    const double tol2 = s->inner_tol * s->inner_tol;
     bool broken = false;
     while (steps < budget && next == ck::B_INNER) {
         const int tid = thread_index();
@@ -314,7 +332,7 @@ __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> 
         }
         const T rho_new = wg_sum_alt<BS>(rn, lds.red, parity);
         ++inner;
-        const bool stop = sqrt((double)rho_new) <= inner_tol || inner >= inner_cap ||
+        const bool stop = (double)rho_new <= tol2 || inner >= inner_cap ||
                           iter + 1 >= max_iter;
         ++iter;
         const T beta = rho_new / rho;
@@ -352,55 +370,75 @@ __device__ __forceinline__ int slot_cg(ck::BSlot *s, int budget, SlotLds<T, BS> 
     return steps;
 }
 
-// One sweep over basis columns 0 .. j of the thread's rows, eight columns at a
-// time: DOT adds V_c . w to lds.wred, else w -= h_c V_c.
+// C basis columns g .. g + C - 1 of the thread's rows: DOT adds V_c . w to
+// lds.wred, else w -= h_c V_c.  The columns of U rows are in flight together.
+template <int C, bool DOT, typename T, int BS>
+__device__ __forceinline__ void basis_columns(int n, int g, const T *__restrict__ V, int64_t ld,
+                                              T (&w)[resident_rows<BS>()], SlotLds<T, BS> &lds) {
+    constexpr int R = resident_rows<BS>();
+    constexpr int most = sizeof(T) == 4 ? 32 : 16;   // loads in flight
+    constexpr int U = most / C < R ? most / C : R;
+    const int tid = thread_index();
+    T acc[C], h[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        acc[c] = 0;
+        h[c] = DOT ? T(0) : lds.h[g + c];
+    }
+#pragma unroll
+    for (int u0 = 0; u0 < R; u0 += U) {
+        if (u0 * BS < n) {
+            T vv[U][C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const T *Vc = V + (int64_t)(g + c) * ld;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    vv[u][c] = Vc[(unsigned)min(tid + (u0 + u) * BS, n - 1)];
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the loads are in flight together
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    if (DOT)
+                        acc[c] += vv[u][c] * w[u0 + u];   // w is 0 past the last row
+                    else
+                        w[u0 + u] -= h[c] * vv[u][c];
+                }
+        }
+    }
+    if (DOT) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const T v = ck::wave_sum_last(acc[c]);   // valid in lane 63
+            if ((tid & 63) == 63)
+                lds.wred[tid >> 6][g + c] = v;
+        }
+    }
+}
+
+// One sweep over basis columns 0 .. j: groups of eight, then four, two, one.
 template <bool DOT, typename T, int BS>
 __device__ __forceinline__ void basis_sweep(int n, int j, const T *__restrict__ V, int64_t ld,
                                             T (&w)[resident_rows<BS>()], SlotLds<T, BS> &lds) {
     constexpr int R = resident_rows<BS>();
-    constexpr int U = sizeof(T) == 4 ? 4 : 2;   // rows in flight, 8 columns of each
-    const int tid = thread_index();
-    for (int g = 0; g <= j; g += 8) {
-        T acc[8], h[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            acc[c] = 0;
-            h[c] = !DOT && g + c <= j ? lds.h[min(g + c, j)] : T(0);
-        }
-#pragma unroll
-        for (int u0 = 0; u0 < R; u0 += U) {
-            if (u0 * BS < n) {
-                T vv[U][8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const T *Vc = V + (int64_t)min(g + c, j) * ld;
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        vv[u][c] = Vc[(unsigned)min(tid + (u0 + u) * BS, n - 1)];
-                }
-                __builtin_amdgcn_sched_barrier(0);   // the loads are in flight together
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        if (DOT)
-                            acc[c] += vv[u][c] * w[u0 + u];   // w is 0 past the last row
-                        else
-                            w[u0 + u] -= h[c] * vv[u][c];
-                    }
-            }
-        }
-        if (DOT) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                if (g + c <= j) {
-                    const T v = ck::wave_sum_last(acc[c]);   // valid in lane 63
-                    if ((tid & 63) == 63)
-                        lds.wred[tid >> 6][g + c] = v;
-                }
-        }
+    const int cols = j + 1;
+    int g = 0;
+    for (; g + 8 <= cols; g += 8)
+        basis_columns<8, DOT, T, BS>(n, g, V, ld, w, lds);
+    if (cols & 4) {
+        basis_columns<4, DOT, T, BS>(n, g, V, ld, w, lds);
+        g += 4;
     }
+    if (cols & 2) {
+        basis_columns<2, DOT, T, BS>(n, g, V, ld, w, lds);
+        g += 2;
+    }
+    if (cols & 1)
+        basis_columns<1, DOT, T, BS>(n, g, V, ld, w, lds);
     if (!DOT) {
+        const int tid = thread_index();
 #pragma unroll
         for (int u = 0; u < R; ++u)
             if (tid + u * BS >= n)
@@ -427,6 +465,8 @@ __device__ __forceinline__ int slot_gmres(ck::BSlot *s, int budget, SlotLds<T, B
     }
     if (tid == 0)
         lds.p[n] = 0;
+    if (s->sell.base != nullptr && tid <= (n + 63) / 64)
+        lds.base[tid] = s->sell.base[tid];
     if (tid < j) {
         lds.cs[tid] = (T)s->cs[tid];
         lds.sn[tid] = (T)s->sn[tid];
@@ -873,11 +913,22 @@ __device__ __forceinline__ void run_slot(ck::BSlot *slots, ck::BStat *stat, int 
                 }
             }
             __syncthreads();
-            const T *V = wsp<T>(s, 0);
+            const T *V = uni(wsp<T>(s, 0));
+            const double *y = uni(s->y);
+            const int64_t ld = uni((int)s->ld);
             for (int i = tid; i < n; i += BS) {
                 double acc = 0;
-                for (int c = 0; c < k; ++c)
-                    acc += (double)s->y[c] * (double)V[(int64_t)c * s->ld + i];
+                for (int c0 = 0; c0 < k; c0 += 8) {
+                    T vv[8];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        vv[c] = (V + (int64_t)min(c0 + c, k - 1) * ld)[(unsigned)i];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        if (c0 + c < k)
+                            acc += y[c0 + c] * (double)vv[c];
+                }
                 s->x[i] += beta * acc;
             }
         }
@@ -900,7 +951,7 @@ __device__ __forceinline__ void run_slot(ck::BSlot *slots, ck::BStat *stat, int 
 // One launch: every listed slot advances by up to `budget` steps.  A slot of
 // at most narrow_n rows runs on 256 threads, a larger one on 1024: a slot's
 // step is a chain of L2 round trips, so more threads shorten it (n = 7,000,
-// FP32 CG: 103 us a step with 256 threads and the vectors in memory, 15 us
+// FP32 CG: 103 us a step with 256 threads and the vectors in memory, 8 us
 // now), while a system of a thousand rows gains nothing from more than 256
 // and leaves the rest of the compute unit to other slots.  The width follows
 // from n alone, so a slot's bits do not depend on the launch it is in.
