@@ -30,9 +30,11 @@ ck_status fail(ck_status st, const char *fmt, ...) {
 }
 
 // features.hip
-ck_status launch_validate(int64_t n, int64_t ncols, int64_t nnz, const int *rp, const int *col,
-                          unsigned *state, hipStream_t s);
-int64_t validate_state_elems(int64_t nnz);
+int64_t ingest_state_ints();
+unsigned ingest_errors(const unsigned *state);
+ck_status launch_ingest(int64_t n, int64_t ncols, int64_t nnz, const int *rp_in,
+                        const int *col_in, const double *val_in, int *rp, int *col, double *val,
+                        float *val32, unsigned *state, hipStream_t s);
 int64_t features_scratch_bytes(int64_t n, int64_t ncols, int64_t nnz);
 ck_status launch_features(const ck_matrix &M, void *scratch, bool symmetry, hipStream_t s);
 void features_from_acc(const void *acc_host, const ck_matrix &M, int64_t *out28);
@@ -300,6 +302,24 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
 
 using namespace ck;
 
+// Whether a kernel on `device` may read the `count` entries directly: device
+// memory of that device, inside one allocation, at the type's alignment.  The
+// copy engine takes, or refuses, the rest (host, managed and peer memory).
+template <typename T>
+static bool readable(const T *p, int64_t count, int device) {
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();   // unknown to the runtime: no error of ours
+        return false;
+    }
+    const size_t at = (size_t)((const char *)p - (const char *)base);
+    return a.type == hipMemoryTypeDevice && a.device == device &&
+           (uintptr_t)p % sizeof(T) == 0 && at <= size && (size - at) / sizeof(T) >= (size_t)count;
+}
+
 extern "C" {
 
 const char *ck_last_error(void) { return g_last_error.c_str(); }
@@ -384,37 +404,40 @@ ck_status spmv_create(ck_handle *out, int64_t nrows, int64_t ncols, int64_t nnz,
     M->flags = flags;
     (void)hipGetDevice(&M->device);
     ck_status st = CK_OK;
-    unsigned *bad = nullptr;
-    unsigned hbad = 0;
+    unsigned *state = nullptr;
+    unsigned hstate[16] = {}, hbad = 0;
     do {
         if ((st = mat_alloc(*M, &M->rp, nrows + 1, s)) != CK_OK) break;
         if ((st = mat_alloc(*M, &M->col, nnz, s)) != CK_OK) break;
         if ((st = mat_alloc(*M, &M->val, nnz, s)) != CK_OK) break;
-        hipError_t e = hipMemcpyAsync(M->rp, d_rowptr, sizeof(int32_t) * (nrows + 1),
-                                      hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess && nnz > 0)
-            e = hipMemcpyAsync(M->col, d_col, sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess && nnz > 0)
-            e = hipMemcpyAsync(M->val, d_val, sizeof(double) * nnz, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) {
-            st = fail(CK_E_HIP, "copy of the CSR arrays failed: %s", hipGetErrorString(e));
-            break;
-        }
-        if (flags & CK_KEEP_FP32) {
-            if ((st = mat_alloc(*M, &M->val32, nnz, s)) != CK_OK) break;
-            if (nnz > 0 && (st = launch_copy<float, double>(nnz, M->val32, M->val, nullptr, s)) != CK_OK)
+        if ((flags & CK_KEEP_FP32) && (st = mat_alloc(*M, &M->val32, nnz, s)) != CK_OK) break;
+        const int64_t ints = ingest_state_ints();
+        if ((st = mat_alloc(*M, &state, ints, s)) != CK_OK) break;
+        if ((st = launch_fill<int>(ints, (int *)state, 0, s)) != CK_OK) break;
+        hipError_t e = hipSuccess;
+        if (!(readable(d_rowptr, nrows + 1, M->device) &&
+              (nnz == 0 || (readable(d_col, nnz, M->device) && readable(d_val, nnz, M->device))))) {
+            e = hipMemcpyAsync(M->rp, d_rowptr, sizeof(int32_t) * (nrows + 1), hipMemcpyDefault, s);
+            if (e == hipSuccess && nnz > 0)
+                e = hipMemcpyAsync(M->col, d_col, sizeof(int32_t) * nnz, hipMemcpyDefault, s);
+            if (e == hipSuccess && nnz > 0)
+                e = hipMemcpyAsync(M->val, d_val, sizeof(double) * nnz, hipMemcpyDefault, s);
+            if (e != hipSuccess) {
+                st = fail(CK_E_HIP, "copy of the CSR arrays failed: %s", hipGetErrorString(e));
                 break;
+            }
+            d_rowptr = M->rp, d_col = M->col, d_val = M->val;   // checked in place
         }
-        if ((st = mat_alloc(*M, &bad, validate_state_elems(nnz), s)) != CK_OK) break;
-        if ((st = launch_fill<int>(2, (int *)bad, 0, s)) != CK_OK) break;
-        if ((st = launch_validate(nrows, ncols, nnz, M->rp, M->col, bad, s)) != CK_OK) break;
-        e = hipMemcpyAsync(&hbad, bad, sizeof hbad, hipMemcpyDeviceToHost, s);
+        if ((st = launch_ingest(nrows, ncols, nnz, d_rowptr, d_col, d_val, M->rp, M->col, M->val,
+                                M->val32, state, s)) != CK_OK) break;
+        e = hipMemcpyAsync(hstate, state, ints * sizeof(int), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
             e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
-            st = fail(CK_E_HIP, "validation failed: %s", hipGetErrorString(e));
+            st = fail(CK_E_HIP, "ingest failed: %s", hipGetErrorString(e));
             break;
         }
+        hbad = ingest_errors(hstate);
         if (hbad) {
             st = fail(CK_E_INVALID, "malformed CSR (code %u): rowptr must start at 0, be "
                       "nondecreasing and end at nnz; columns in range and strictly increasing",
@@ -423,7 +446,7 @@ ck_status spmv_create(ck_handle *out, int64_t nrows, int64_t ncols, int64_t nnz,
         }
     } while (false);
     (void)hipStreamSynchronize(s);   // nothing may still write the arrays
-    mat_free(*M, bad);
+    mat_free(*M, state);
     if (st != CK_OK) {
         release(M);
         return st;

@@ -6,13 +6,13 @@
 // the floating-point features from them.  Passes:
 //   feat_rows : one lane per row  -> sum r, sum r^2, max r, min r, span,
 //               row-length histogram                           (reads rowptr, 2 cols/row)
-//   feat_nnz  : rows of at most kLongRow entries, 8 lanes per row striding
-//               the row (coalesced) -> longest run of consecutive columns,
-//               diagonal flags, main-diagonal count, symmetry  (reads col [+ val])
-//   feat_long : the same for longer rows (listed by feat_rows), one
-//               workgroup per row
+//   feat_nnz  : 8 lanes per row striding the row (coalesced), rows longer than
+//               kLongRow by the whole workgroup -> longest run of consecutive
+//               columns, diagonal flags, main-diagonal count, symmetry
+//               (reads col [+ val])
 //   feat_ndiag: count set diagonal flags
 #include <algorithm>
+#include <cstring>
 
 #include "matrix.hpp"
 
@@ -21,7 +21,6 @@ namespace {
 struct FeatAcc {
     unsigned long long sum_r, sum_r2, max_r, min_r, span, cluster, diag_nnz, ndiag, asym;
     unsigned long long hist[16];
-    unsigned long long nlong;   // rows longer than kLongRow, listed by feat_rows
 };
 
 __device__ __forceinline__ int hist_bin(long long r) {
@@ -43,7 +42,7 @@ __global__ __launch_bounds__(256) void fill_u128(int64_t n16, uint4 *__restrict_
 __global__ void feat_init(FeatAcc *acc) {
     if (threadIdx.x == 0) {
         acc->sum_r = acc->sum_r2 = acc->max_r = acc->span = acc->cluster = 0;
-        acc->diag_nnz = acc->ndiag = acc->asym = acc->nlong = 0;
+        acc->diag_nnz = acc->ndiag = acc->asym = 0;
         acc->min_r = ~0ull;
         for (int b = 0; b < 16; ++b)
             acc->hist[b] = 0;
@@ -56,21 +55,17 @@ __global__ void feat_init(FeatAcc *acc) {
 // Slots are field-major (field f of block b at f * grid + b), so the finish
 // reads each field coalesced.
 constexpr int kRowFields = 21;   // sum r, sum r^2, span, max r, min r, histogram[16]
-// Rows longer than this go to the whole-workgroup passes (feat_long,
-// csr_validate_long), which take them from a list; at most nnz / 513 of them.
+// Rows longer than this are run by whole workgroups.
 constexpr int kLongRow = 512;
-__host__ __device__ constexpr int64_t long_list_cap(int64_t nnz) { return nnz / (kLongRow + 1) + 1; }
 constexpr int kNnzFields = 2;    // longest-run sum, main-diagonal count
 
 // Grid-stride over rows.
 // The row-length histogram is counted in registers (16 counters per lane,
 // summed once at the end): LDS atomics on the one bin that most rows share
 // serialised every wave.
-__global__ __launch_bounds__(256) void feat_rows(int64_t n, int64_t nnz,
-                                                 const int *__restrict__ rp,
+__global__ __launch_bounds__(256) void feat_rows(int64_t n, const int *__restrict__ rp,
                                                  const int *__restrict__ col,
-                                                 unsigned long long *__restrict__ part_rows,
-                                                 FeatAcc *acc, int *__restrict__ long_list) {
+                                                 unsigned long long *__restrict__ part_rows) {
     unsigned long long *slot = part_rows + blockIdx.x;   // field f at slot[f * gridDim.x]
     __shared__ unsigned long long h[16];
     __shared__ unsigned long long part[5][4];
@@ -92,11 +87,6 @@ __global__ __launch_bounds__(256) void feat_rows(int64_t n, int64_t nnz,
         mn = ri < mn ? ri : mn;
         if (k1 > k0)
             span += (unsigned long long)(col[k1 - 1] - col[k0]);
-        if (ri > (unsigned long long)kLongRow) {   // a validated CSR has at most the cap
-            const unsigned long long at = atomicAdd(&acc->nlong, 1ull);
-            if ((int64_t)at < long_list_cap(nnz))
-                long_list[at] = (int)i;
-        }
         const int bin = hist_bin((long long)ri);
 #pragma unroll
         for (int b = 0; b < 16; ++b)
@@ -186,15 +176,15 @@ __device__ __forceinline__ void fold_step(Stretch &st, unsigned long long m) {
 constexpr int kDiagMemo = 4;
 
 struct DiagMemo {
-    int64_t d[kDiagMemo];
+    unsigned d[kDiagMemo];   // n + ncols - 1 diagonals are below 2^32 - 1
     int slot;
     __device__ void init() {
 #pragma unroll
         for (int m = 0; m < kDiagMemo; ++m)
-            d[m] = -1;
+            d[m] = ~0u;
         slot = 0;
     }
-    __device__ __forceinline__ void mark(int64_t dg, unsigned char *__restrict__ flag) {
+    __device__ __forceinline__ void mark(unsigned dg, unsigned char *__restrict__ flag) {
         bool seen = false;
 #pragma unroll
         for (int m = 0; m < kDiagMemo; ++m)
@@ -252,9 +242,14 @@ __device__ __forceinline__ void add_block_counts(unsigned long long cl, unsigned
     }
 }
 
-// Rows of at most kLongRow entries: L = 8 lanes per row, lane l reading
-// entries l, l + 8, ... of the row (eight consecutive columns per step,
-// coalesced); the wave steps together up to its longest row.
+// L = 8 lanes per row, lane l reading entries l, l + 8, ... of the row (eight
+// consecutive columns per step, coalesced); the wave steps together up to its
+// longest row.  Rows longer than kLongRow are left to the end of the group and
+// run by the whole block, lane t reading entry t of each 256-entry step, the
+// four waves' continue masks folded in wave order.
+// Listing them for a launch of their own cost one same-address atomic per
+// long row in the row pass and 207 us with the chip part-filled (power-law
+// n = 1.2M, 33M entries, all passes 595 us; 475 us this way).
 template <bool SYM>
 __global__ __launch_bounds__(256) void feat_nnz(int64_t n, const int *__restrict__ rp,
                                                 const int *__restrict__ col,
@@ -263,23 +258,43 @@ __global__ __launch_bounds__(256) void feat_nnz(int64_t n, const int *__restrict
                                                 FeatAcc *acc,
                                                 unsigned long long *__restrict__ part_nnz) {
     constexpr int L = 8;
-    const int lane = threadIdx.x & (L - 1);
-    const int gbase = (threadIdx.x & 63) & ~(L - 1);   // the group's first lane in the wave
+    __shared__ int s_col[256];
+    __shared__ unsigned long long s_mask[4];
+    // Long rows of a group.  Three counters in turn: the one of the next group
+    // is cleared before this group's barrier, two groups after its last reader.
+    __shared__ int s_long[256 / L], s_count[3];
+    const int tid = threadIdx.x;
+    const int lane = tid & (L - 1);
+    const int gbase = (tid & 63) & ~(L - 1);   // the group's first lane in the wave
     unsigned long long dcount = 0, asym = 0, cl = 0;
     DiagMemo memo;
     memo.init();
     // once any block has found an unmatched entry the answer is fixed, so
     // later blocks skip the transposed-entry searches
     const bool search = SYM && __builtin_nontemporal_load(&acc->asym) == 0;
+    auto entry = [&](int64_t i, int k, int c) {
+        memo.mark((unsigned)(c - i + (n - 1)), diag_flag);
+        if (c == i)
+            dcount += 1;
+        if (search && asym == 0 && unmatched<SYM>(i, c, val[k], rp, col, val))
+            asym = 1;
+    };
+    if (tid < 3)
+        s_count[tid] = 0;
+    __syncthreads();
     const int64_t groups = (n + 256 / L - 1) / (256 / L);
+    int turn = 0;
     for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {   // uniform per block
-        const int64_t i = g * (256 / L) + threadIdx.x / L;
+        const int64_t i = g * (256 / L) + tid / L;
         int k0 = 0, r = 0;
         if (i < n) {
             k0 = rp[i];
             r = rp[i + 1] - k0;
-            if (r > kLongRow)
-                r = 0;                      // feat_long's row
+            if (r > kLongRow) {
+                if (lane == 0)
+                    s_long[atomicAdd(&s_count[turn], 1)] = (int)i;
+                r = 0;
+            }
         }
         // the wave's longest row (every lane runs the steps below together,
         // so the DPP moves always read active lanes)
@@ -298,78 +313,54 @@ __global__ __launch_bounds__(256) void feat_nnz(int64_t n, const int *__restrict
                 cprev = prev_last;
             const bool cont = in && t + lane > 0 && c == cprev + 1;
             const unsigned long long bal = __ballot(cont);
-            fold_step<L>(st, bal >> gbase);
+            if (bal != 0)
+                fold_step<L>(st, bal >> gbase);
+            else
+                st.cur = 0;   // what fold_step makes of a step without continuing entries
             // the group's last column, for its first lane (half-row mirror:
             // lane 0 of each eight reads lane 7)
             prev_last = __builtin_amdgcn_update_dpp(0, c, 0x141, 0xf, 0xf, true);
-            if (in) {
-                memo.mark((int64_t)c - i + (n - 1), diag_flag);
-                if (c == i)
-                    dcount += 1;
-                if (search && asym == 0 && unmatched<SYM>(i, c, val[k], rp, col, val))
-                    asym = 1;
-            }
+            if (in)
+                entry(i, k, c);
         }
         if (lane == 0 && r > 0)
             cl += (unsigned long long)(st.best + 1);
+        const int next = turn == 2 ? 0 : turn + 1;
+        if (tid == 0)
+            s_count[next] = 0;
+        __syncthreads();
+        const int count = s_count[turn];
+        turn = next;
+        for (int q = 0; q < count; ++q) {   // sums and flags: their order does not matter
+            const int64_t i = s_long[q];
+            const int k0 = rp[i], r = rp[i + 1] - k0;
+            Stretch st{0, 0};
+            int prev_last = 0;
+            for (int t = 0; t < r; t += 256) {
+                const bool in = t + tid < r;
+                const int k = k0 + t + tid;
+                const int c = in ? col[k] : 0;
+                s_col[tid] = c;
+                __syncthreads();
+                const int cprev = tid > 0 ? s_col[tid - 1] : prev_last;
+                const bool cont = in && t + tid > 0 && c == cprev + 1;
+                const unsigned long long bal = __ballot(cont);
+                if ((tid & 63) == 0)
+                    s_mask[tid >> 6] = bal;
+                if (in)
+                    entry(i, k, c);
+                __syncthreads();
+                if (tid == 0)
+                    for (int w = 0; w < 4; ++w)
+                        fold_step<64>(st, s_mask[w]);
+                prev_last = s_col[255];
+                __syncthreads();   // s_col and s_mask are rewritten by the next step
+            }
+            if (tid == 0)
+                cl += (unsigned long long)(st.best + 1);
+        }
     }
     add_block_counts(cl, dcount, asym, acc, part_nnz + blockIdx.x);
-}
-
-// Rows longer than kLongRow (listed by feat_rows): a block runs each with
-// all 256 lanes, lane t reading entry t of each 256-entry step; the four
-// waves' continue masks are folded in wave order.
-
-template <bool SYM>
-__global__ __launch_bounds__(256) void feat_long(int64_t n, const int *__restrict__ rp,
-                                                 const int *__restrict__ col,
-                                                 const double *__restrict__ val,
-                                                 unsigned char *__restrict__ diag_flag,
-                                                 FeatAcc *acc, const int *__restrict__ long_list,
-                                                 unsigned long long *__restrict__ part_long) {
-    __shared__ int s_col[256];
-    __shared__ unsigned long long s_mask[4];
-    const int tid = threadIdx.x;
-    unsigned long long dcount = 0, asym = 0, cl = 0;
-    DiagMemo memo;
-    memo.init();
-    const bool search = SYM && __builtin_nontemporal_load(&acc->asym) == 0;
-    const int64_t cnt =
-        min((int64_t)__builtin_nontemporal_load(&acc->nlong), long_list_cap(rp[n]));
-    for (int64_t q = blockIdx.x; q < cnt; q += gridDim.x) {
-        const int64_t i = long_list[q];
-        const int k0 = rp[i], r = rp[i + 1] - k0;
-        Stretch st{0, 0};
-        int prev_last = 0;
-        for (int t = 0; t < r; t += 256) {
-            const bool in = t + tid < r;
-            const int k = k0 + t + tid;
-            const int c = in ? col[k] : 0;
-            s_col[tid] = c;
-            __syncthreads();
-            const int cprev = tid > 0 ? s_col[tid - 1] : prev_last;
-            const bool cont = in && t + tid > 0 && c == cprev + 1;
-            const unsigned long long bal = __ballot(cont);
-            if ((tid & 63) == 0)
-                s_mask[tid >> 6] = bal;
-            if (in) {
-                memo.mark((int64_t)c - i + (n - 1), diag_flag);
-                if (c == i)
-                    dcount += 1;
-                if (search && asym == 0 && unmatched<SYM>(i, c, val[k], rp, col, val))
-                    asym = 1;
-            }
-            __syncthreads();
-            if (tid == 0)
-                for (int w = 0; w < 4; ++w)
-                    fold_step<64>(st, s_mask[w]);
-            prev_last = s_col[255];
-            __syncthreads();   // s_col and s_mask are rewritten by the next step
-        }
-        if (tid == 0)
-            cl += (unsigned long long)(st.best + 1);
-    }
-    add_block_counts(cl, dcount, asym, acc, part_long + blockIdx.x);
 }
 
 // Counts the set flags, 16 bytes per lane (each byte is 0 or 1; bytes past
@@ -397,7 +388,6 @@ __global__ __launch_bounds__(256) void feat_ndiag(int64_t n16, const uint4 *__re
 // and order-free) into the accumulators.  One block of 1024 threads.
 __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned long long *pr,
                                                    int Gr, const unsigned long long *pn, int Gn,
-                                                   const unsigned long long *pl, int Gl,
                                                    const unsigned long long *pd, int Gd) {
     constexpr int F = kRowFields + kNnzFields + 1;   // + diagonals
     unsigned long long v[F];
@@ -418,10 +408,6 @@ __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned
     for (int b = threadIdx.x; b < Gn; b += 1024) {
         v[21] += pn[b];
         v[22] += pn[Gn + b];
-    }
-    for (int b = threadIdx.x; b < Gl; b += 1024) {
-        v[21] += pl[b];
-        v[22] += pl[Gl + b];
     }
     for (int b = threadIdx.x; b < Gd; b += 1024)
         v[23] += pd[b];
@@ -468,75 +454,144 @@ __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned
     }
 }
 
-// ---- validation ---------------------------------------------------------------
-// Row pointers (each row's bounds checked before any of its columns is
-// read), then the columns of rows of at most kLongRow entries with 8 lanes
-// per row; longer rows with valid bounds go to a list (valid bounds make
-// the rows disjoint, so at most long_list_cap(nnz) of them) for
-// csr_validate_long.  state[0] = error bits, state[1] = listed rows.
-__global__ __launch_bounds__(256) void csr_validate(int64_t n, int64_t ncols, int64_t nnz,
-                                                    const int *__restrict__ rp,
-                                                    const int *__restrict__ col,
-                                                    unsigned *state, int *__restrict__ long_list) {
-    constexpr int L = 8;
-    unsigned *bad = state;
-    const int lane = threadIdx.x & (L - 1);
-    const int64_t i = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
-    if (i > n)
-        return;
-    if (i == 0 && lane == 0 && rp[0] != 0)
-        atomicOr(bad, 1u);
-    if (i == n) {
-        if (lane == 0 && (int64_t)rp[n] != nnz)
-            atomicOr(bad, 2u);
-        return;
-    }
-    const int64_t k0 = rp[i], k1 = rp[i + 1];
-    if (k1 < k0 || k0 < 0 || k1 > nnz) {
-        if (lane == 0)
-            atomicOr(bad, 4u);
-        return;
-    }
-    if (k1 - k0 > kLongRow) {
-        if (lane == 0) {
-            // rows with valid bounds may still overlap when other rows are
-            // malformed: never write past the list (those rows are flagged)
-            const unsigned at = atomicAdd(&state[1], 1u);
-            if ((int64_t)at < long_list_cap(nnz))
-                long_list[at] = (int)i;
-            else
-                atomicOr(bad, 16u);
+// ---- ingest: copy and validation -----------------------------------------------
+// The entries are copied (and cast) flat, and checked on the way: columns in
+// range, and the number of descents, entries whose column is not above the one
+// before.  With sound row pointers the columns increase inside every row
+// exactly when every descent is the first entry of a row, i.e. when there are
+// as many descents as rows that start with one (ingest_rows counts those).
+// One pass over the entries at the copy rate, whatever the row lengths, and
+// the rows' scattered reads by other workgroups of the same launch: n = 471K,
+// 16M entries: three copies, 95 us, and a check by rows, 58 us, before; 101 us
+// now (as two launches, 76 + 30 us).
+struct IngestState {
+    unsigned bad, descents, row_descents, pad;
+};
+
+// V entries per thread and step; V > 1 needs 16-byte aligned arrays.  The
+// arrays may be checked in place (in == out): the values written are the ones
+// read.  Block `b` of G.
+template <int V, bool F32>
+__device__ __forceinline__ void ingest_entries(int64_t b, int64_t G, int64_t nnz, int64_t ncols,
+                                               const int *col_in, const double *val_in, int *col,
+                                               double *val, float *val32, IngestState *state) {
+    unsigned descents = 0;
+    bool range = false;
+    const int64_t steps = nnz / V;
+    auto check = [&](int prev, int c, bool first) {
+        range |= c < 0 || c >= ncols;
+        descents += !first && c <= prev ? 1u : 0u;
+    };
+    for (int64_t t = b * 256 + threadIdx.x; t < steps; t += G * 256) {
+        const int64_t k = t * V;
+        const int before = k > 0 ? col_in[k - 1] : 0;
+        int c[V];
+        double v[V];
+        if constexpr (V == 4) {
+            const int4 ci = *(const int4 *)(col_in + k);
+            const double2 v0 = *(const double2 *)(val_in + k), v1 = *(const double2 *)(val_in + k + 2);
+            c[0] = ci.x, c[1] = ci.y, c[2] = ci.z, c[3] = ci.w;
+            v[0] = v0.x, v[1] = v0.y, v[2] = v1.x, v[3] = v1.y;
+            *(int4 *)(col + k) = ci;
+            *(double2 *)(val + k) = v0;
+            *(double2 *)(val + k + 2) = v1;
+            if (F32)
+                *(float4 *)(val32 + k) =
+                    make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+        } else {
+            c[0] = col_in[k];
+            v[0] = val_in[k];
+            col[k] = c[0];
+            val[k] = v[0];
+            if (F32)
+                val32[k] = (float)v[0];
         }
-        return;
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+            check(u > 0 ? c[u > 0 ? u - 1 : 0] : before, c[u], u == 0 && k == 0);
     }
-    for (int64_t k = k0 + lane; k < k1; k += L) {
-        const int c = col[k];
-        if (c < 0 || c >= ncols || (k > k0 && c <= col[k - 1])) {
-            atomicOr(bad, 8u);
-            return;
-        }
+    if (V > 1 && b == 0 && threadIdx.x < nnz - steps * V) {   // the last entries
+        const int64_t k = steps * V + threadIdx.x;
+        const int c = col_in[k];
+        const double v = val_in[k];
+        col[k] = c;
+        val[k] = v;
+        if (F32)
+            val32[k] = (float)v;
+        check(k > 0 ? col_in[k - 1] : 0, c, k == 0);
+    }
+    __shared__ unsigned part[4], any;
+    if (threadIdx.x == 0)
+        any = 0;
+    __syncthreads();
+    descents = ck::wave_sum(descents);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = descents;
+    if (__any(range) && (threadIdx.x & 63) == 0)
+        any = 1;   // racing stores agree
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned d = part[0] + part[1] + part[2] + part[3];
+        if (d)
+            atomicAdd(&state->descents, d);
+        if (any)
+            atomicOr(&state->bad, 8u);
     }
 }
 
-// Columns of the listed long rows, each with all 256 lanes of a block.
-__global__ __launch_bounds__(256) void csr_validate_long(int64_t ncols, int64_t nnz,
-                                                         const int *__restrict__ rp,
-                                                         const int *__restrict__ col,
-                                                         unsigned *state,
-                                                         const int *__restrict__ long_list) {
-    const int64_t cnt =
-        min((int64_t)__builtin_nontemporal_load(&state[1]), long_list_cap(nnz));
-    for (int64_t q = blockIdx.x; q < cnt; q += gridDim.x) {
-        const int64_t i = long_list[q];
-        const int64_t k0 = rp[i], k1 = rp[i + 1];
-        for (int64_t k = k0 + threadIdx.x; k < k1; k += 256) {
-            const int c = col[k];
-            if (c < 0 || c >= ncols || (k > k0 && c <= col[k - 1])) {
-                atomicOr(&state[0], 8u);
-                break;
-            }
+// Row pointers: copied, checked (start 0, nondecreasing, inside 0 .. nnz, end
+// nnz), and the rows that start with a descent counted (each row's bounds are
+// checked before an entry of it is read).
+__device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int64_t nnz,
+                                            const int *rp_in, const int *col_in, int *rp,
+                                            IngestState *state) {
+    unsigned bad = 0, starts = 0;
+    for (int64_t i = b * 256 + threadIdx.x; i <= n; i += G * 256) {
+        const int64_t k0 = rp_in[i];
+        rp[i] = (int)k0;
+        if (i == 0 && k0 != 0)
+            bad |= 1u;
+        if (i == n) {
+            if (k0 != nnz)
+                bad |= 2u;
+            continue;
         }
+        const int64_t k1 = rp_in[i + 1];
+        if (k1 < k0 || k0 < 0 || k1 > nnz)
+            bad |= 4u;
+        else if (k1 > k0 && k0 > 0 && col_in[k0] <= col_in[k0 - 1])
+            ++starts;
     }
+    __shared__ unsigned part[4], flags;
+    if (threadIdx.x == 0)
+        flags = 0;
+    __syncthreads();
+    starts = ck::wave_sum(starts);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = starts;
+    if (bad)
+        atomicOr(&flags, bad);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned d = part[0] + part[1] + part[2] + part[3];
+        if (d)
+            atomicAdd(&state->row_descents, d);
+        if (flags)
+            atomicOr(&state->bad, flags);
+    }
+}
+
+// Workgroups 0 .. Gr - 1 take the rows, the others the entries.
+template <int V, bool F32>
+__global__ __launch_bounds__(256) void ingest(int64_t Gr, int64_t n, int64_t ncols, int64_t nnz,
+                                              const int *rp_in, const int *col_in,
+                                              const double *val_in, int *rp, int *col, double *val,
+                                              float *val32, IngestState *state) {
+    if (blockIdx.x < Gr)
+        ingest_rows(blockIdx.x, Gr, n, nnz, rp_in, col_in, rp, state);
+    else
+        ingest_entries<V, F32>(blockIdx.x - Gr, gridDim.x - Gr, nnz, ncols, col_in, val_in, col,
+                               val, val32, state);
 }
 
 // ---- conversions ----------------------------------------------------------------
@@ -595,17 +650,33 @@ __global__ __launch_bounds__(256) void row_max(int64_t n, const int *__restrict_
 // ---------------------------------------------------------------------------
 namespace ck {
 
-// Ints of the validation state: error bits, list length, the long-row list.
-int64_t validate_state_elems(int64_t nnz) { return 2 + long_list_cap(nnz); }
+int64_t ingest_state_ints() { return sizeof(IngestState) / sizeof(int); }
 
-// `state` (validate_state_elems ints, the first two cleared) gets the error bits in state[0].
-ck_status launch_validate(int64_t n, int64_t ncols, int64_t nnz, const int *rp, const int *col,
-                          unsigned *state, hipStream_t s) {
-    const int64_t G = ceil_div(n + 1, 256 / 8);
-    int *list = (int *)(state + 2);
-    hipLaunchKernelGGL(csr_validate, dim3(G), dim3(256), 0, s, n, ncols, nnz, rp, col, state, list);
-    hipLaunchKernelGGL(csr_validate_long, dim3(1024), dim3(256), 0, s, ncols, nnz, rp, col, state,
-                       list);
+// Error bits of a finished ingest (0: a sound CSR).
+unsigned ingest_errors(const unsigned *state) {
+    IngestState st;
+    std::memcpy(&st, state, sizeof st);
+    return st.bad ? st.bad : st.descents != st.row_descents ? 8u : 0u;
+}
+
+// Copies the caller's CSR and checks it; `state` (ingest_state_ints ints) is
+// cleared by the caller.
+ck_status launch_ingest(int64_t n, int64_t ncols, int64_t nnz, const int *rp_in,
+                        const int *col_in, const double *val_in, int *rp, int *col, double *val,
+                        float *val32, unsigned *state, hipStream_t s) {
+    IngestState *st = (IngestState *)state;
+    const bool wide = (((uintptr_t)col_in | (uintptr_t)val_in | (uintptr_t)col | (uintptr_t)val |
+                        (uintptr_t)val32) & 15) == 0;
+    const int64_t Gr = std::min<int64_t>(ceil_div(n + 1, 256), 2048);
+    const int64_t Ge = std::min<int64_t>(ceil_div(nnz, wide ? 1024 : 256), 4096);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(Gr + Ge), dim3(256), 0, s, Gr, n, ncols, nnz, rp_in, col_in,
+                           val_in, rp, col, val, val32, st);
+    };
+    if (wide)
+        val32 ? go(ingest<4, true>) : go(ingest<4, false>);
+    else
+        val32 ? go(ingest<1, true>) : go(ingest<1, false>);
     CK_HIP(hipGetLastError());
     return CK_OK;
 }
@@ -614,14 +685,12 @@ int64_t features_acc_offset(int64_t n, int64_t ncols);
 
 // Scratch of the feature pass: the diagonal flags (n + ncols - 1 bytes,
 // rounded up to 256), the accumulators (512 bytes), then the partial slots
-// of the passes (grids of at most kGridRows, kGridNnz, kGridLong and
-// kGridDiag blocks).
-constexpr int64_t kGridRows = 1024, kGridNnz = 2048, kGridLong = 1024, kGridDiag = 1024;
-constexpr int64_t kPartialWords =
-    kGridRows * kRowFields + (kGridNnz + kGridLong) * kNnzFields + kGridDiag;
+// of the passes (grids of at most kGridRows, kGridNnz and kGridDiag blocks).
+constexpr int64_t kGridRows = 1024, kGridNnz = 2048, kGridDiag = 1024;
+constexpr int64_t kPartialWords = kGridRows * kRowFields + kGridNnz * kNnzFields + kGridDiag;
 
 int64_t features_scratch_bytes(int64_t n, int64_t ncols, int64_t nnz) {
-    return ((n + ncols + 255) / 256) * 256 + 512 + 8 * kPartialWords + 4 * long_list_cap(nnz);
+    return ((n + ncols + 255) / 256) * 256 + 512 + 8 * kPartialWords;
 }
 
 ck_status launch_features(const ck_matrix &M, void *scratch, bool symmetry, hipStream_t s) {
@@ -632,9 +701,7 @@ ck_status launch_features(const ck_matrix &M, void *scratch, bool symmetry, hipS
     FeatAcc *acc = (FeatAcc *)((char *)scratch + features_acc_offset(M.n, M.ncols));
     unsigned long long *pr = (unsigned long long *)((char *)acc + 512);
     unsigned long long *pn = pr + kGridRows * kRowFields;
-    unsigned long long *pl = pn + kGridNnz * kNnzFields;
-    unsigned long long *pd = pl + kGridLong * kNnzFields;
-    int *long_list = (int *)(pd + kGridDiag);
+    unsigned long long *pd = pn + kGridNnz * kNnzFields;
     hipLaunchKernelGGL(feat_init, dim3(1), dim3(64), 0, s, acc);
     if (n16 > 0)
         hipLaunchKernelGGL(fill_u128, dim3(std::min<int64_t>(ceil_div(n16, 256), 4096)), dim3(256),
@@ -642,24 +709,18 @@ ck_status launch_features(const ck_matrix &M, void *scratch, bool symmetry, hipS
     if (M.n > 0) {
         const int64_t Gr = std::min<int64_t>(ceil_div(M.n, 256), kGridRows);
         const int64_t G = std::min<int64_t>(ceil_div(M.n, 256 / 8), kGridNnz);
-        const int64_t GL = kGridLong;
         const int64_t Gd = std::min<int64_t>(ceil_div(n16, 256), kGridDiag);
-        hipLaunchKernelGGL(feat_rows, dim3(Gr), dim3(256), 0, s, M.n, M.nnz, M.rp, M.col, pr, acc,
-                           long_list);
+        hipLaunchKernelGGL(feat_rows, dim3(Gr), dim3(256), 0, s, M.n, M.rp, M.col, pr);
         if (symmetry && M.n == M.ncols) {
             hipLaunchKernelGGL((feat_nnz<true>), dim3(G), dim3(256), 0, s, M.n, M.rp, M.col,
                                M.val, flags, acc, pn);
-            hipLaunchKernelGGL((feat_long<true>), dim3(GL), dim3(256), 0, s, M.n, M.rp, M.col,
-                               M.val, flags, acc, long_list, pl);
         } else {
             hipLaunchKernelGGL((feat_nnz<false>), dim3(G), dim3(256), 0, s, M.n, M.rp, M.col,
                                M.val, flags, acc, pn);
-            hipLaunchKernelGGL((feat_long<false>), dim3(GL), dim3(256), 0, s, M.n, M.rp, M.col,
-                               M.val, flags, acc, long_list, pl);
         }
         hipLaunchKernelGGL(feat_ndiag, dim3(Gd), dim3(256), 0, s, n16, (const uint4 *)flags, pd);
-        hipLaunchKernelGGL(feat_finish, dim3(1), dim3(1024), 0, s, acc, pr, (int)Gr, pn, (int)G, pl,
-                           (int)GL, pd, (int)Gd);
+        hipLaunchKernelGGL(feat_finish, dim3(1), dim3(1024), 0, s, acc, pr, (int)Gr, pn, (int)G, pd,
+                           (int)Gd);
     }
     CK_HIP(hipGetLastError());
     return CK_OK;
