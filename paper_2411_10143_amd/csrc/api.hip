@@ -4,6 +4,7 @@
 #include <cstdarg>
 #include <cstring>
 #include <limits>
+#include <vector>
 
 #include "matrix.hpp"
 #include "devcache.hpp"
@@ -31,7 +32,7 @@ ck_status fail(ck_status st, const char *fmt, ...) {
 
 // features.hip
 int64_t ingest_state_ints();
-unsigned ingest_errors(const unsigned *state);
+unsigned ingest_result(const unsigned *state, int64_t *max_row);
 ck_status launch_ingest(int64_t n, int64_t ncols, int64_t nnz, const int *rp_in,
                         const int *col_in, const double *val_in, int *rp, int *col, double *val,
                         float *val32, unsigned *state, hipStream_t s);
@@ -40,7 +41,6 @@ ck_status launch_features(const ck_matrix &M, void *scratch, bool symmetry, hipS
 void features_from_acc(const void *acc_host, const ck_matrix &M, int64_t *out28);
 int64_t features_acc_offset(int64_t n, int64_t ncols);
 size_t features_acc_size();
-ck_status launch_row_max(int64_t n, const int *rp, unsigned long long *out, hipStream_t s);
 ck_status launch_to_ell(const ck_matrix &M, int64_t K, int64_t pitch, int *ecol, double *evl,
                         float *evl32, hipStream_t s);
 ck_status launch_to_coo(const ck_matrix &M, int *row, hipStream_t s);
@@ -110,7 +110,6 @@ ck_status compute_features(ck_matrix &M, ck_features &F, hipStream_t s, bool sym
         ints[27] = 0;
     std::memcpy(&F, ints, sizeof ints);
     derive_features(F);
-    M.max_row = F.max_r;
     return CK_OK;
 }
 
@@ -124,40 +123,15 @@ static ck_status mark_built(std::atomic<bool> &flag, hipStream_t s) {
     return CK_OK;
 }
 
-ck_status ensure_max_row(ck_matrix &M, hipStream_t s) {
-    if (M.max_row >= 0)
-        return CK_OK;
-    if (M.n == 0) {
-        M.max_row = 0;
-        return CK_OK;
-    }
-    unsigned long long *d = nullptr;
-    unsigned long long h = 0;
-    CK_TRY(mat_alloc(M, &d, 1, s));
-    ck_status st = launch_fill<int>(2, (int *)d, 0, s);
-    if (st == CK_OK)
-        st = launch_row_max(M.n, M.rp, d, s);
-    if (st == CK_OK && hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess)
-        st = fail(CK_E_HIP, "row-length read-back failed");
-    if (hipStreamSynchronize(s) != hipSuccess && st == CK_OK)
-        st = fail(CK_E_HIP, "row-length pass failed");
-    mat_free(M, d);
-    CK_TRY(st);
-    M.max_row = (int64_t)h;
-    return CK_OK;
-}
-
 ck_status build_slot_copy(ck_matrix &M, bool fp32, hipStream_t s) {
     std::lock_guard<std::mutex> lk(M.mu);
     if (M.has_slot[fp32].load())
         return CK_OK;
-    CK_TRY(ensure_max_row(M, s));
-    M.slot_max_row = M.max_row;
     const int vb = fp32 ? 4 : 8;
-    CK_TRY(mat_alloc(M, &M.slot_mem[fp32], slot_copy_bytes(M.n, M.nnz, M.slot_max_row, vb), s));
+    CK_TRY(mat_alloc(M, &M.slot_mem[fp32], slot_copy_bytes(M.n, M.nnz, M.max_row, vb), s));
     const ck_status st = launch_slot_copy(
         M.n, M.rp, M.col, M.val, fp32 ? M.val32 : nullptr,
-        slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.slot_max_row, vb), s);
+        slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, vb), s);
     if (st != CK_OK) {
         mat_free(M, M.slot_mem[fp32]);
         M.slot_mem[fp32] = nullptr;
@@ -181,7 +155,6 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             return CK_OK;
         if (!M.merge_plan)
             CK_TRY(mat_alloc(M, &M.merge_plan, merge_plan_ints(M.n, M.nnz), s));
-        CK_TRY(ensure_max_row(M, s));
         M.merge_cut = merge_cuts_rows(M.max_row);
         CK_TRY(launch_merge_plan(M.n, M.nnz, M.rp, M.merge_plan, s));
         return mark_built(M.has_merge_plan, s);
@@ -193,12 +166,11 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
         const int64_t N8 = (int64_t)P8 * M.n;   // the most panel rows P can give
         if (N8 + 1 > (int64_t)std::numeric_limits<int32_t>::max())
             return fail(CK_E_UNSUPPORTED, "too many panel rows");
-        CK_TRY(ensure_max_row(M, s));
         int *tmp = nullptr;
-        CK_TRY(mat_alloc(M, &tmp, N8 + 2 + panel_scan_tmp_elems(N8), s));
+        CK_TRY(mat_alloc(M, &tmp, panel_tmp_ints(N8), s));
         int P = P8;
-        bool counted = false;
-        ck_status st = panel_choose_count(M, tmp, s, &P, &counted);
+        int64_t filled = 0;
+        ck_status st = panel_choose_count(M, tmp, s, &P, &filled);
         const int64_t W = ceil_div(std::max<int64_t>(M.ncols, 1), P);
         const int64_t N = (int64_t)P * M.n;
         if (st == CK_OK)
@@ -211,12 +183,12 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
             st = mat_alloc(M, &M.panel_val32, M.nnz, s);
         if (st == CK_OK)
             st = launch_to_panel(M, P, W, tmp, tmp + N, M.panel_rp, M.panel_col, M.panel_val,
-                                 M.panel_val32, counted, s);
+                                 M.panel_val32, s);
         M.panel_P = P;
         M.panel_W = W;
         M.panel_rows = N;
         if (st == CK_OK)
-            st = panel_make_rows(M, tmp, s);   // only the non-empty panel rows, if that pays
+            st = panel_make_rows(M, tmp, filled, s);   // only the non-empty panel rows, if that pays
         const int64_t R = M.panel_rows;
         if (st == CK_OK)
             st = mat_alloc(M, &M.panel_plan, merge_plan_ints(R, M.nnz), s);
@@ -282,7 +254,6 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
     }
     if (M.has_ell.load())
         return CK_OK;
-    CK_TRY(ensure_max_row(M, s));
     const int64_t K = M.max_row;
     const int64_t pitch = ceil_div(M.n, 64) * 64;
     if (K * pitch > 8 * M.nnz)
@@ -405,13 +376,14 @@ ck_status spmv_create(ck_handle *out, int64_t nrows, int64_t ncols, int64_t nnz,
     (void)hipGetDevice(&M->device);
     ck_status st = CK_OK;
     unsigned *state = nullptr;
-    unsigned hstate[16] = {}, hbad = 0;
+    unsigned hbad = 0;
+    std::vector<unsigned> hstate(ingest_state_ints());
     do {
         if ((st = mat_alloc(*M, &M->rp, nrows + 1, s)) != CK_OK) break;
         if ((st = mat_alloc(*M, &M->col, nnz, s)) != CK_OK) break;
         if ((st = mat_alloc(*M, &M->val, nnz, s)) != CK_OK) break;
         if ((flags & CK_KEEP_FP32) && (st = mat_alloc(*M, &M->val32, nnz, s)) != CK_OK) break;
-        const int64_t ints = ingest_state_ints();
+        const int64_t ints = (int64_t)hstate.size();
         if ((st = mat_alloc(*M, &state, ints, s)) != CK_OK) break;
         if ((st = launch_fill<int>(ints, (int *)state, 0, s)) != CK_OK) break;
         hipError_t e = hipSuccess;
@@ -430,14 +402,14 @@ ck_status spmv_create(ck_handle *out, int64_t nrows, int64_t ncols, int64_t nnz,
         }
         if ((st = launch_ingest(nrows, ncols, nnz, d_rowptr, d_col, d_val, M->rp, M->col, M->val,
                                 M->val32, state, s)) != CK_OK) break;
-        e = hipMemcpyAsync(hstate, state, ints * sizeof(int), hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(hstate.data(), state, ints * sizeof(int), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
             e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             st = fail(CK_E_HIP, "ingest failed: %s", hipGetErrorString(e));
             break;
         }
-        hbad = ingest_errors(hstate);
+        hbad = ingest_result(hstate.data(), &M->max_row);
         if (hbad) {
             st = fail(CK_E_INVALID, "malformed CSR (code %u): rowptr must start at 0, be "
                       "nondecreasing and end at nnz; columns in range and strictly increasing",

@@ -78,6 +78,11 @@ __device__ __forceinline__ float dpp_read(float v) {
 }
 
 template <int CTRL, int RM, int BM>
+__device__ __forceinline__ int dpp_read(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, RM, BM, true);
+}
+
+template <int CTRL, int RM, int BM>
 __device__ __forceinline__ unsigned long long dpp_read(unsigned long long v) {
     const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, RM, BM,
                                                              true);

@@ -462,11 +462,12 @@ __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned
 // as many descents as rows that start with one (ingest_rows counts those).
 // One pass over the entries at the copy rate, whatever the row lengths, and
 // the rows' scattered reads by other workgroups of the same launch: n = 471K,
-// 16M entries: three copies, 95 us, and a check by rows, 58 us, before; 101 us
-// now (as two launches, 76 + 30 us).
-struct IngestState {
-    unsigned bad, descents, row_descents, pad;
+// 16M entries: three copies, 95 us, and a check by rows, 58 us, before; 79 us
+// now.
+struct IngestState {   // one of kSpread
+    unsigned bad, descents, row_descents, max_row, pad[ck::kSpreadInts - 4];
 };
+static_assert(sizeof(IngestState) == ck::kSpreadInts * sizeof(int), "spread counters");
 
 // V entries per thread and step; V > 1 needs 16-byte aligned arrays.  The
 // arrays may be checked in place (in == out): the values written are the ones
@@ -540,12 +541,12 @@ __device__ __forceinline__ void ingest_entries(int64_t b, int64_t G, int64_t nnz
 }
 
 // Row pointers: copied, checked (start 0, nondecreasing, inside 0 .. nnz, end
-// nnz), and the rows that start with a descent counted (each row's bounds are
-// checked before an entry of it is read).
+// nnz), the rows that start with a descent counted (each row's bounds are
+// checked before an entry of it is read), and the longest row found.
 __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int64_t nnz,
                                             const int *rp_in, const int *col_in, int *rp,
                                             IngestState *state) {
-    unsigned bad = 0, starts = 0;
+    unsigned bad = 0, starts = 0, longest = 0;
     for (int64_t i = b * 256 + threadIdx.x; i <= n; i += G * 256) {
         const int64_t k0 = rp_in[i];
         rp[i] = (int)k0;
@@ -557,15 +558,21 @@ __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int
             continue;
         }
         const int64_t k1 = rp_in[i + 1];
-        if (k1 < k0 || k0 < 0 || k1 > nnz)
+        if (k1 < k0 || k0 < 0 || k1 > nnz) {
             bad |= 4u;
-        else if (k1 > k0 && k0 > 0 && col_in[k0] <= col_in[k0 - 1])
-            ++starts;
+        } else {
+            if (k1 > k0 && k0 > 0 && col_in[k0] <= col_in[k0 - 1])
+                ++starts;
+            longest = max(longest, (unsigned)(k1 - k0));
+        }
     }
-    __shared__ unsigned part[4], flags;
+    __shared__ unsigned part[4], flags, s_longest;
     if (threadIdx.x == 0)
-        flags = 0;
+        flags = s_longest = 0;
     __syncthreads();
+    longest = (unsigned)ck::wave_max_last((unsigned long long)longest);   // in lane 63
+    if ((threadIdx.x & 63) == 63)
+        atomicMax(&s_longest, longest);
     starts = ck::wave_sum(starts);
     if ((threadIdx.x & 63) == 0)
         part[threadIdx.x >> 6] = starts;
@@ -576,6 +583,7 @@ __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int
         const unsigned d = part[0] + part[1] + part[2] + part[3];
         if (d)
             atomicAdd(&state->row_descents, d);
+        atomicMax(&state->max_row, s_longest);
         if (flags)
             atomicOr(&state->bad, flags);
     }
@@ -587,6 +595,7 @@ __global__ __launch_bounds__(256) void ingest(int64_t Gr, int64_t n, int64_t nco
                                               const int *rp_in, const int *col_in,
                                               const double *val_in, int *rp, int *col, double *val,
                                               float *val32, IngestState *state) {
+    state += blockIdx.x % ck::kSpread;
     if (blockIdx.x < Gr)
         ingest_rows(blockIdx.x, Gr, n, nnz, rp_in, col_in, rp, state);
     else
@@ -638,25 +647,24 @@ __global__ __launch_bounds__(256) void csr_to_coo(int64_t n, const int *__restri
         row[k] = (int)i;
 }
 
-__global__ __launch_bounds__(256) void row_max(int64_t n, const int *__restrict__ rp,
-                                               unsigned long long *out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    unsigned long long r = i < n ? (unsigned long long)(rp[i + 1] - rp[i]) : 0ull;
-    r = ck::wave_max_last(r);   // valid in lane 63
-    if ((threadIdx.x & 63) == 63)
-        atomicMax(out, r);
-}
-
 // ---------------------------------------------------------------------------
 namespace ck {
 
-int64_t ingest_state_ints() { return sizeof(IngestState) / sizeof(int); }
+int64_t ingest_state_ints() { return kSpread * kSpreadInts; }
 
-// Error bits of a finished ingest (0: a sound CSR).
-unsigned ingest_errors(const unsigned *state) {
-    IngestState st;
-    std::memcpy(&st, state, sizeof st);
-    return st.bad ? st.bad : st.descents != st.row_descents ? 8u : 0u;
+// Error bits of a finished ingest (0: a sound CSR), and the longest row.
+unsigned ingest_result(const unsigned *state, int64_t *max_row) {
+    unsigned bad = 0, descents = 0, row_descents = 0;
+    *max_row = 0;
+    for (int t = 0; t < kSpread; ++t) {
+        IngestState st;
+        std::memcpy(&st, state + t * kSpreadInts, sizeof st);
+        bad |= st.bad;
+        descents += st.descents;
+        row_descents += st.row_descents;
+        *max_row = std::max<int64_t>(*max_row, st.max_row);
+    }
+    return bad ? bad : descents != row_descents ? 8u : 0u;
 }
 
 // Copies the caller's CSR and checks it; `state` (ingest_state_ints ints) is
@@ -779,12 +787,6 @@ void features_from_acc(const void *acc_host, const ck_matrix &M, int64_t *out28)
 
 int64_t features_acc_offset(int64_t n, int64_t ncols) { return ((n + ncols + 255) / 256) * 256; }
 size_t features_acc_size() { return sizeof(FeatAcc); }
-
-ck_status launch_row_max(int64_t n, const int *rp, unsigned long long *out, hipStream_t s) {
-    hipLaunchKernelGGL(row_max, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, rp, out);
-    CK_HIP(hipGetLastError());
-    return CK_OK;
-}
 
 ck_status launch_to_ell(const ck_matrix &M, int64_t K, int64_t pitch, int *ecol, double *evl,
                         float *evl32, hipStream_t s) {

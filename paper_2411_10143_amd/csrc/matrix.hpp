@@ -77,10 +77,9 @@ struct ck_matrix {
     int64_t hyb_K = 0, hyb_pitch = 0, hyb_nt = 0;
     int hyb_L = 1;
     std::atomic<bool> has_hyb{false};
-    int64_t max_row = -1;             // longest row, once known
+    int64_t max_row = 0;              // longest row
     // slot copies (batched.hpp) of a small matrix, FP64 and FP32 values
     char *slot_mem[2] = {nullptr, nullptr};
-    int64_t slot_max_row = 0;         // the longest row their layout assumes
     std::atomic<bool> has_slot[2] = {false, false};
     // feature scratch of the device-resident cascade (kept with the handle)
     char *devsel_scratch = nullptr;
@@ -126,8 +125,11 @@ struct SpmvArgs {
     void *carry = nullptr;
 };
 
-// The longest row of M, counted (and remembered) if it is not known yet.
-ck_status ensure_max_row(ck_matrix &M, hipStream_t s);
+// Counters that every workgroup of a large grid adds to are kept kSpread
+// times, kSpreadInts ints apart (one 4,096-workgroup grid adding to a single
+// word waits 37 us for it); the host sums them.
+constexpr int kSpread = 32, kSpreadInts = 64;
+
 // Builds M's slot copy (of the FP32 values if fp32; M.n <= kSlotRows) if it is
 // not there yet; returns when it is built.  Its bytes: slot_bytes_of.
 ck_status build_slot_copy(ck_matrix &M, bool fp32, hipStream_t s);

@@ -17,40 +17,136 @@
 #include "solvers.hpp"
 
 
-// cnt[p*n + i] = entries of row i whose column lies in panel p
-__global__ __launch_bounds__(256) void panel_count(int64_t n, int P, int64_t W,
+// Rows longer than this are not run by their eight lanes entry by entry: with
+// rows of 10,000 entries on eight lanes the copy of a power-law matrix (n =
+// 1.2M, 33M entries) took 1,420 us, 328 us now.
+constexpr int kLongPanelRow = 512;
+
+// column / W by the rounded reciprocal: off by at most one either way before
+// the correction (a column is below 2^31, a panel index below 2^14).
+__device__ __forceinline__ int panel_of(int c, int W, float inv) {
+    int q = (int)((float)c * inv);
+    const int64_t lo = (int64_t)q * W;
+    q -= c < lo ? 1 : 0;
+    q += c >= lo + W ? 1 : 0;
+    return q;
+}
+
+// cnt[p*n + i] = entries of row i whose column lies in panel p, and *filled +=
+// the panel rows that have any.  A workgroup takes 32 rows, eight lanes each,
+// and eight panels at a time.  Rows of at most kCountRow entries are counted
+// entry by entry, by comparing each column with the panels' ends (B of them;
+// instructions bound the pass: dividing each column by W took 62 us where this
+// takes 26); in longer rows each lane searches its panel's ends.  The counts go
+// through LDS so that they are stored 32 rows to a panel.  One lane per row
+// searching panel after panel took 97 us for 16M entries in four panels, one
+// lane per panel 64 us.
+constexpr int kCountRow = 64;
+__global__ __launch_bounds__(256) void panel_count(int64_t n, int P, int W,
                                                    const int *__restrict__ rp,
                                                    const int *__restrict__ col,
-                                                   int *__restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n)
-        return;
-    const int k0 = rp[i], k1 = rp[i + 1];
-    int k = k0;
-    for (int p = 0; p < P; ++p) {
-        const int64_t hi = (int64_t)(p + 1) * W;   // first column past panel p
-        int lo = k, top = k1;                        // first entry with col >= hi
-        while (lo < top) {
-            const int mid = (lo + top) >> 1;
-            if (col[mid] < hi)
-                lo = mid + 1;
-            else
-                top = mid;
+                                                   int *__restrict__ cnt, unsigned *filled) {
+    constexpr int L = 8, R = 256 / L, U = 4;
+    __shared__ int s_len[R][L + 1];
+    __shared__ unsigned part[4];
+    const int tid = threadIdx.x, lane = tid & (L - 1), row = tid / L;
+    unsigned full = 0;
+    const int64_t groups = (n + R - 1) / R;
+    // entries below each of the first B - 1 ends; the row's other entries of
+    // these panels end the B-th
+    auto count = [&](auto ends, int k0, int k1, int p0) {
+        constexpr int B = decltype(ends)::value;
+        int end[B], below[B];
+#pragma unroll
+        for (int e = 0; e < B; ++e) {
+            end[e] = (int)min((int64_t)(p0 + e + 1) * W, (int64_t)INT_MAX);
+            below[e] = 0;
         }
-        cnt[(int64_t)p * n + i] = lo - k;
-        k = lo;
+        for (int t = k0; t < k1; t += L * U) {
+            int c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = t + u * L + lane;
+                c[u] = k < k1 ? col[k] : INT_MAX;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < B; ++e)
+                    below[e] += c[u] < end[e] ? 1 : 0;
+        }
+        int mine = 0, before = 0;
+#pragma unroll
+        for (int e = 0; e < B; ++e) {
+            below[e] = ck::group_sum_last<L>(below[e]);   // in every lane
+            if (lane == e)
+                mine = below[e] - before;
+            before = below[e];
+        }
+        s_len[row][lane] = mine;
+        return before;
+    };
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int64_t i = g * R + row;
+        int k0 = i < n ? rp[i] : 0;
+        const int k1 = i < n ? rp[i + 1] : 0;
+        const bool shrt = k1 - k0 <= kCountRow;
+        for (int p0 = 0; p0 < P; p0 += L) {
+            if (shrt) {
+                if (P - p0 <= 4)   // uniform
+                    k0 += count(std::integral_constant<int, 4>(), k0, k1, p0);
+                else
+                    k0 += count(std::integral_constant<int, 8>(), k0, k1, p0);
+            } else {
+                auto find = [&](int64_t first) {   // the first entry at or past column `first`
+                    int lo = k0, top = k1;
+                    while (lo < top) {
+                        const int mid = (lo + top) >> 1;
+                        if (col[mid] < first)
+                            lo = mid + 1;
+                        else
+                            top = mid;
+                    }
+                    return lo;
+                };
+                const int64_t first = (int64_t)(p0 + lane) * W;
+                const int at = find(first);
+                int end = __shfl_down(at, 1, L);
+                if (lane == L - 1)
+                    end = p0 + L < P ? find(first + W) : k1;
+                s_len[row][lane] = end - at;
+            }
+            __syncthreads();
+            const int p = tid / R, r = tid % R;
+            if (p0 + p < P && g * R + r < n) {
+                const int len = s_len[r][p];
+                cnt[(int64_t)(p0 + p) * n + g * R + r] = len;
+                full += len > 0 ? 1u : 0u;
+            }
+            __syncthreads();
+        }
+    }
+    full = ck::wave_sum(full);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = full;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned t = part[0] + part[1] + part[2] + part[3];
+        if (t)
+            atomicAdd(&filled[blockIdx.x % ck::kSpread * ck::kSpreadInts], t);
     }
 }
 
-// Panel-major copy: row i's panel-p entries go to prp[p*n + i] onwards.
-// Eight lanes per row.  For panels p0 .. p0 + 7, lane l holds panel p0 + l's
-// destination and length; an exclusive sum over the eight lengths gives each
-// panel's first entry within the row (columns are sorted, so a row's entries
-// of consecutive panels are consecutive).  The eight lanes then copy the
+// Panel-major copy: row i's panel-p entries go to prp[p*n + i] onwards.  A
+// workgroup takes 32 rows, eight lanes each, and eight panels at a time.  The
+// rows' destinations and lengths in those panels (staged in LDS, read 32 rows
+// to a panel) give each panel's first entry within the row, since a row's
+// entries of consecutive panels are consecutive.  The eight lanes copy the
 // row's entries of those panels together, lane l taking entries l, l + 8, ...
-// (coalesced loads): an entry's panel is its column / W, and the lane holding
-// that panel supplies the destination by a shuffle.  Every lane of a row runs
-// the same number of steps, so the shuffles always read active lanes.
+// (coalesced loads), an entry's panel being its column / W.  Rows over
+// kLongPanelRow are copied at the end by the whole workgroup.  16M entries in
+// four panels: 150 us with the panels' destinations read per row and one entry
+// per lane in flight, 115 us this way; power-law, 33M entries, 328 us.
 template <bool F32>
 __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
                                                   const int *__restrict__ rp,
@@ -59,18 +155,43 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
                                                   const int *__restrict__ prp,
                                                   int *__restrict__ pcol, double *__restrict__ pval,
                                                   float *__restrict__ pval32) {
-    constexpr int L = 8;
-    const int lane = threadIdx.x & (L - 1);
-    const int64_t i = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
-    if (i >= n)
-        return;   // whole groups leave together (8 divides the wave)
-    int base = rp[i];
+    constexpr int L = 8, R = 256 / L, U = 4;
+    __shared__ int s_long[R], s_count;
+    __shared__ int s_dst[L][R + 1];     // panel p0 + p, row r
+    __shared__ int s_shift[R][L + 1];   // destination minus the entry's place in the row
+    __shared__ int s_first[L + 1];
+    const int tid = threadIdx.x, lane = tid & (L - 1), row = tid / L;
+    const int64_t i0 = (int64_t)blockIdx.x * R, i = i0 + row;
+    const float inv = 1.0f / (float)W;
+    auto put = [&](int dst, int c, double v) {
+        pcol[dst] = c;
+        pval[dst] = v;
+        if (F32)
+            pval32[dst] = (float)v;
+    };
+    if (tid == 0)
+        s_count = 0;
+    __syncthreads();
+    int base = i < n ? rp[i] : 0;
+    const bool shrt = i >= n || rp[i + 1] - base <= kLongPanelRow;
+    if (!shrt && lane == 0)
+        s_long[atomicAdd(&s_count, 1)] = row;
     for (int p0 = 0; p0 < P; p0 += L) {
-        // lanes past the last panel (P not a multiple of 8) hold an empty segment
-        const bool has = p0 + lane < P;
-        const int64_t at = (int64_t)(p0 + lane) * n + i;
-        const int dst0 = has ? prp[at] : 0;
-        const int len = has ? prp[at + 1] - dst0 : 0;
+        {   // rows past n end where row n - 1 does: empty
+            const int p = tid / R, r = tid % R;
+            if (p0 + p < P) {
+                const int64_t at = (int64_t)(p0 + p) * n;
+                s_dst[p][r] = prp[at + min(i0 + r, n)];
+                if (r == R - 1)
+                    s_dst[p][R] = prp[at + min(i0 + R, n)];
+            } else {   // panels past the last: empty
+                s_dst[p][r] = 0;
+                if (r == R - 1)
+                    s_dst[p][R] = 0;
+            }
+        }
+        __syncthreads();
+        const int dst = s_dst[lane][row], len = s_dst[lane][row + 1] - dst;
         int ex = len;   // inclusive scan over the group's lanes, then exclusive
 #pragma unroll
         for (int off = 1; off < L; off <<= 1) {
@@ -78,65 +199,92 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
             if (lane >= off)
                 ex += o;
         }
-        const int total = __shfl(ex, L - 1, L);
-        ex -= len;
-        for (int k0 = 0; k0 < total; k0 += L) {
-            const int k = k0 + lane;
-            const bool in = k < total;
-            const int c = in ? col[base + k] : p0 * W;
-            const int q = c / W - p0;   // 0 <= q < 8 for the row's entries of these panels
-            const int d0 = __shfl(dst0, q, L);
-            const int e0 = __shfl(ex, q, L);
-            if (in) {
-                const int dst = d0 + (k - e0);
-                const double v = val[base + k];
-                pcol[dst] = c;
-                pval[dst] = v;
-                if (F32)
-                    pval32[dst] = (float)v;
+        const int total = shrt ? __shfl(ex, L - 1, L) : 0;
+        s_shift[row][lane] = dst - (ex - len);
+        __syncthreads();
+        for (int k0 = 0; k0 < total; k0 += L * U) {
+            int c[U];
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * L + lane;
+                c[u] = k < total ? col[base + k] : -1;
+                v[u] = k < total ? val[base + k] : 0.0;
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c[u] >= 0)
+                    put(s_shift[row][panel_of(c[u], W, inv) - p0] + k0 + u * L + lane, c[u], v[u]);
         }
         base += total;
+        __syncthreads();   // s_dst and s_shift are rewritten
+    }
+    const int count = s_count;   // written before the barriers, and not again
+    for (int t = 0; t < count; ++t) {
+        const int64_t r = i0 + s_long[t];
+        int from = rp[r];
+        for (int p0 = 0; p0 < P; p0 += L) {
+            if (tid < L) {
+                const bool has = p0 + tid < P;
+                const int64_t at = (int64_t)(p0 + tid) * n + r;
+                const int d = has ? prp[at] : 0;
+                s_first[tid + 1] = has ? prp[at + 1] - d : 0;
+                s_dst[tid][0] = d;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s_first[0] = 0;
+                for (int q = 1; q <= L; ++q)
+                    s_first[q] += s_first[q - 1];
+            }
+            __syncthreads();
+            const int total = s_first[L];
+            for (int k = tid; k < total; k += 256) {
+                const int c = col[from + k];
+                const int q = panel_of(c, W, inv) - p0;
+                put(s_dst[q][0] + (k - s_first[q]), c, val[from + k]);
+            }
+            from += total;
+            __syncthreads();   // s_dst and s_first are rewritten
+        }
     }
 }
 
 // Exclusive scan of Nin int counts into Nout >= Nin outputs (inputs past Nin
 // read as 0, so out[Nin] is the total): 2048 items per workgroup, each thread
-// scanning 8 consecutive items, then the 256 thread totals in order.  The
+// scanning 8 consecutive items, then the 256 thread totals by wave scans.  The
 // block totals go to sums[] for the next level.
 __global__ __launch_bounds__(256) void scan_blocks(int64_t Nin, int64_t Nout,
                                                    const int *__restrict__ in,
                                                    int *__restrict__ out, int *__restrict__ sums) {
-    __shared__ int s[2048];
+    __shared__ int s[2048 + 256];   // one slot of padding per eight (bank conflicts)
     const int64_t base = (int64_t)blockIdx.x * 2048;
     for (int t = threadIdx.x; t < 2048; t += 256)
-        s[t] = base + t < Nin ? in[base + t] : 0;
+        s[t + (t >> 3)] = base + t < Nin ? in[base + t] : 0;
     __syncthreads();
     int local[8];
     int acc = 0;
     for (int t = 0; t < 8; ++t) {
         local[t] = acc;
-        acc += s[threadIdx.x * 8 + t];
+        acc += s[threadIdx.x * 9 + t];
     }
-    __shared__ int tsum[256];
-    tsum[threadIdx.x] = acc;
+    __shared__ int wsum[4];
+    const int sc = ck::wave_scan(acc), w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 63)
+        wsum[w] = sc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const int v = tsum[t];
-            tsum[t] = run;
-            run += v;
-        }
-        sums[blockIdx.x] = run;
-    }
+    int off = sc - acc;
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+        off += u < w ? wsum[u] : 0;
+    if (threadIdx.x == 255)
+        sums[blockIdx.x] = off + acc;
+    for (int t = 0; t < 8; ++t)
+        s[threadIdx.x * 9 + t] = off + local[t];
     __syncthreads();
-    const int off = tsum[threadIdx.x];
-    for (int t = 0; t < 8; ++t) {
-        const int64_t g = base + threadIdx.x * 8 + t;
-        if (g < Nout)
-            out[g] = off + local[t];
-    }
+    for (int t = threadIdx.x; t < 2048; t += 256)
+        if (base + t < Nout)
+            out[base + t] = s[t + (t >> 3)];
 }
 
 __global__ __launch_bounds__(256) void scan_add(int64_t N, int *__restrict__ out,
@@ -144,25 +292,6 @@ __global__ __launch_bounds__(256) void scan_add(int64_t N, int *__restrict__ out
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g < N)
         out[g] += offs[g / 2048];
-}
-
-// *total += number of nonzero counts (one atomic per block)
-__global__ __launch_bounds__(256) void count_nonzero(int64_t N, const int *__restrict__ cnt,
-                                                     unsigned long long *total) {
-    unsigned long long c = 0;
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < N;
-         k += (int64_t)gridDim.x * 256)
-        c += cnt[k] > 0 ? 1ull : 0ull;
-    __shared__ unsigned long long part[4];
-    c = ck::wave_sum(c);
-    if ((threadIdx.x & 63) == 0)
-        part[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long t = part[0] + part[1] + part[2] + part[3];
-        if (t)
-            atomicAdd(total, t);
-    }
 }
 
 // flag[k] = 1 if panel row k holds entries (in place over the counts)
@@ -307,34 +436,46 @@ int panel_count_for(int64_t ncols, int value_bytes) {
 // 4 MB slice: 465 -> 483 us).
 constexpr int64_t kSliceP4 = 5 * (int64_t(1) << 19);   // 2.5 MB
 
-ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
-                             bool *counted) {
-    const int P8 = panel_count_for(M.ncols, 8);
-    *P_out = P8;
-    *counted = false;
-    if (P8 != 8 || M.n == 0 || M.ncols * 8 > 4 * kSliceP4)
-        return CK_OK;
-    if (M.max_row > 4 * ceil_div(M.nnz, M.n))
-        return CK_OK;
-    const int64_t N4 = 4 * M.n;
-    const int64_t W4 = ceil_div(std::max<int64_t>(M.ncols, 1), 4);
-    // counts of the four panels, then the number of non-empty panel rows;
-    // the counter sits after the counts, 8-byte aligned (tmp holds >= 8n + 2 ints)
-    unsigned long long *total = (unsigned long long *)(tmp + ((N4 + 1) / 2) * 2);
-    CK_TRY(launch_fill<int>(2, (int *)total, 0, s));
-    hipLaunchKernelGGL(panel_count, dim3(ceil_div(M.n, 256)), dim3(256), 0, s, M.n, 4, W4, M.rp,
-                       M.col, tmp);
-    hipLaunchKernelGGL(count_nonzero, dim3(std::min<int64_t>(ceil_div(N4, 256), 1024)), dim3(256),
-                       0, s, N4, tmp, total);
+// The per-row panel counts into cnt (P*n ints) and, read back, how many are not
+// zero; their counters follow them.
+static ck_status count_panels(const ck_matrix &M, int P, int64_t W, int *cnt, int64_t *filled,
+                              hipStream_t s) {
+    constexpr int64_t ints = kSpread * kSpreadInts;
+    int *total = cnt + (int64_t)P * M.n;
+    int host[ints];
+    CK_TRY(launch_fill<int>(ints, total, 0, s));
+    hipLaunchKernelGGL(panel_count, dim3(std::min<int64_t>(ceil_div(M.n, 256 / 8), 4096)), dim3(256),
+                       0, s, M.n, P, (int)W, M.rp, M.col, cnt, (unsigned *)total);
     CK_HIP(hipGetLastError());
-    unsigned long long ne = 0;
-    CK_HIP(hipMemcpyAsync(&ne, total, sizeof ne, hipMemcpyDeviceToHost, s));
+    CK_HIP(hipMemcpyAsync(host, total, sizeof host, hipMemcpyDeviceToHost, s));
     CK_HIP(hipStreamSynchronize(s));
-    if (4 * (int64_t)ne > 3 * N4) {   // the P = 4 layout would be dense
-        *P_out = 4;
-        *counted = true;              // tmp[0 .. 4n) holds its counts
-    }
+    *filled = 0;
+    for (int t = 0; t < kSpread; ++t)
+        *filled += (unsigned)host[t * kSpreadInts];
     return CK_OK;
+}
+
+ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
+                             int64_t *filled) {
+    const int P8 = panel_count_for(M.ncols, 8);
+    const int64_t W8 = ceil_div(std::max<int64_t>(M.ncols, 1), P8);
+    *P_out = P8;
+    *filled = 0;
+    if (M.n == 0)
+        return CK_OK;
+    if (P8 == 8 && M.ncols * 8 <= 4 * kSliceP4 && M.max_row <= 4 * ceil_div(M.nnz, M.n)) {
+        const int64_t W4 = ceil_div(std::max<int64_t>(M.ncols, 1), 4);
+        CK_TRY(count_panels(M, 4, W4, tmp, filled, s));
+        if (4 * *filled > 3 * (4 * M.n)) {   // the P = 4 layout would be dense
+            *P_out = 4;
+            return CK_OK;
+        }
+    }
+    return count_panels(M, P8, W8, tmp, filled, s);
+}
+
+int64_t panel_tmp_ints(int64_t N) {
+    return N + std::max<int64_t>(kSpread * kSpreadInts, panel_scan_tmp_elems(N));
 }
 
 int64_t panel_scan_tmp_elems(int64_t N) {
@@ -363,10 +504,7 @@ ck_status launch_scan_exclusive(int64_t N, const int *in, int *out, int *tmp, hi
 }
 
 ck_status launch_to_panel(const ck_matrix &M, int P, int64_t W, int *cnt, int *tmp, int *prp,
-                          int *pcol, double *pval, float *pval32, bool counted, hipStream_t s) {
-    const int64_t g = ceil_div(M.n, 256);
-    if (!counted)   // else cnt already holds this P's counts (panel_choose_count)
-        hipLaunchKernelGGL(panel_count, dim3(g), dim3(256), 0, s, M.n, P, W, M.rp, M.col, cnt);
+                          int *pcol, double *pval, float *pval32, hipStream_t s) {
     CK_TRY(launch_scan_exclusive((int64_t)P * M.n, cnt, prp, tmp, s));
     const int64_t g8 = ceil_div(M.n, 256 / 8);
     const int Wi = (int)W;   // W <= ncols < 2^31
@@ -380,22 +518,16 @@ ck_status launch_to_panel(const ck_matrix &M, int P, int64_t W, int *cnt, int *t
     return CK_OK;
 }
 
-ck_status panel_make_rows(ck_matrix &M, int *cnt, hipStream_t s) {
-    const int64_t n = M.n, N = (int64_t)M.panel_P * n;
+ck_status panel_make_rows(ck_matrix &M, int *cnt, int64_t filled, hipStream_t s) {
+    const int64_t n = M.n, N = (int64_t)M.panel_P * n, NE = filled;
     M.panel_rows = N;
-    if (N == 0)
+    if (4 * NE > 3 * N || N == 0)   // dense rows are cheaper
         return CK_OK;
     int *pos = nullptr;
     CK_TRY(mat_alloc(M, &pos, N + 1 + panel_scan_tmp_elems(N), s));
     hipLaunchKernelGGL(panel_nonempty, dim3(ceil_div(N, 256)), dim3(256), 0, s, N, cnt);
     ck_status st = launch_scan_exclusive(N, cnt, pos, pos + N + 1, s);
-    int ne = 0;
-    if (st == CK_OK && (hipMemcpyAsync(&ne, pos + N, sizeof ne, hipMemcpyDeviceToHost, s) !=
-                            hipSuccess ||
-                        hipStreamSynchronize(s) != hipSuccess))
-        st = fail(CK_E_HIP, "panel row count read-back failed");
-    const int64_t NE = ne;
-    if (st != CK_OK || 4 * NE > 3 * N) {   // dense rows are cheaper (or failed)
+    if (st != CK_OK) {
         (void)hipStreamSynchronize(s);
         mat_free(M, pos);
         return st;

@@ -62,7 +62,6 @@ struct MatEntry {
     int64_t conv_bytes = 0;         // estimated bytes of its converted copy
     ck_config run_cfg{};            // what the resident copy runs (cfg, or the
                                     // default when cfg's copy did not fit)
-    int64_t max_row = -1;           // longest row, once counted
     uint64_t last_use = 0;
 };
 
@@ -139,7 +138,7 @@ int64_t handle_bytes(const ck_matrix &M) {
         b += 4 * merge_plan_ints(M.n, M.nnz);
     for (int fp32 = 0; fp32 < 2; ++fp32)
         if (M.has_slot[fp32].load())
-            b += slot_copy_bytes(M.n, M.nnz, M.slot_max_row, fp32 ? 4 : 8);
+            b += slot_copy_bytes(M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
     return b;
 }
 
@@ -276,15 +275,11 @@ ck_status ensure_resident(ck_server &S, MatEntry &e) {
         S.st.prediction_cache_hits += 1;
     }
     e.run_cfg = e.cfg;
-    if (e.max_row < 0)
-        e.max_row = e.h->max_row;
-    else
-        e.h->max_row = e.max_row;   // made resident again
-    if (e.n <= S.o.small_n && e.n <= kSlotRows && e.max_row >= 0) {
+    if (e.n <= S.o.small_n && e.n <= kSlotRows) {
         // the slots' copy of the matrix, where it fits beside a request's
         // workspace without evicting anything (its products give the bits of
         // the CSR arrays, so a slot's result does not depend on it)
-        const int64_t copy = slot_copy_bytes(e.n, e.nnz, e.max_row, fp32 ? 4 : 8);
+        const int64_t copy = slot_copy_bytes(e.n, e.nnz, e.h->max_row, fp32 ? 4 : 8);
         if (S.bytes_in_use + copy + request_bytes(S, e, true) <= S.o.budget_bytes)
             (void)build_slot_copy(*e.h, fp32, S.stream);
         S.bytes_in_use -= e.bytes;
@@ -387,7 +382,7 @@ Admit admit_one(ck_server &S, Request *r) {
     b.val64 = e.h->val;
     b.val32 = e.h->val32;
     if (e.h->has_slot[fp32].load())
-        b.sell = slot_copy_at(e.h->slot_mem[fp32], e.n, e.nnz, e.h->slot_max_row, fp32 ? 4 : 8);
+        b.sell = slot_copy_at(e.h->slot_mem[fp32], e.n, e.nnz, e.h->max_row, fp32 ? 4 : 8);
     b.b = r->b;
     b.x = r->x;
     b.r64 = r->r64;

@@ -832,7 +832,7 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool cg, int m) {
         CK_TRY(build_slot_copy(M, fp32, c.s));
     BSlot *h = (BSlot *)std::calloc(1, sizeof(BSlot));
     if (M.n <= kSlotRows)
-        h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.slot_max_row, fp32 ? 4 : 8);
+        h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
     h->kind = kind;
     h->n = (int)M.n;
     h->lanes = c.cfg.lanes;
