@@ -266,7 +266,10 @@ def _check(st):
 def _stream(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        # The current stream's handle itself: torch.cuda.current_stream() builds a
+        # Stream object for it, 2.9 us of a small product's 7.3 us per call (the
+        # handle 0.4 us).  Asked for on every call: the caller may change it.
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
