@@ -277,7 +277,11 @@ ck_status ck_default_config(ck_handle h, ck_config *out);
  * panel-major copy of the column and value arrays, P column panels of
  * ceil(ncols/P) columns (see ck_panel_layout), with per-panel row pointers
  * (P*nrows + 1 int32), or, when at most 3/4 of the P*nrows panel rows hold
- * entries, pointers and matrix-row indices of the non-empty ones only.  DIA: the ndiag distinct offsets
+ * entries, pointers and matrix-row indices of the non-empty ones only.
+ * Scattered matrices of at least 1.3M entries in even rows that are long
+ * against ncols / 15,360 are copied by slices of x instead (10 bytes per entry,
+ * 4 more with CK_KEEP_FP32): products then gather from LDS and use nrows values
+ * of workspace per slice, 64 MiB at most.  DIA: the ndiag distinct offsets
  * col - row of the stored entries (int32, ascending) and ndiag*pitch values,
  * diagonal k of row i at k*pitch + i, +0.0 where no entry is stored
  * (pitch = nrows rounded up to 64); refused with CK_E_UNSUPPORTED when
@@ -394,7 +398,8 @@ ck_status ck_export_coo_rows(ck_handle h, int32_t *d_row, hipStream_t s);
  * of non-empty panel rows in the row-list one).  P is 8q with at most 2 MB
  * of FP64 x per panel, or 4 when x fits four slices of 2.5 MB, the longest
  * row is at most 4x ceil(nnz/nrows) and more than 3/4 of the 4*nrows panel
- * rows hold entries.  CK_E_INVALID without a CSR-panel copy. */
+ * rows hold entries.  A copy by slices of x (see spmv_convert) is cut finer;
+ * its panels are counted by this call.  CK_E_INVALID without a CSR-panel copy. */
 ck_status ck_panel_layout(ck_handle h, int32_t *panels, int64_t *width, int64_t *stored_rows);
 
 /* ck_dot -- deterministic two-stage FP64 dot product of two device vectors
@@ -413,7 +418,8 @@ ck_status ck_config_from_id(int32_t id, ck_config *out);
  * launches (for matching profiler output); fp32 selects the FP32 variant.
  * DIA's kernel is specialised for the matrix's diagonal count: its name ends
  * in ", ND>", ND being 3, 5, 7, 9, 13, 15, 19 or 27, or 0 for any other
- * count, and is spmv_dia_const when every diagonal's values are equal.  Writes a
+ * count, and is spmv_dia_const when every diagonal's values are equal.
+ * CSR-panel's is spmv_slices after a copy by slices of x.  Writes a
  * NUL-terminated string of at most cap bytes. */
 ck_status ck_kernel_name(const ck_config *cfg, int32_t fp32, char *buf, size_t cap);
 

@@ -16,7 +16,7 @@ OBJ = os.path.join(HERE, "_build")
 ARCH = os.environ.get("PYTORCH_ROCM_ARCH", "gfx950").split(";")[0]
 
 SOURCES = ["api.hip", "spmv.hip", "vecops.hip", "gmres.hip", "features.hip", "solvers.hip",
-           "predictor.cpp", "batched.hip", "server.hip", "panel.hip", "smallcg.hip",
+           "predictor.cpp", "batched.hip", "server.hip", "panel.hip", "slices.hip", "smallcg.hip",
            "diahyb.hip", "devcache.hip", "devcascade.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

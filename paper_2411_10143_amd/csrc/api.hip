@@ -12,6 +12,7 @@
 #include "batched.hpp"
 #include "panel.hpp"
 #include "predictor.hpp"
+#include "slices.hpp"
 #include "solvers.hpp"
 
 namespace ck {
@@ -32,7 +33,7 @@ ck_status fail(ck_status st, const char *fmt, ...) {
 
 // features.hip
 int64_t ingest_state_ints();
-unsigned ingest_result(const unsigned *state, int64_t *max_row);
+unsigned ingest_result(const unsigned *state, int64_t *max_row, int64_t *span);
 ck_status launch_ingest(int64_t n, int64_t ncols, int64_t nnz, const int *rp_in,
                         const int *col_in, const double *val_in, int *rp, int *col, double *val,
                         float *val32, unsigned *state, hipStream_t s);
@@ -71,6 +72,7 @@ static void release(ck_matrix *M) {
     mat_free(*M, M->panel_val);
     mat_free(*M, M->panel_val32);
     mat_free(*M, M->merge_plan);
+    free_slices(*M);
     mat_free(*M, M->panel_plan);
     mat_free(*M, M->panel_row);
     mat_free(*M, M->slot_mem[0]);
@@ -162,6 +164,15 @@ ck_status convert_format(ck_matrix &M, const ck_config &c, hipStream_t s) {
     if (c.format == CK_FMT_CSR) {   // CSR-panel
         if (M.has_panel.load())
             return CK_OK;
+        const int slices = slices_of(M.n, M.ncols, M.nnz, M.max_row, M.span);
+        if (slices > 0) {
+            const ck_status st = build_slices(M, slices, s);
+            if (st == CK_OK)
+                return mark_built(M.has_panel, s);
+            (void)hipStreamSynchronize(s);
+            free_slices(M);
+            return st;
+        }
         const int P8 = panel_count_for(M.ncols, 8);
         const int64_t N8 = (int64_t)P8 * M.n;   // the most panel rows P can give
         if (N8 + 1 > (int64_t)std::numeric_limits<int32_t>::max())
@@ -291,6 +302,22 @@ static bool readable(const T *p, int64_t count, int device) {
            (uintptr_t)p % sizeof(T) == 0 && at <= size && (size - at) / sizeof(T) >= (size_t)count;
 }
 
+// The panels that M's entries would make (CSR-panel's rule), counted on the null stream.
+static ck_status panel_shape(ck_matrix &M, int32_t *panels, int64_t *width, int64_t *rows) {
+    int *tmp = nullptr;
+    int P = 0;
+    int64_t filled = 0;
+    CK_TRY(mat_alloc(M, &tmp, panel_tmp_ints((int64_t)panel_count_for(M.ncols, 8) * M.n), nullptr));
+    const ck_status st = panel_choose_count(M, tmp, nullptr, &P, &filled);
+    (void)hipStreamSynchronize(nullptr);
+    mat_free(M, tmp);
+    CK_TRY(st);
+    *panels = P;
+    *width = ceil_div(std::max<int64_t>(M.ncols, 1), P);
+    *rows = 4 * filled > 3 * (P * M.n) ? P * M.n : filled;
+    return CK_OK;
+}
+
 extern "C" {
 
 const char *ck_last_error(void) { return g_last_error.c_str(); }
@@ -409,7 +436,7 @@ ck_status spmv_create(ck_handle *out, int64_t nrows, int64_t ncols, int64_t nnz,
             st = fail(CK_E_HIP, "ingest failed: %s", hipGetErrorString(e));
             break;
         }
-        hbad = ingest_result(hstate.data(), &M->max_row);
+        hbad = ingest_result(hstate.data(), &M->max_row, &M->span);
         if (hbad) {
             st = fail(CK_E_INVALID, "malformed CSR (code %u): rowptr must start at 0, be "
                       "nondecreasing and end at nnz; columns in range and strictly increasing",
@@ -733,6 +760,8 @@ ck_status ck_panel_layout(ck_handle h, int32_t *panels, int64_t *width, int64_t 
         return fail(CK_E_INVALID, "NULL argument");
     if (!h->has_panel.load())
         return fail(CK_E_INVALID, "matrix has no CSR-panel copy");
+    if (h->slice_val != nullptr)   // cut finer than its panels, which are counted here
+        return panel_shape(*h, panels, width, stored_rows);
     *panels = h->panel_P;
     *width = h->panel_W;
     *stored_rows = h->panel_rows;

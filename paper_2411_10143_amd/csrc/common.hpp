@@ -206,6 +206,16 @@ __device__ __forceinline__ T group_sum(T v) {
     return v;
 }
 
+// column / W by the rounded reciprocal: off by at most one either way before
+// the correction (a column is below 2^31, a panel index below 2^14).
+__device__ __forceinline__ int panel_of(int c, int W, float inv) {
+    int q = (int)((float)c * inv);
+    const int64_t lo = (int64_t)q * W;
+    q -= c < lo ? 1 : 0;
+    q += c >= lo + W ? 1 : 0;
+    return q;
+}
+
 // Block (256 threads) sum, result valid in thread 0.  Fixed order.
 // Floating-point sums use the DPP wave sum (its total sits in lane 63).
 template <typename T>

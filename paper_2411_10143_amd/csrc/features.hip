@@ -465,7 +465,9 @@ __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned
 // 16M entries: three copies, 95 us, and a check by rows, 58 us, before; 79 us
 // now.
 struct IngestState {   // one of kSpread
-    unsigned bad, descents, row_descents, max_row, pad[ck::kSpreadInts - 4];
+    unsigned bad, descents, row_descents, max_row;
+    unsigned long long span;
+    unsigned pad[ck::kSpreadInts - 6];
 };
 static_assert(sizeof(IngestState) == ck::kSpreadInts * sizeof(int), "spread counters");
 
@@ -542,11 +544,13 @@ __device__ __forceinline__ void ingest_entries(int64_t b, int64_t G, int64_t nnz
 
 // Row pointers: copied, checked (start 0, nondecreasing, inside 0 .. nnz, end
 // nnz), the rows that start with a descent counted (each row's bounds are
-// checked before an entry of it is read), and the longest row found.
+// checked before an entry of it is read), the longest row found, and the
+// distances from the rows' first column to their last added up.
 __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int64_t nnz,
                                             const int *rp_in, const int *col_in, int *rp,
                                             IngestState *state) {
     unsigned bad = 0, starts = 0, longest = 0;
+    unsigned long long span = 0;
     for (int64_t i = b * 256 + threadIdx.x; i <= n; i += G * 256) {
         const int64_t k0 = rp_in[i];
         rp[i] = (int)k0;
@@ -561,18 +565,25 @@ __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int
         if (k1 < k0 || k0 < 0 || k1 > nnz) {
             bad |= 4u;
         } else {
-            if (k1 > k0 && k0 > 0 && col_in[k0] <= col_in[k0 - 1])
-                ++starts;
+            if (k1 > k0) {
+                const int c = col_in[k0];
+                starts += k0 > 0 && c <= col_in[k0 - 1] ? 1u : 0u;
+                span += (unsigned long long)(long long)(col_in[k1 - 1] - c);   // sorted, if sound
+            }
             longest = max(longest, (unsigned)(k1 - k0));
         }
     }
     __shared__ unsigned part[4], flags, s_longest;
+    __shared__ unsigned long long part_span[4];
     if (threadIdx.x == 0)
         flags = s_longest = 0;
     __syncthreads();
     longest = (unsigned)ck::wave_max_last((unsigned long long)longest);   // in lane 63
     if ((threadIdx.x & 63) == 63)
         atomicMax(&s_longest, longest);
+    span = ck::wave_sum_last(span);
+    if ((threadIdx.x & 63) == 63)
+        part_span[threadIdx.x >> 6] = span;
     starts = ck::wave_sum(starts);
     if ((threadIdx.x & 63) == 0)
         part[threadIdx.x >> 6] = starts;
@@ -584,6 +595,7 @@ __device__ __forceinline__ void ingest_rows(int64_t b, int64_t G, int64_t n, int
         if (d)
             atomicAdd(&state->row_descents, d);
         atomicMax(&state->max_row, s_longest);
+        atomicAdd(&state->span, part_span[0] + part_span[1] + part_span[2] + part_span[3]);
         if (flags)
             atomicOr(&state->bad, flags);
     }
@@ -652,10 +664,12 @@ namespace ck {
 
 int64_t ingest_state_ints() { return kSpread * kSpreadInts; }
 
-// Error bits of a finished ingest (0: a sound CSR), and the longest row.
-unsigned ingest_result(const unsigned *state, int64_t *max_row) {
+// Error bits of a finished ingest (0: a sound CSR), the longest row and the sum
+// of the rows' spans.
+unsigned ingest_result(const unsigned *state, int64_t *max_row, int64_t *span) {
     unsigned bad = 0, descents = 0, row_descents = 0;
     *max_row = 0;
+    *span = 0;
     for (int t = 0; t < kSpread; ++t) {
         IngestState st;
         std::memcpy(&st, state + t * kSpreadInts, sizeof st);
@@ -663,6 +677,7 @@ unsigned ingest_result(const unsigned *state, int64_t *max_row) {
         descents += st.descents;
         row_descents += st.row_descents;
         *max_row = std::max<int64_t>(*max_row, st.max_row);
+        *span += (int64_t)st.span;
     }
     return bad ? bad : descents != row_descents ? 8u : 0u;
 }

@@ -78,6 +78,15 @@ struct ck_matrix {
     int hyb_L = 1;
     std::atomic<bool> has_hyb{false};
     int64_t max_row = 0;              // longest row
+    int64_t span = 0;                 // sum over the rows of last column - first column
+    // Slices of x: what CSR-panel makes of a matrix to which slices_of() gives some
+    // (none of the panel arrays then; the layout: slices.hip)
+    int slice_P = 0;
+    int32_t *slice_base = nullptr;       // all in one block, which slice_val starts
+    unsigned short *slice_ends = nullptr;
+    unsigned short *slice_col = nullptr;
+    double *slice_val = nullptr;
+    float *slice_val32 = nullptr;
     // slot copies (batched.hpp) of a small matrix, FP64 and FP32 values
     char *slot_mem[2] = {nullptr, nullptr};
     std::atomic<bool> has_slot[2] = {false, false};

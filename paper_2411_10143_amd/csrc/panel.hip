@@ -22,16 +22,6 @@
 // 1.2M, 33M entries) took 1,420 us, 328 us now.
 constexpr int kLongPanelRow = 512;
 
-// column / W by the rounded reciprocal: off by at most one either way before
-// the correction (a column is below 2^31, a panel index below 2^14).
-__device__ __forceinline__ int panel_of(int c, int W, float inv) {
-    int q = (int)((float)c * inv);
-    const int64_t lo = (int64_t)q * W;
-    q -= c < lo ? 1 : 0;
-    q += c >= lo + W ? 1 : 0;
-    return q;
-}
-
 // cnt[p*n + i] = entries of row i whose column lies in panel p, and *filled +=
 // the panel rows that have any.  A workgroup takes 32 rows, eight lanes each,
 // and eight panels at a time.  Rows of at most kCountRow entries are counted
@@ -214,7 +204,7 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (c[u] >= 0)
-                    put(s_shift[row][panel_of(c[u], W, inv) - p0] + k0 + u * L + lane, c[u], v[u]);
+                    put(s_shift[row][ck::panel_of(c[u], W, inv) - p0] + k0 + u * L + lane, c[u], v[u]);
         }
         base += total;
         __syncthreads();   // s_dst and s_shift are rewritten
@@ -241,7 +231,7 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
             const int total = s_first[L];
             for (int k = tid; k < total; k += 256) {
                 const int c = col[from + k];
-                const int q = panel_of(c, W, inv) - p0;
+                const int q = ck::panel_of(c, W, inv) - p0;
                 put(s_dst[q][0] + (k - s_first[q]), c, val[from + k]);
             }
             from += total;
@@ -484,7 +474,7 @@ int64_t panel_scan_tmp_elems(int64_t N) {
     return b1 + b1 + b2 + b2 + 2048 + 64;
 }
 
-// Exclusive scan of N ints (N + 1 outputs: out[N] = total), three levels.
+// Exclusive scan of N ints (N + 1 outputs: out[N] = total), up to three levels.
 ck_status launch_scan_exclusive(int64_t N, const int *in, int *out, int *tmp, hipStream_t s) {
     const int64_t M = N + 1;                     // in[N] is read as 0 via the bound
     const int64_t b1 = ceil_div(M, 2048);
@@ -496,8 +486,10 @@ ck_status launch_scan_exclusive(int64_t N, const int *in, int *out, int *tmp, hi
         return fail(CK_E_UNSUPPORTED, "scan too large");
     hipLaunchKernelGGL(scan_blocks, dim3(b1), dim3(256), 0, s, N, M, in, out, s1);
     hipLaunchKernelGGL(scan_blocks, dim3(b2), dim3(256), 0, s, b1, b1, s1, s1x, s2);
-    hipLaunchKernelGGL(scan_blocks, dim3(1), dim3(256), 0, s, b2, b2, s2, s2x, s3);
-    hipLaunchKernelGGL(scan_add, dim3(ceil_div(b1, 256)), dim3(256), 0, s, b1, s1x, s2x);
+    if (b2 > 1) {
+        hipLaunchKernelGGL(scan_blocks, dim3(1), dim3(256), 0, s, b2, b2, s2, s2x, s3);
+        hipLaunchKernelGGL(scan_add, dim3(ceil_div(b1, 256)), dim3(256), 0, s, b1, s1x, s2x);
+    }
     hipLaunchKernelGGL(scan_add, dim3(ceil_div(M, 256)), dim3(256), 0, s, M, out, s1x);
     CK_HIP(hipGetLastError());
     return CK_OK;
@@ -588,15 +580,14 @@ ck_status launch_panel_combine(const ck_matrix &M, const SpmvArgs<T> &a, const T
         CK_HIP(hipGetLastError());
         return CK_OK;
     }
+    const int P = M.slice_val != nullptr ? M.slice_P : M.panel_P;
     if (dot)
-        hipLaunchKernelGGL((panel_combine<T, false, true>), grid, dim3(256), 0, s, M.n, M.panel_P,
-                           G, ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
+        hipLaunchKernelGGL((panel_combine<T, false, true>), grid, dim3(256), 0, s, M.n, P, G, ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
     else if (beta)
-        hipLaunchKernelGGL((panel_combine<T, true, false>), grid, dim3(256), 0, s, M.n, M.panel_P,
-                           G, ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
+        hipLaunchKernelGGL((panel_combine<T, true, false>), grid, dim3(256), 0, s, M.n, P, G, ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
     else
-        hipLaunchKernelGGL((panel_combine<T, false, false>), grid, dim3(256), 0, s, M.n,
-                           M.panel_P, G, ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
+        hipLaunchKernelGGL((panel_combine<T, false, false>), grid, dim3(256), 0, s, M.n, P, G,
+                           ypart, a.alpha, a.beta, a.y, a.x, a.dot_partials, a.skip);
     CK_HIP(hipGetLastError());
     return CK_OK;
 }

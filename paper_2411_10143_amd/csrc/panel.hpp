@@ -26,7 +26,8 @@ ck_status launch_to_panel(const ck_matrix &M, int P, int64_t W, int *cnt, int *t
 // row-list layout when at most 3/4 of the P*n panel rows are filled (cnt is
 // overwritten).  Returns when done.
 ck_status panel_make_rows(ck_matrix &M, int *cnt, int64_t filled, hipStream_t s);
-// y = alpha * (sum of the P partial vectors, in panel order) + beta * y
+// y = alpha * (sum of the P partial vectors, in panel order) + beta * y (M's slices'
+// where it has them)
 template <typename T>
 ck_status launch_panel_combine(const ck_matrix &M, const SpmvArgs<T> &a, const T *ypart,
                                int64_t G_dot, hipStream_t s);

@@ -34,6 +34,7 @@
 #include "matrix.hpp"
 #include "diahyb.hpp"
 #include "panel.hpp"
+#include "slices.hpp"
 #include "predictor.hpp"
 #include "solvers.hpp"
 
@@ -130,7 +131,9 @@ int64_t handle_bytes(const ck_matrix &M) {
                         : 4 * M.dia_nd + M.dia_nd * M.dia_pitch * (8 + (M.dia_val32 ? 4 : 0));
     if (M.has_hyb.load())
         b += 4 * M.hyb_nt + M.hyb_K * M.hyb_pitch * (12 + (M.hyb_val32 ? 4 : 0));
-    if (M.has_panel.load())
+    if (M.has_panel.load() && M.slice_val != nullptr)
+        b += slices_bytes(M.n, M.nnz, M.slice_P, M.val32 != nullptr);
+    else if (M.has_panel.load())
         b += M.nnz * (12 + (M.panel_val32 ? 4 : 0)) +
              (M.panel_row ? 4 * M.panel_rows + 4 * (int64_t)M.panel_P * (M.panel_B + 1) : 0) +
              4 * merge_plan_ints(M.panel_rows, M.nnz);

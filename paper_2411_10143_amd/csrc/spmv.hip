@@ -29,6 +29,7 @@
 #include "diahyb.hpp"
 #include "matrix.hpp"
 #include "panel.hpp"
+#include "slices.hpp"
 #include "solvers.hpp"
 
 using ck::ld_stream;
@@ -766,27 +767,32 @@ static int64_t carry_array_bytes(int64_t G, bool fp32) {
     return ((G * (int64_t)sizeof(int) + 255) / 256) * 256 + G * (fp32 ? 4 : 8) + 256;
 }
 
+// CSR-panel: per-panel partial sums, then (merge-path panels) the carries of the
+// merge over the panel rows in workgroups of `items`; sized for the dense P*n
+// layout (an upper bound: the row-list layout has fewer rows, and the size is
+// also needed before the conversion decides).
+static int64_t panel_work_bytes(const ck_matrix &M, int64_t items, bool fp32) {
+    const int64_t rows = (int64_t)panel_count_for(M.ncols, 8) * M.n;
+    return ((rows * (fp32 ? 4 : 8) + 255) / 256) * 256 +
+           carry_array_bytes(ceil_div(rows + M.nnz, items), fp32);
+}
+
+// The same for slices of x, if M takes them: at most 64 MiB.
+static int64_t slices_work_bytes_of(const ck_matrix &M, bool fp32) {
+    return slices_work_bytes(M.n, slices_of(M.n, M.ncols, M.nnz, M.max_row, M.span), fp32);
+}
+
 int64_t spmv_carry_bytes(const ck_matrix &M, const ck_config &c, bool fp32) {
-    if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL) {
-        // per-panel partial sums, then (merge-path panels) the carries of the
-        // merge over the panel rows; sized for the dense P*n layout (an upper
-        // bound: the row-list layout has fewer rows, and the size is also
-        // needed before the conversion decides)
-        const int64_t rows = (int64_t)panel_count_for(M.ncols, 8) * M.n;
-        return ((rows * (fp32 ? 4 : 8) + 255) / 256) * 256 +
-               carry_array_bytes(ceil_div(rows + M.nnz, kMergeSpan), fp32);
-    }
+    if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL)
+        return std::max(panel_work_bytes(M, kMergeSpan, fp32), slices_work_bytes_of(M, fp32));
     return carry_array_bytes(carry_blocks(M, c), fp32);
 }
 
 int64_t spmv_noalloc_bytes(const ck_matrix &M, const ck_config &c) {
-    int64_t b = spmv_carry_bytes(M, c, false);
-    if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL) {
-        const int64_t items = (int64_t)panel_count_for(M.ncols, 8) * M.n + M.nnz;
-        b += carry_array_bytes(ceil_div(items, 256 * kMergeIPT), false) -
-             carry_array_bytes(ceil_div(items, kMergeSpan), false);
-    }
-    return b;
+    if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL)
+        return std::max(panel_work_bytes(M, 256 * kMergeIPT, false),
+                        slices_work_bytes_of(M, false));
+    return spmv_carry_bytes(M, c, false);
 }
 
 // ---- merge-path plan: G + 1 coordinate pairs and 64 words of row-end bits per
@@ -1039,7 +1045,8 @@ ck_status launch_spmv(const ck_matrix &M, const ck_config &c, const SpmvArgs<T> 
         void *ws = a.carry;
         if (ws == nullptr)
             CK_HIP(hipMallocAsync(&ws, (size_t)spmv_carry_bytes(M, c, sizeof(T) == 4), s));
-        st = panel_merge_spmv<T>(M, a, ws, spmv_dot_blocks(M, c), s);
+        st = M.slice_val != nullptr ? launch_slices<T>(M, a, (T *)ws, spmv_dot_blocks(M, c), s)
+                                    : panel_merge_spmv<T>(M, a, ws, spmv_dot_blocks(M, c), s);
         if (a.carry == nullptr)
             CK_HIP(hipFreeAsync(ws, s));
     } else if (M.nnz == 0 && !dot) {
