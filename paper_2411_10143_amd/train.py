@@ -23,8 +23,9 @@ decision tree per stage and export the trees as the library's model file.
 
 The corpus is synthetic (stencil, power-law, block-diagonal and uniform-random
 families, disjoint seeds from the 48 held-out evaluation matrices, plus
-Chung-Lu graph Laplacians, whose hub columns none of those families has),
-timed on this GPU.
+Chung-Lu graph Laplacians, whose hub columns none of those families has, and
+uniform-random rows of other lengths than the uniform family's), timed on this
+GPU.
 
   python -m paper_2411_10143_amd.train collect --out data.csv [--count 200]
   python -m paper_2411_10143_amd.train retime --data data.csv --out new.csv --configs 11
@@ -112,16 +113,19 @@ def collect(out_csv, count=600, seed=9000, reps=None):
     import paper_2411_10143_amd as ck
     from synth import workloads as W
 
-    specs = W.training_specs(count=count, seed=seed)
+    specs = W.training_specs(count=count, seed=seed) + W.row_specs()
     new = not os.path.exists(out_csv)
     done = set()
     if not new:
         with open(out_csv) as f:
             done = {row["name"] for row in csv.DictReader(f)}
+    # one column per name ("nnz" is a feature too), in the order of the file
+    fields = list(dict.fromkeys(["name", "family", "n", "nnz"] + FEATURES +
+                                [f"t{c}" for c in range(CONFIGS)]))
     f = open(out_csv, "a", newline="")
-    w = csv.writer(f)
+    w = csv.DictWriter(f, fieldnames=fields)
     if new:
-        w.writerow(["name", "family", "n", "nnz"] + FEATURES + [f"t{c}" for c in range(CONFIGS)])
+        w.writeheader()
     t0 = time.time()
     for i, spec in enumerate(specs):
         name, fam, k, n, s = spec
@@ -135,8 +139,10 @@ def collect(out_csv, count=600, seed=9000, reps=None):
         times = time_all_configs(ck, Mx, x, y, reps=reps)
         Mx.close()
         del x, y
-        w.writerow([name, fam, A.n, A.nnz] + [repr(v) for v in F.model_inputs()] +
-                   [repr(v) for v in times])
+        row = {"name": name, "family": fam, "n": A.n}
+        row.update((k, repr(v)) for k, v in zip(FEATURES, F.model_inputs()))
+        row.update((f"t{c}", repr(t)) for c, t in enumerate(times))
+        w.writerow(row)
         f.flush()
         best = int(np.argmin(times))
         print(f"[{i + 1}/{len(specs)}] {name} nnz={A.nnz} best={ck.CONFIG_NAMES[best]} "
@@ -170,7 +176,8 @@ def retime(in_csv, out_csv, configs, count=600, seed=9000, reps=None, jobs=8, tm
     with open(in_csv) as f:
         rows = list(csv.DictReader(f))
     byname = {r["name"]: r for r in rows}
-    specs = [sp for sp in W.training_specs(count=count, seed=seed) if sp[0] in byname]
+    specs = [sp for sp in W.training_specs(count=count, seed=seed) + W.row_specs()
+             if sp[0] in byname]
     d = tempfile.mkdtemp(dir=tmpdir)
     work = [(sp, os.path.join(d, f"m{i}.npz")) for i, sp in enumerate(specs)]
     t0 = time.time()
@@ -313,7 +320,7 @@ def main(argv=None):
     fa = sub.add_parser("fit")
     fa.add_argument("--data", required=True, nargs="+")
     fa.add_argument("--model", required=True)
-    fa.add_argument("--max-depth", type=int, default=5)
+    fa.add_argument("--max-depth", type=int, default=6)
     fa.add_argument("--min-leaf", type=int, default=1)
     fa.add_argument("--start-depth", type=int, default=8)
     fa.add_argument("--start-min-leaf", type=int, default=3)
@@ -325,14 +332,18 @@ def main(argv=None):
     elif a.cmd == "retime":
         retime(a.data, a.out, a.configs, a.count, a.seed, a.reps, a.jobs)
     else:
-        Xs, Ts = [], []
+        Xs, Ts, names = [], [], []
         for d in a.data:
-            X, T, _ = load(d)
+            X, T, N = load(d)
             Xs.append(X)
             Ts.append(T)
+            names += N
         X, T = np.concatenate(Xs), np.concatenate(Ts)
         trees, Y = fit_trees(X, T, a.max_depth, a.min_leaf, tie=a.tie)
-        start = fit_start(X, T, a.start_depth, a.start_min_leaf)
+        # the start tree without the "rows" family: its CSR-merge times are with
+        # the partition, which a matrix has not got when a solve starts
+        known = np.array(["_rows" not in n for n in names])
+        start = fit_start(X[known], T[known], a.start_depth, a.start_min_leaf)
         picks = np.array([cascade_predict(trees, x) for x in X])
         rows = np.arange(len(T))
         slow = T[rows, picks] / T.min(axis=1)

@@ -21,6 +21,11 @@ from . import matrices as M
 FAMILIES = ("banded", "powerlaw", "blockdiag", "uniform")
 TRAIN_FAMILIES = FAMILIES + ("graph",)
 GRAPH_MAX_N = 600_000        # keeps a training graph's generation to seconds
+# row lengths (least, most) of the "rows" training family: uniform-random
+# columns like "uniform", whose rows all average 34 entries
+ROW_LENGTHS = ((1, 8), (4, 16), (8, 24), (4, 32), (1, 40), (16, 48), (30, 40), (50, 150),
+               (100, 300))
+ROWS_MAX_NNZ = 12_000_000
 BANDED_R = (5, 7, 9, 13, 19, 27, 5, 7, 9, 13, 19, 27)
 
 
@@ -44,6 +49,8 @@ def family_matrix(family: str, k: int, n: int, seed: int) -> M.CSR:
         return M.block_diagonal(n, seed)
     if family == "uniform":
         return M.uniform_random(n, seed)
+    if family == "rows":
+        return M.uniform_random(n, seed, *ROW_LENGTHS[k])
     if family == "graph":
         return M.graph_laplacian_chung_lu(n, seed, mean_degree=(4, 8, 16, 32)[k % 4],
                                           zipf_s=(1.8, 2.0, 2.2)[k % 3],
@@ -82,6 +89,20 @@ def training_specs(count: int = 600, seed: int = 9000, lo: float = 1e4, hi: floa
             n = min(n, GRAPH_MAX_N)
         k = int(rng.integers(0, 12))
         out.append((f"train{t}_{fam}_n{n}", fam, k, n, seed + 1 + t))
+    return out
+
+
+def row_specs(count: int = 162, seed: int = 9700, lo: float = 1e4, hi: float = 1e6):
+    """Training matrices of the "rows" family: the row lengths cycle, n
+    log-uniform from lo to hi or to ROWS_MAX_NNZ entries."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for t in range(count):
+        k = t % len(ROW_LENGTHS)
+        top = min(hi, ROWS_MAX_NNZ / (sum(ROW_LENGTHS[k]) / 2))
+        n = int(round(10 ** rng.uniform(math.log10(lo), math.log10(top))))
+        out.append((f"train_rows{t}_{ROW_LENGTHS[k][0]}-{ROW_LENGTHS[k][1]}_n{n}", "rows", k, n,
+                    seed + 1 + t))
     return out
 
 
