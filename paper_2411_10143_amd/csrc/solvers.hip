@@ -781,10 +781,14 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
 
 enum class Solver { CG, GMRES };
 
-// Systems up to this size run the whole solve inside one 1024-thread
-// workgroup (the batched slot kernel): at this size a launch per step costs
-// more than the step itself.
-constexpr int64_t kSmallN = 16384;
+// CG systems of at most this many rows run in one workgroup (FP64 ones of at most
+// kWgCgMaxN in a kernel of their own).  Per iteration, one workgroup against the
+// multi-workgroup kernels: mixed, 2D Laplacian, n = 1,024 3.7 us, 10.7; n = 8,100 9.5,
+// 12.3; FP64 n = 6,400 11.2, 12.3; n = 8,100 13.0, 12.4; 3D n = 8,000 15.4, 13.7; past
+// kSlotRows a workgroup's vectors leave LDS.  GMRES never does: its steps are three
+// launches of about 20 us together (FP64 24) up to n = 20,000, and one workgroup takes
+// 19.7 (29) at n = 250, 31 (55) at n = 4,096, 51 (97) at n = 8,192 and 169 (243) at 8,193.
+constexpr int64_t kSmallMixed = kSlotRows, kSmallFp64 = 6144;
 
 // FP64 CG of a system of at most kWgCgMaxN rows in one single-workgroup launch
 ck_status wg_cg_solve(SolveCtx &c, const double *b, double *x) {
@@ -812,10 +816,9 @@ ck_status wg_cg_solve(SolveCtx &c, const double *b, double *x) {
                 h.relres);
 }
 
-ck_status small_solve(SolveCtx &c, const double *b, double *x, bool cg, int m) {
+ck_status small_solve(SolveCtx &c, const double *b, double *x) {
     ck_matrix &M = c.M;
     const bool fp32 = c.o.precision == CK_PREC_MIXED;
-    const int kind = cg ? B_CG : B_GMRES;
     const int64_t ld = ceil_div(M.n, 64) * 64;
     Workspace ws(c.M, c.s);
     BSlot *slot;
@@ -826,17 +829,14 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool cg, int m) {
     CK_TRY(ws.get(&slot, 1));
     CK_TRY(ws.get(&stat, 1));
     CK_TRY(ws.get(&active, 1));
-    CK_TRY(ws.get(&work, bslot_work_elems(kind, M.n, m) * (fp32 ? 4 : 8)));
+    CK_TRY(ws.get(&work, bslot_work_elems(B_CG, M.n, 0) * (fp32 ? 4 : 8)));
     CK_TRY(ws.get(&r64, ld));
-    if (M.n <= kSlotRows)
-        CK_TRY(build_slot_copy(M, fp32, c.s));
+    CK_TRY(build_slot_copy(M, fp32, c.s));
     BSlot *h = (BSlot *)std::calloc(1, sizeof(BSlot));
-    if (M.n <= kSlotRows)
-        h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
-    h->kind = kind;
+    h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
+    h->kind = B_CG;
     h->n = (int)M.n;
     h->lanes = c.cfg.lanes;
-    h->m = m;
     h->rp = M.rp;
     h->col = M.col;
     h->val64 = M.val;
@@ -964,8 +964,9 @@ ck_status solve(ck_handle hnd, const double *b, double *x, const ck_solve_opts *
         return st;
     }
     const bool vector_cfg = c.cfg.format == CK_FMT_CSR && c.cfg.algorithm == CK_ALG_VECTOR;
-    if (M.n <= kSmallN && !run_async && vector_cfg && (which == Solver::CG || m <= kBMaxM)) {
-        const ck_status st = small_solve(c, b, x, which == Solver::CG, m);
+    const int64_t small = opts->precision == CK_PREC_FP64 ? kSmallFp64 : kSmallMixed;
+    if (M.n <= small && !run_async && vector_cfg && which == Solver::CG) {
+        const ck_status st = small_solve(c, b, x);
         res->final_config = c.cfg;
         res->status = st;
         res->t_total_us = us_since(t0);
