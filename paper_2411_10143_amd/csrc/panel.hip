@@ -134,10 +134,15 @@ __global__ __launch_bounds__(256) void panel_count(int64_t n, int P, int W,
 // entries of consecutive panels are consecutive.  The eight lanes copy the
 // row's entries of those panels together, lane l taking entries l, l + 8, ...
 // (coalesced loads), an entry's panel being its column / W.  Rows over
-// kLongPanelRow are copied at the end by the whole workgroup.  16M entries in
-// four panels: 150 us with the panels' destinations read per row and one entry
-// per lane in flight, 115 us this way; power-law, 33M entries, 328 us.
-template <bool F32>
+// kLongPanelRow are copied at the end by the whole workgroup: power-law rows, 33M
+// entries, 328 us.  STAGE (matrices with no such row): the entries are put in order
+// in LDS and leave it panel by panel, coalesced, unless a group has more than
+// kPanelStage of them.  Stored from where they are read, a few to a line, 16M
+// entries in four panels took 113 us, 97 us this way; of rows of 27 in eight panels
+// most lines are partial either way, and the LDS costs waves (328 us, 414).
+constexpr int kPanelStage = 2048;
+
+template <bool F32, bool STAGE>
 __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
                                                   const int *__restrict__ rp,
                                                   const int *__restrict__ col,
@@ -149,7 +154,9 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
     __shared__ int s_long[R], s_count;
     __shared__ int s_dst[L][R + 1];     // panel p0 + p, row r
     __shared__ int s_shift[R][L + 1];   // destination minus the entry's place in the row
-    __shared__ int s_first[L + 1];
+    __shared__ int s_first[L + 1];      // of each panel's entries in LDS
+    __shared__ double s_val[STAGE ? kPanelStage : 1];
+    __shared__ int s_col[STAGE ? kPanelStage : 1];
     const int tid = threadIdx.x, lane = tid & (L - 1), row = tid / L;
     const int64_t i0 = (int64_t)blockIdx.x * R, i = i0 + row;
     const float inv = 1.0f / (float)W;
@@ -190,7 +197,16 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
                 ex += o;
         }
         const int total = shrt ? __shfl(ex, L - 1, L) : 0;
-        s_shift[row][lane] = dst - (ex - len);
+        if (STAGE && tid < 64) {   // where the panels start in LDS
+            const int count = tid < L ? s_dst[tid][R] - s_dst[tid][0] : 0;
+            const int scan = ck::wave_scan(count);
+            if (tid <= L)
+                s_first[tid] = scan - count;
+        }
+        if (STAGE)
+            __syncthreads();
+        const bool staged = STAGE && s_count == 0 && s_first[L] <= kPanelStage;   // uniform
+        s_shift[row][lane] = dst - (ex - len) - (staged ? s_dst[lane][0] - s_first[lane] : 0);
         __syncthreads();
         for (int k0 = 0; k0 < total; k0 += L * U) {
             int c[U];
@@ -203,11 +219,27 @@ __global__ __launch_bounds__(256) void panel_fill(int64_t n, int P, int W,
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (c[u] >= 0)
-                    put(s_shift[row][ck::panel_of(c[u], W, inv) - p0] + k0 + u * L + lane, c[u], v[u]);
+                if (c[u] >= 0) {
+                    const int to =
+                        s_shift[row][ck::panel_of(c[u], W, inv) - p0] + k0 + u * L + lane;
+                    if (staged) {
+                        s_col[to] = c[u];
+                        s_val[to] = v[u];
+                    } else {
+                        put(to, c[u], v[u]);
+                    }
+                }
         }
         base += total;
-        __syncthreads();   // s_dst and s_shift are rewritten
+        __syncthreads();
+        if (staged) {
+            for (int p = tid >> 6; p < L; p += 4) {
+                const int from = s_first[p], count = s_first[p + 1] - from, to = s_dst[p][0];
+                for (int k = tid & 63; k < count; k += 64)
+                    put(to + k, s_col[from + k], s_val[from + k]);
+            }
+            __syncthreads();   // s_dst, s_shift and s_first are rewritten
+        }
     }
     const int count = s_count;   // written before the barriers, and not again
     for (int t = 0; t < count; ++t) {
@@ -500,12 +532,15 @@ ck_status launch_to_panel(const ck_matrix &M, int P, int64_t W, int *cnt, int *t
     CK_TRY(launch_scan_exclusive((int64_t)P * M.n, cnt, prp, tmp, s));
     const int64_t g8 = ceil_div(M.n, 256 / 8);
     const int Wi = (int)W;   // W <= ncols < 2^31
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(g8), dim3(256), 0, s, M.n, P, Wi, M.rp, M.col, M.val, prp,
+                           pcol, pval, pval32);
+    };
+    const bool stage = M.max_row <= kLongPanelRow && M.max_row * M.n <= 4 * M.nnz;
     if (pval32)
-        hipLaunchKernelGGL((panel_fill<true>), dim3(g8), dim3(256), 0, s, M.n, P, Wi, M.rp,
-                           M.col, M.val, prp, pcol, pval, pval32);
+        stage ? go(panel_fill<true, true>) : go(panel_fill<true, false>);
     else
-        hipLaunchKernelGGL((panel_fill<false>), dim3(g8), dim3(256), 0, s, M.n, P, Wi, M.rp,
-                           M.col, M.val, prp, pcol, pval, pval32);
+        stage ? go(panel_fill<false, true>) : go(panel_fill<false, false>);
     CK_HIP(hipGetLastError());
     return CK_OK;
 }

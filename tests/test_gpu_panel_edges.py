@@ -37,6 +37,8 @@ LENGTHS = {
     "rows_31": [70] * 31,
     "rows_33": [3] * 30 + [900, 0, 20],
     "short": [0, 1, 2, 0, 0] * 300,
+    "even": [34, 20, 48] * 70 + [64],          # 32 rows fit the staging of the copy
+    "even_long": [180, 200, 90] * 30,          # and do not
 }
 
 
