@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256) void panel_combine_rows(
     const int64_t b = ck::xcd_block(G);
     if (b < 0)
         return;
-    __shared__ T acc[256];
+    __shared__ double acc[256];   // as in panel_combine
     const int tid = threadIdx.x;
     T mine = 0;
     for (int64_t blk = b; blk < B; blk += G) {
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256) void panel_combine_rows(
         }
         const int64_t i = r0 + tid;
         if (i < n) {
-            T out = alpha * acc[tid];
+            T out = alpha * (T)acc[tid];
             if (BETA)
                 out += beta * y[i];
             y[i] = out;
@@ -404,7 +404,9 @@ __global__ __launch_bounds__(256) void panel_combine_rows(
     }
 }
 
-// y = alpha * sum_p ypart[p] + beta * y   (+ per-block partial of y.x for CG)
+// y = alpha * sum_p ypart[p] + beta * y   (+ per-block partial of y.x for CG).
+// FP32 partial sums are added in FP64, which costs nothing here: with up to 22
+// of them (slices of x) the FP32 sum's rounding showed in the result.
 template <typename T, bool BETA, bool DOT>
 __global__ __launch_bounds__(256) void panel_combine(int64_t n, int P, int64_t G,
                                                      const T *__restrict__ ypart, T alpha, T beta,
@@ -418,10 +420,10 @@ __global__ __launch_bounds__(256) void panel_combine(int64_t n, int P, int64_t G
         return;
     T mine = 0;
     for (int64_t i = b * 256 + threadIdx.x; i < n; i += G * 256) {
-        T s = 0;
+        double s = 0;
         for (int p = 0; p < P; ++p)
             s += ypart[(int64_t)p * n + i];
-        T out = alpha * s;
+        T out = alpha * (T)s;
         if (BETA)
             out += beta * y[i];
         y[i] = out;
