@@ -482,7 +482,7 @@ def bench_cg_lap2d(args):
                 {"latency_ms": {"p50": round(1e3 * float(np.percentile(lat, 50)), 3),
                                 "p99": round(1e3 * float(np.percentile(lat, 99)), 3)},
                  "iterations": int(np.median(iters)), "solves": len(lat)},
-                {"bound": "hbm", "kernel": "cg_wg<4> (single-workgroup CG)",
+                {"bound": "hbm", "kernel": "cg_wg<512, 8> (single-workgroup CG)",
                  "achieved": round(eff, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                  "frac": round(eff / HBM_PEAK_GBS, 5), "traffic": None,
                  "note": "n=4096: the whole system sits in one CU's registers and LDS; "
@@ -835,7 +835,7 @@ def solver_summary(args):
     lat, r, x = _timed_solves(ck, ck.cg_solve, Mx, b, 100, 5, tol=1e-10)
     assert oracle.relres(A, b.cpu().numpy(), x.cpu().numpy()) <= 1e-10
     row = {"default_path": {**_lat(lat), "iterations": r["iterations"],
-                            "kernel": "cg_wg<4>: whole solve in one workgroup, one lane per row, matrix in registers"}}
+                            "kernel": "cg_wg<512, 8>: whole solve in one workgroup, one lane per row, matrix in registers"}}
     cfg = ck.default_config(Mx.handle)
     lat, r, x = _timed_solves(ck, ck.cg_solve, Mx, b, 100, 5, tol=1e-10, config=cfg)
     assert oracle.relres(A, b.cpu().numpy(), x.cpu().numpy()) <= 1e-10

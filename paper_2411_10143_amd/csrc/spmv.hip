@@ -47,7 +47,7 @@ constexpr int kScalarCap = 4096;  // products staged per LDS chunk (CSR-scalar)
 // than the dispatcher can issue in a few microseconds.
 //
 // Fused CG step: every block adds q_i * p_i over its rows (x = p, y = q) and
-// stores its partial; the CG "sigma" finish kernel sums them in block order
+// stores its partial; the r update (or a one-block finish) sums them in block order
 // and sets alpha = rho / sigma (or flags a breakdown when sigma <= 0).
 template <typename T, bool DOT>
 __device__ __forceinline__ void cg_sigma_epilogue(T mine, ck::CgDev<T> *cg, T *partials,
