@@ -384,73 +384,42 @@ __global__ __launch_bounds__(256) void feat_ndiag(int64_t n16, const uint4 *__re
         part_diag[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-// Sums the partial slots of every pass (integer sums, max and min: exact
-// and order-free) into the accumulators.  One block of 1024 threads.
+// Sums (maximum, minimum) the passes' slots of every block; integers, so exact
+// and order-free.  One block of sixteen waves, a wave per field (eight take two),
+// its lanes striding the slots with eight loads in flight: with a thread per slot
+// and 24 block reductions one after the other it took 13.4 us, 9.1 us this way.
 __global__ __launch_bounds__(1024) void feat_finish(FeatAcc *acc, const unsigned long long *pr,
                                                    int Gr, const unsigned long long *pn, int Gn,
                                                    const unsigned long long *pd, int Gd) {
-    constexpr int F = kRowFields + kNnzFields + 1;   // + diagonals
-    unsigned long long v[F];
+    using u64 = unsigned long long;
+    constexpr int F = kRowFields + kNnzFields + 1, U = 8;   // + diagonals
+    const int lane = threadIdx.x & 63;
+    for (int f = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); f < F; f += 16) {
+        const bool rows = f < kRowFields, nnz = !rows && f < kRowFields + kNnzFields;
+        const int G = rows ? Gr : nnz ? Gn : Gd;
+        const u64 *q = rows ? pr + (int64_t)f * Gr : nnz ? pn + (int64_t)(f - kRowFields) * Gn : pd;
+        const u64 none = f == 4 ? ~0ull : 0ull;
+        auto join = [&](u64 x, u64 y) { return f == 3 ? max(x, y) : f == 4 ? min(x, y) : x + y; };
+        u64 t = none;
+        for (int b0 = lane; b0 < G; b0 += 64 * U) {
+            u64 v[U];
 #pragma unroll
-    for (int f = 0; f < F; ++f)
-        v[f] = f == 4 ? ~0ull : 0ull;
-    for (int b = threadIdx.x; b < Gr; b += 1024) {
-        const unsigned long long *q = pr + b;   // field f at q[f * Gr]
-        v[0] += q[0];
-        v[1] += q[Gr];
-        v[2] += q[2 * Gr];
-        v[3] = q[3 * Gr] > v[3] ? q[3 * Gr] : v[3];
-        v[4] = q[4 * Gr] < v[4] ? q[4 * Gr] : v[4];
+            for (int u = 0; u < U; ++u)
+                v[u] = q[min(b0 + 64 * u, G - 1)];
 #pragma unroll
-        for (int h = 0; h < 16; ++h)
-            v[5 + h] += q[(int64_t)(5 + h) * Gr];
-    }
-    for (int b = threadIdx.x; b < Gn; b += 1024) {
-        v[21] += pn[b];
-        v[22] += pn[Gn + b];
-    }
-    for (int b = threadIdx.x; b < Gd; b += 1024)
-        v[23] += pd[b];
-    __shared__ unsigned long long part[F][16];
-    const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-        unsigned long long t;
-        if (f == 3)   // wave results in lane 63
-            t = ck::wave_max_last(v[f]);
-        else if (f == 4)
-            t = ck::wave_min_last(v[f]);
-        else
-            t = ck::wave_sum_last(v[f]);
-        if ((threadIdx.x & 63) == 63)
-            part[f][w] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < F) {
-        const int f = threadIdx.x;
-        unsigned long long t = part[f][0];
-        for (int u = 1; u < 16; ++u) {
-            const unsigned long long o = part[f][u];
-            t = f == 3 ? (o > t ? o : t) : f == 4 ? (o < t ? o : t) : t + o;
+            for (int u = 0; u < U; ++u)
+                t = join(t, b0 + 64 * u < G ? v[u] : none);
         }
-        if (f == 0)
-            acc->sum_r = t;
-        else if (f == 1)
-            acc->sum_r2 = t;
-        else if (f == 2)
-            acc->span = t;
-        else if (f == 3)
-            acc->max_r = t;
-        else if (f == 4)
-            acc->min_r = t;
-        else if (f < 21)
+        t = f == 3 ? ck::wave_max_last(t) : f == 4 ? ck::wave_min_last(t) : ck::wave_sum_last(t);
+        if (lane != 63)   // the wave's result is in lane 63
+            continue;
+        u64 *const one[] = {&acc->sum_r, &acc->sum_r2, &acc->span, &acc->max_r, &acc->min_r};
+        if (f < 5)
+            *one[f] = t;
+        else if (rows)
             acc->hist[f - 5] = t;
-        else if (f == 21)
-            acc->cluster = t;
-        else if (f == 22)
-            acc->diag_nnz = t;
         else
-            acc->ndiag = t;
+            *(f == 21 ? &acc->cluster : f == 22 ? &acc->diag_nnz : &acc->ndiag) = t;
     }
 }
 
