@@ -75,6 +75,15 @@ def time_all_configs(ck, Mx, x, y, warmup=10, reps=None):
     return out
 
 
+def time_unplanned_merge(ck, Mx, x, y, warmup=10, reps=None):
+    """Mean us per CSR-merge product of a handle not converted to it, whose
+    workgroups search their starts: what a solve that starts on it runs."""
+    cfg = ck.config_from_id(8)
+    if reps is None:
+        reps = reps_for(ck.time_spmv(Mx.handle, cfg, x, y, warmup=warmup, reps=5))
+    return ck.time_spmv(Mx.handle, cfg, x, y, warmup=2, reps=reps)
+
+
 def _first_within(t, tie):
     """Index of the first time within a factor (1 + tie) of the smallest."""
     t = np.asarray(t, dtype=np.float64)
@@ -121,7 +130,7 @@ def collect(out_csv, count=600, seed=9000, reps=None):
             done = {row["name"] for row in csv.DictReader(f)}
     # one column per name ("nnz" is a feature too), in the order of the file
     fields = list(dict.fromkeys(["name", "family", "n", "nnz"] + FEATURES +
-                                [f"t{c}" for c in range(CONFIGS)]))
+                                [f"t{c}" for c in range(CONFIGS)] + ["t8_start"]))
     f = open(out_csv, "a", newline="")
     w = csv.DictWriter(f, fieldnames=fields)
     if new:
@@ -136,12 +145,14 @@ def collect(out_csv, count=600, seed=9000, reps=None):
         F = ck.spmv_features(Mx.handle)
         x = torch.from_numpy(np.random.default_rng(s).uniform(-1, 1, A.ncols)).cuda()
         y = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+        t8_start = time_unplanned_merge(ck, Mx, x, y, reps=reps)
         times = time_all_configs(ck, Mx, x, y, reps=reps)
         Mx.close()
         del x, y
         row = {"name": name, "family": fam, "n": A.n}
         row.update((k, repr(v)) for k, v in zip(FEATURES, F.model_inputs()))
         row.update((f"t{c}", repr(t)) for c, t in enumerate(times))
+        row["t8_start"] = repr(t8_start)
         w.writerow(row)
         f.flush()
         best = int(np.argmin(times))
@@ -192,6 +203,8 @@ def retime(in_csv, out_csv, configs, count=600, seed=9000, reps=None, jobs=8, tm
             y = torch.zeros(A.n, dtype=torch.float64, device="cuda")
             for cid in configs:
                 cfg = ck.config_from_id(cid)
+                if cid == 8:
+                    byname[name]["t8_start"] = repr(time_unplanned_merge(ck, Mx, x, y, reps=reps))
                 try:
                     ck.spmv_convert(Mx.handle, cfg)
                 except ck.CkError as e:
@@ -211,7 +224,10 @@ def retime(in_csv, out_csv, configs, count=600, seed=9000, reps=None, jobs=8, tm
             del x, y
     os.rmdir(d)
     with open(out_csv, "w", newline="") as f:
-        w = csv.DictWriter(f, fieldnames=list(rows[0].keys()))
+        fields = list(rows[0].keys())
+        if any("t8_start" in r for r in rows) and "t8_start" not in fields:
+            fields.append("t8_start")
+        w = csv.DictWriter(f, fieldnames=fields)
         w.writeheader()
         for r in rows:
             w.writerow(r)
@@ -227,6 +243,16 @@ def load(path):
                       for c in range(CONFIGS)])
             names.append(row["name"])
     return np.array(X), np.array(T), names
+
+
+def load_start_times(path):
+    """The times of load(), CSR-merge's without its plan where they are known."""
+    _, T, _ = load(path)
+    with open(path) as f:
+        for t, row in zip(T, csv.DictReader(f)):
+            if row.get("t8_start"):
+                t[8] = float(row["t8_start"])
+    return T
 
 
 def fit_trees(X, T, max_depth=8, min_leaf=2, seed=0, tie=0.0):
@@ -332,28 +358,25 @@ def main(argv=None):
     elif a.cmd == "retime":
         retime(a.data, a.out, a.configs, a.count, a.seed, a.reps, a.jobs)
     else:
-        Xs, Ts, names = [], [], []
+        Xs, Ts, Ss = [], [], []
         for d in a.data:
-            X, T, N = load(d)
+            X, T, _ = load(d)
             Xs.append(X)
             Ts.append(T)
-            names += N
-        X, T = np.concatenate(Xs), np.concatenate(Ts)
+            Ss.append(load_start_times(d))
+        X, T, S = np.concatenate(Xs), np.concatenate(Ts), np.concatenate(Ss)
         trees, Y = fit_trees(X, T, a.max_depth, a.min_leaf, tie=a.tie)
-        # the start tree without the "rows" family: its CSR-merge times are with
-        # the partition, which a matrix has not got when a solve starts
-        known = np.array(["_rows" not in n for n in names])
-        start = fit_start(X[known], T[known], a.start_depth, a.start_min_leaf)
+        start = fit_start(X, S, a.start_depth, a.start_min_leaf)
         picks = np.array([cascade_predict(trees, x) for x in X])
         rows = np.arange(len(T))
         slow = T[rows, picks] / T.min(axis=1)
         s_pick = start_predict(start, X)
         d_pick = np.array([default_id(int(x[0]), int(x[2])) for x in X])
         gm = lambda r: math.exp(np.mean(np.log(r)))
-        best9 = T[:, :NO_COPY].min(axis=1)
+        best9 = S[:, :NO_COPY].min(axis=1)
         note = (f"{len(X)} training matrices; training-set geomean t_pred/t_best = "
-                f"{gm(slow):.4f}; start tree vs the best of ids 0..8 {gm(T[rows, s_pick] / best9):.4f} "
-                f"(default rule {gm(T[rows, d_pick] / best9):.4f})")
+                f"{gm(slow):.4f}; start tree vs the best of ids 0..8 {gm(S[rows, s_pick] / best9):.4f} "
+                f"(default rule {gm(S[rows, d_pick] / best9):.4f})")
         export(trees + [start], a.model, note)
         print(note)
 

@@ -93,8 +93,9 @@ def training_specs(count: int = 600, seed: int = 9000, lo: float = 1e4, hi: floa
 
 
 def row_specs(count: int = 162, seed: int = 9700, lo: float = 1e4, hi: float = 1e6):
-    """Training matrices of the "rows" family: the row lengths cycle, n
-    log-uniform from lo to hi or to ROWS_MAX_NNZ entries."""
+    """Training matrices of the "rows" family (the row lengths cycle, n
+    log-uniform from lo to hi or to ROWS_MAX_NNZ entries) and small power-law
+    ones."""
     rng = np.random.default_rng(seed)
     out = []
     for t in range(count):
@@ -103,6 +104,10 @@ def row_specs(count: int = 162, seed: int = 9700, lo: float = 1e4, hi: float = 1
         n = int(round(10 ** rng.uniform(math.log10(lo), math.log10(top))))
         out.append((f"train_rows{t}_{ROW_LENGTHS[k][0]}-{ROW_LENGTHS[k][1]}_n{n}", "rows", k, n,
                     seed + 1 + t))
+    # power-law rows at the low end of the sizes, where training_specs has few
+    for t in range(36):
+        n = int(round(10 ** rng.uniform(math.log10(0.8 * lo), math.log10(2.5 * lo))))
+        out.append((f"train_rows_powerlaw{t}_n{n}", "powerlaw", t % 12, n, seed + 1001 + t))
     return out
 
 
