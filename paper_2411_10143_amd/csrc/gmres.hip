@@ -173,7 +173,7 @@ __device__ __forceinline__ void step_end(int s, int m, int64_t G, const T *__res
 // Givens step s from what step_end formed: Hessenberg column s, previous
 // rotations, new rotation, residual estimate and the cycle stop decision.  No
 // field that other blocks of the same kernel read is changed, except `halt`
-// (a block that sees it set only leaves out rows nothing will use).
+// (a wave that sees it set only leaves out rows nothing will use).
 template <typename T>
 __device__ __forceinline__ void givens_step(int s, int m, GmDev<T> *st, StepEnd<T> &e) {
     const int t = threadIdx.x;

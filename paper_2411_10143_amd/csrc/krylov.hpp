@@ -3,6 +3,7 @@
 // host only enqueues work and polls a small status record.
 #pragma once
 
+#include "cgstate.hpp"
 #include "common.hpp"
 
 namespace ck {
@@ -24,28 +25,6 @@ constexpr int kFoldPartials = 2048;
 // the next pass sums them all, so they are kept few.
 constexpr int kGmThreads = 512;
 constexpr int kGmMaxBlocks = 256;
-
-// Run states shared by the solvers
-enum : int { RUN = 0, CONVERGED = 1, BREAKDOWN = 2, BUDGET = 3 };
-
-// CG (Hestenes-Stiefel) scalars.  `state` != RUN makes every iteration
-// kernel a no-op, so the host may enqueue ahead of convergence.
-template <typename T>
-struct CgDev {
-    T rho;            // r.r of the current residual
-    T rho_prev;       // rho as the sigma finish saw it (read by the x/p
-                      // update while its block 0 replaces rho)
-    T sigma;          // p.Ap
-    T alpha, beta;
-    double bnorm;     // ||rhs|| of this (inner) solve
-    double tol;       // stop when sqrt(rho)/bnorm <= tol
-    double relres;    // last sqrt(rho)/bnorm
-    int state;
-    int iter;         // iterations completed
-    int max_iter;
-    int go;           // set by the sigma finish: 1 when this iteration's
-                      // x/p update runs (state RUN and sigma > 0)
-};
 
 // GMRES(m) cycle scalars (Givens form of the Hessenberg least squares).
 // cycle_stop ends the current cycle's Arnoldi steps; final_state ends the

@@ -117,9 +117,8 @@ inline void mat_free(ck_matrix &M, void *p) { mem_free(M.mem, p); }
 //  skip   : if non-null and *skip != 0 when the launch starts, it does nothing
 //           (lets a solver enqueue iterations ahead of its convergence test).
 //  cg     : fused CG step (only where spmv_fuses_dot() holds): the launch also
-//           forms sigma = y.x (x = p, y = q = A p) and its last block sets
-//           alpha = rho/sigma, or state = BREAKDOWN when sigma <= 0.
-//           dot_partials needs spmv_dot_blocks() entries.
+//           leaves every block's part of sigma = y.x (x = p, y = q = A p) in
+//           dot_partials, spmv_dot_blocks() entries.
 //  carry  : workspace of spmv_carry_bytes() for merge-path and COO carries
 //           and CSR-panel partial sums; when null the launch allocates it
 //           stream-ordered.

@@ -144,8 +144,8 @@ __global__ __launch_bounds__(256) void cg_sigma(int64_t n, int64_t G, const T *_
         partials[b] = s;
 }
 
-// sigma = p.Ap; alpha = rho/sigma, or BREAKDOWN when sigma <= 0.  `go`
-// tells the x/p update of this iteration whether to run.
+// sigma = p.Ap; alpha = rho/sigma.  `go` tells the r and x/p updates of this
+// iteration whether to run (not when sigma <= 0).
 template <typename T>
 __global__ __launch_bounds__(256) void cg_sigma_finish(int64_t G, const T *__restrict__ partials,
                                                        CgDev<T> *cg) {
@@ -156,26 +156,16 @@ __global__ __launch_bounds__(256) void cg_sigma_finish(int64_t G, const T *__res
         return;
     }
     const T sigma = ck::sum_partials(partials, G, lds);
-    if (threadIdx.x == 0) {
-        cg->sigma = sigma;
-        cg->rho_prev = cg->rho;
-        if (!(sigma > T(0))) {
-            cg->state = ck::BREAKDOWN;
-            cg->go = 0;
-        } else {
-            cg->alpha = cg->rho / sigma;
-            cg->go = 1;
-        }
-    }
+    if (threadIdx.x == 0)
+        ck::cg_store_sigma(cg, cg->rho, sigma);
 }
 
 // r -= alpha q; partials of r.r (x is updated with p in cg_rho_update_xp,
 // which reads p anyway).  FOLD: the sigma finish happens here: every block
 // sums the Gs sigma partials in the same order and forms alpha = rho / sigma
-// itself, and block 0 alone stores the scalars (no block reads a field that
-// block 0 stores, but `state`, and a block that finds it changed to BREAKDOWN
-// only leaves a little earlier).  The sum takes about 1.3 us of every block; the
-// finish kernel took 4.2 us and the gap of one more launch.
+// itself, and block 0 alone stores the scalars, none of which another block
+// reads.  After a breakdown r is left as it was.  The sum takes about 1.3 us of
+// every block; the finish kernel took 4.2 us and the gap of one more launch.
 template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void cg_update_r(int64_t n, int64_t G, T *__restrict__ r,
                                                    const T *__restrict__ q,
@@ -184,38 +174,34 @@ __global__ __launch_bounds__(256) void cg_update_r(int64_t n, int64_t G, T *__re
                                                    CgDev<T> *cg) {
     __shared__ T lds[4];
     __shared__ T alpha_s;
-    if (cg->state != ck::RUN) {
+    __shared__ int ok_s;
+    if (cg->state != ck::RUN) {   // not stored here: every wave reads the same
         if (FOLD && blockIdx.x == 0 && threadIdx.x == 0)
             cg->go = 0;
         return;
     }
     T alpha;
+    bool ok;
     if constexpr (FOLD) {
         const T rho = cg->rho;
         const T sigma = ck::sum_partials(sigma_partials, Gs, lds);
         if (threadIdx.x == 0) {
-            const bool ok = sigma > T(0);
-            const T a = ok ? rho / sigma : T(0);
-            alpha_s = a;
-            if (blockIdx.x == 0) {
-                cg->sigma = sigma;
-                cg->rho_prev = rho;
-                cg->go = ok;
-                if (ok)
-                    cg->alpha = a;
-                else
-                    cg->state = ck::BREAKDOWN;
-            }
+            alpha_s = rho / sigma;
+            ok_s = sigma > T(0);
+            if (blockIdx.x == 0)
+                ck::cg_store_sigma(cg, rho, sigma);
         }
         __syncthreads();
         alpha = alpha_s;
+        ok = ok_s;
     } else {
         alpha = cg->alpha;
+        ok = cg->go;
     }
-    const int64_t b = blockIdx.x;
+    const int64_t b = blockIdx.x, rows = ok ? n : 0;
     T s = 0, rv[kVecUnroll], qv[kVecUnroll];
     batched(
-        n, b, G,
+        rows, b, G,
         [&](int u, int64_t i) {
             rv[u] = r[i];
             qv[u] = q[i];
@@ -238,7 +224,7 @@ __global__ __launch_bounds__(256) void cg_update_r(int64_t n, int64_t G, T *__re
 // converged, sets p = r + beta p there.  Block 0 alone stores the scalars.
 // No block reads a field that block 0 stores: `go`, rho_prev and alpha were
 // set by the sigma finish.  Block 0 reports the iteration's outcome to the
-// host, also when the solve had stopped before it.
+// host, also when the solve had stopped before it, and records a breakdown.
 template <typename T>
 __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
                                                         const T *__restrict__ partials,
@@ -250,8 +236,10 @@ __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
     __shared__ T beta_s;
     __shared__ int run_s;
     if (!cg->go) {
-        if (blockIdx.x == 0 && threadIdx.x == 0)
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ck::cg_store_no_step(cg);
             ck::report(progress, cg->relres, seq, ck::kReportDone);
+        }
         return;
     }
     const T alpha = cg->alpha;
