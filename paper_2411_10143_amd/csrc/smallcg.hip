@@ -13,8 +13,7 @@
 // a scratch buffer, so that each product reads it in whole cache lines (the
 // row-major arrays, read one entry per lane per step, re-fetched partly used
 // lines at every step).  The product sums each row with one lane in
-// ascending entry order; the loads of all R rows' next entries are issued
-// together.  Dot products reduce in a fixed
+// ascending entry order, many entries' loads issued together.  Dot products reduce in a fixed
 // order (wave butterfly, then the wave sums by halves), so the result is
 // deterministic.
 //
@@ -89,31 +88,51 @@ struct StopTest {
     }
 };
 
-// q[u] = (A v)[row u of this thread], v in LDS.  (Issuing step t + 1's loads
-// before step t's gathers measured 6 % slower here.)
+// q += entries k .. k + E - 1 (to `last` at most) of a row times v, in their order.
+template <int E>
+__device__ __forceinline__ void wg_row(int k, int last, const int *__restrict__ col,
+                                       const double *__restrict__ val, const double *v,
+                                       double &q) {
+    int cc[E];
+    double vv[E], g[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int kk = min(k + e, last);
+        cc[e] = col[kk];
+        vv[e] = val[kk];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        g[e] = v[cc[e]];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (k + e <= last)
+            q += vv[e] * g[e];
+}
+
+// q[u] = (A v)[row u of this thread], v in LDS.  One row after the other, its next
+// sixteen entries in flight together: they share cache lines, and a lane with a long
+// row does not take its other rows through as many steps.  Stepping all rows together,
+// an entry each, took (us per iteration, 1024 threads of at most 4 rows; 512 of at most
+// 8; now): n = 4,000, rows of 17 on average 51.6, 53.8, 34.5; of 51 181, 185, 91; one
+// row of 4,000 863, 1,373, 112; power-law rows up to 1,407 543, 635, 188.  Thirty-two
+// entries at a time gain more on long rows (one of 4,000: 81) but leave rows of 17 no
+// faster than they were (49).
 template <int R>
-__device__ __forceinline__ void wg_matvec(const int (&kb)[R], const int (&ke)[R], int trips,
+__device__ __forceinline__ void wg_matvec(const int (&kb)[R], const int (&ke)[R],
                                           const int *__restrict__ col,
                                           const double *__restrict__ val, const double *v,
                                           double (&q)[R]) {
 #pragma unroll
-    for (int u = 0; u < R; ++u)
+    for (int u = 0; u < R; ++u) {
         q[u] = 0;
-    for (int t = 0; t < trips; ++t) {
-        int cc[R];
-        double vv[R];
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int k = kb[u] + t;
-            const int kk = k < ke[u] ? k : 0;   // entry 0 exists when trips > 0
-            cc[u] = col[kk];
-            vv[u] = val[kk];
-        }
-        __builtin_amdgcn_sched_barrier(0);   // every row's loads in flight together
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (kb[u] + t < ke[u])
-                q[u] += vv[u] * v[cc[u]];
+        int k = kb[u];
+        for (; k + 8 < ke[u]; k += 16)
+            wg_row<16>(k, ke[u] - 1, col, val, v, q[u]);
+        for (; k < ke[u]; k += 8)
+            wg_row<8>(k, ke[u] - 1, col, val, v, q[u]);
     }
 }
 
@@ -246,7 +265,7 @@ __device__ __forceinline__ void wg_matvec_centre(const unsigned (&rcp)[kWgRegPai
 enum { kWgRows = 0, kWgColMajor = 1, kWgReg = 2, kWgCentre = 3 };
 template <int T, int R, int MODE>
 __device__ __forceinline__ void cg_wg_run(int n, const int (&kb)[R], const int (&ke)[R],
-                                          const int (&len)[R], int trips, int K,
+                                          const int (&len)[R], int K,
                                           double (&xr)[R], double bb,
                                           const int *__restrict__ col,
                                           const double *__restrict__ val,
@@ -299,7 +318,7 @@ __device__ __forceinline__ void cg_wg_run(int n, const int (&kb)[R], const int (
         else if constexpr (cm)
             wg_matvec_cm<T, R>(len, K, ccol, cval, v, q);
         else
-            wg_matvec<R>(kb, ke, trips, col, val, v, q);
+            wg_matvec<R>(kb, ke, col, val, v, q);
     };
     if constexpr (cm) {
         for (int s = 0; s < K; s += 2) {
@@ -433,7 +452,7 @@ __device__ __forceinline__ void cg_wg_run(int n, const int (&kb)[R], const int (
     }
 }
 
-// ccol / cval: scratch of kWgCgColMajorK / 2 * R * 1024 pairs for the
+// ccol / cval: scratch of kWgCgColMajorK / 2 * T * R pairs for the
 // column-major copy, used when no row has more than kWgCgColMajorK entries.
 template <int T, int R>
 __global__ __launch_bounds__(T) void cg_wg(int n, const int *__restrict__ rp,
@@ -489,16 +508,16 @@ __global__ __launch_bounds__(T) void cg_wg(int n, const int *__restrict__ rp,
         apart = __syncthreads_and(apart) != 0;
     }
     if (apart)
-        cg_wg_run<T, R, kWgCentre>(n, kb, ke, len, trips, K, xr, bb, col, val, b, x, tol, max_iter,
+        cg_wg_run<T, R, kWgCentre>(n, kb, ke, len, K, xr, bb, col, val, b, x, tol, max_iter,
                                    ccol, cval, out, v, red, parity);
     else if (K <= kWgCgRegK)
-        cg_wg_run<T, R, kWgReg>(n, kb, ke, len, trips, K, xr, bb, col, val, b, x, tol, max_iter,
+        cg_wg_run<T, R, kWgReg>(n, kb, ke, len, K, xr, bb, col, val, b, x, tol, max_iter,
                              ccol, cval, out, v, red, parity);
     else if (K <= ck::kWgCgColMajorK)
-        cg_wg_run<T, R, kWgColMajor>(n, kb, ke, len, trips, K, xr, bb, col, val, b, x, tol,
+        cg_wg_run<T, R, kWgColMajor>(n, kb, ke, len, K, xr, bb, col, val, b, x, tol,
                                   max_iter, ccol, cval, out, v, red, parity);
     else
-        cg_wg_run<T, R, kWgRows>(n, kb, ke, len, trips, K, xr, bb, col, val, b, x, tol, max_iter,
+        cg_wg_run<T, R, kWgRows>(n, kb, ke, len, K, xr, bb, col, val, b, x, tol, max_iter,
                               ccol, cval, out, v, red, parity);
 }
 
