@@ -342,7 +342,13 @@ ck_status spmv_apply_f32(ck_handle h, const ck_config *cfg, float alpha, const f
  * product takes one lane per row (final_config reports CSR-vector with 1
  * lane; known_start does not change this path); other systems of at most
  * 8192 rows (FP64 6144) with a CSR-vector configuration and no async run on
- * the request loop's batched kernel. */
+ * the request loop's batched kernel where their entries and longest row are
+ * few enough for one workgroup.  There a configuration given by use_config,
+ * chosen by known_start or predicted (CK_EXEC_SEQUENTIAL) runs in every
+ * product; the default one runs in the FP64 residuals, and the inner products
+ * may take one lane per row instead, from a copy of the matrix that the handle
+ * keeps (6 bytes an entry, FP64 10, and at most 64 times that for the longest
+ * row). */
 ck_status cg_solve(ck_handle h, const double *d_b, double *d_x, const ck_solve_opts *opts,
                    ck_solve_result *res, hipStream_t s);
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "krylov.hpp"
+#include "slotrule.hpp"
 
 namespace ck {
 
@@ -45,7 +46,7 @@ struct BSlot {
     double bnorm, tol;
     int max_iter, inner_cap;
     int keep_x0;          // 1: start from the x given; 0: start from x = 0
-    int pad0;
+    int inner_lanes;      // lanes per row of the inner products, 1 with a slot copy
     // state
     int phase, status, iter, outer, inner_iter, j, launches, pad;
     double beta, relres, inner_tol, rho;
@@ -80,6 +81,7 @@ int64_t bslot_work_elems(int kind, int64_t n, int m);
 // max_n = the most rows of a listed slot; slots of at most narrow_n rows run on
 // 256 threads, the others on 1024.  `stat` and `active` may be pinned host memory.
 constexpr int kNarrowN = 1024;   // the request loop's narrow_n
+constexpr int kNarrowThreads = 256, kWideThreads = 1024;
 ck_status launch_batched_chunk(BSlot *slots, BStat *stat, const int *active, int nactive,
                                int budget, bool fp32, hipStream_t s, int64_t max_n,
                                int narrow_n);

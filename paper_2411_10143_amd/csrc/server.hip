@@ -240,6 +240,19 @@ bool make_room(ck_server &S, const MatEntry *keep, int64_t need) {
     return true;
 }
 
+int lanes_for(const MatEntry &e) {
+    if (e.run_cfg.format == CK_FMT_CSR && e.run_cfg.algorithm == CK_ALG_VECTOR &&
+        e.run_cfg.lanes >= 1)
+        return e.run_cfg.lanes;
+    return default_config(e.n, e.nnz).lanes;
+}
+
+// Whether the inner products of a resident matrix's slots take one lane per row.
+bool one_lane_for(const MatEntry &e, bool fp32) {
+    return slot_one_lane(e.n, e.nnz, e.h->max_row, lanes_for(e),
+                         e.n <= kNarrowN ? kNarrowThreads : kWideThreads, fp32);
+}
+
 // Makes the matrix resident (evicting idle ones if needed) and fills its
 // prediction cache; the cascade's configuration runs only if its converted
 // copy fits the budget too (else the default configuration).  CK_E_NOMEM:
@@ -278,7 +291,7 @@ ck_status ensure_resident(ck_server &S, MatEntry &e) {
         S.st.prediction_cache_hits += 1;
     }
     e.run_cfg = e.cfg;
-    if (e.n <= S.o.small_n && e.n <= kSlotRows) {
+    if (e.n <= S.o.small_n && e.n <= kSlotRows && one_lane_for(e, fp32)) {
         // the slots' copy of the matrix, where it fits beside a request's
         // workspace without evicting anything (its products give the bits of
         // the CSR arrays, so a slot's result does not depend on it)
@@ -299,13 +312,6 @@ ck_status ensure_resident(ck_server &S, MatEntry &e) {
         S.bytes_in_use += e.bytes;
     }
     return CK_OK;
-}
-
-int lanes_for(const MatEntry &e) {
-    if (e.run_cfg.format == CK_FMT_CSR && e.run_cfg.algorithm == CK_ALG_VECTOR &&
-        e.run_cfg.lanes >= 1)
-        return e.run_cfg.lanes;
-    return default_config(e.n, e.nnz).lanes;
 }
 
 // A request that does not fit: it waits while in-flight work holds memory
@@ -384,6 +390,7 @@ Admit admit_one(ck_server &S, Request *r) {
     b.col = e.h->col;
     b.val64 = e.h->val;
     b.val32 = e.h->val32;
+    b.inner_lanes = one_lane_for(e, fp32) ? 1 : b.lanes;
     if (e.h->has_slot[fp32].load())
         b.sell = slot_copy_at(e.h->slot_mem[fp32], e.n, e.nnz, e.h->max_row, fp32 ? 4 : 8);
     b.b = r->b;

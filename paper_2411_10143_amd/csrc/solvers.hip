@@ -781,13 +781,13 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
 
 enum class Solver { CG, GMRES };
 
-// CG systems of at most this many rows run in one workgroup (FP64 ones of at most
-// kWgCgMaxN in a kernel of their own).  Per iteration, one workgroup against the
-// multi-workgroup kernels: mixed, 2D Laplacian, n = 1,024 3.7 us, 10.7; n = 8,100 9.5,
-// 12.3; FP64 n = 6,400 11.2, 12.3; n = 8,100 13.0, 12.4; 3D n = 8,000 15.4, 13.7; past
-// kSlotRows a workgroup's vectors leave LDS.  GMRES never does: its steps are three
-// launches of about 20 us together (FP64 24) up to n = 20,000, and one workgroup takes
-// 19.7 (29) at n = 250, 31 (55) at n = 4,096, 51 (97) at n = 8,192 and 169 (243) at 8,193.
+// CG systems of more rows than this never run in one workgroup: past kSlotRows the
+// vectors leave its LDS, and in FP64 the multi-workgroup kernels overtake it even on
+// rows of two or three entries (n = 6,144 9.0 us an iteration against 12.6, n = 8,100
+// 13.0 and 12.4; mixed n = 8,192 11.9 and 19.8).  Below, entries and the longest row
+// decide (slotrule.hpp).  GMRES never runs in one: its steps are three launches of 15
+// to 19 us together (FP64 18 to 23) at 8 to 2,000 rows, where one workgroup took 20 to
+// 52 (26 to 75).
 constexpr int64_t kSmallMixed = kSlotRows, kSmallFp64 = 6144;
 
 // FP64 CG of a system of at most kWgCgMaxN rows in one single-workgroup launch
@@ -816,7 +816,9 @@ ck_status wg_cg_solve(SolveCtx &c, const double *b, double *x) {
                 h.relres);
 }
 
-ck_status small_solve(SolveCtx &c, const double *b, double *x) {
+// A CG solve on the request loop's kernel; one_lane: its inner products take one lane
+// per row, else the configuration's.
+ck_status small_solve(SolveCtx &c, const double *b, double *x, bool one_lane) {
     ck_matrix &M = c.M;
     const bool fp32 = c.o.precision == CK_PREC_MIXED;
     const int64_t ld = ceil_div(M.n, 64) * 64;
@@ -831,9 +833,12 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x) {
     CK_TRY(ws.get(&active, 1));
     CK_TRY(ws.get(&work, bslot_work_elems(B_CG, M.n, 0) * (fp32 ? 4 : 8)));
     CK_TRY(ws.get(&r64, ld));
-    CK_TRY(build_slot_copy(M, fp32, c.s));
+    if (one_lane)
+        CK_TRY(build_slot_copy(M, fp32, c.s));
     BSlot *h = (BSlot *)std::calloc(1, sizeof(BSlot));
-    h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
+    h->inner_lanes = one_lane ? 1 : c.cfg.lanes;
+    if (one_lane)
+        h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
     h->kind = B_CG;
     h->n = (int)M.n;
     h->lanes = c.cfg.lanes;
@@ -952,7 +957,6 @@ ck_status solve(ck_handle hnd, const double *b, double *x, const ck_solve_opts *
     const bool run_async = opts->async == CK_EXEC_ASYNC && !opts->use_config;
     if (opts->async == CK_EXEC_SEQUENTIAL && !opts->use_config)
         CK_TRY(sequential_predict(c));
-    const int m = opts->restart > 0 ? opts->restart : 30;
     if (M.n <= kWgCgMaxN && which == Solver::CG && opts->precision == CK_PREC_FP64 &&
         opts->async == CK_EXEC_DEFAULT && !opts->use_config) {
         // the whole solve in one single-workgroup launch; its product takes
@@ -964,9 +968,17 @@ ck_status solve(ck_handle hnd, const double *b, double *x, const ck_solve_opts *
         return st;
     }
     const bool vector_cfg = c.cfg.format == CK_FMT_CSR && c.cfg.algorithm == CK_ALG_VECTOR;
-    const int64_t small = opts->precision == CK_PREC_FP64 ? kSmallFp64 : kSmallMixed;
-    if (M.n <= small && !run_async && vector_cfg && which == Solver::CG) {
-        const ck_status st = small_solve(c, b, x);
+    const bool fp32 = opts->precision == CK_PREC_MIXED;
+    // a configuration that the caller or the cascade has chosen is the one that runs
+    const bool one_lane =
+        vector_cfg && (c.cfg.lanes == 1 ||
+                       (!opts->use_config && !opts->known_start &&
+                        opts->async == CK_EXEC_DEFAULT &&
+                        slot_one_lane(M.n, M.nnz, M.max_row, c.cfg.lanes, kWideThreads, fp32)));
+    if (which == Solver::CG && vector_cfg && !run_async &&
+        M.n <= (fp32 ? kSmallMixed : kSmallFp64) &&
+        cg_in_one_workgroup(M.n, M.nnz, M.max_row, c.cfg.lanes, one_lane, kWideThreads, fp32)) {
+        const ck_status st = small_solve(c, b, x, one_lane);
         res->final_config = c.cfg;
         res->status = st;
         res->t_total_us = us_since(t0);
