@@ -833,11 +833,11 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool one_lane) {
     CK_TRY(ws.get(&active, 1));
     CK_TRY(ws.get(&work, bslot_work_elems(B_CG, M.n, 0) * (fp32 ? 4 : 8)));
     CK_TRY(ws.get(&r64, ld));
-    if (one_lane)
-        CK_TRY(build_slot_copy(M, fp32, c.s));
+    // the copy is an option: without it the CSR arrays give the same bits
+    const bool copy = one_lane && build_slot_copy(M, fp32, c.s) == CK_OK;
     BSlot *h = (BSlot *)std::calloc(1, sizeof(BSlot));
     h->inner_lanes = one_lane ? 1 : c.cfg.lanes;
-    if (one_lane)
+    if (copy)
         h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
     h->kind = B_CG;
     h->n = (int)M.n;
