@@ -425,6 +425,24 @@ int lanes_for_mean(int64_t total, int64_t rows) {
 
 }  // namespace
 
+// convert_to_dia's scratch: a representative value, a flag and a position for each
+// of the N offsets, the scan's, one flag more, and (a block of its own) a row mask
+static int64_t dia_tmp_bytes(int64_t N) {
+    return 8 * N + 4 * (2 * N + 1 + panel_scan_tmp_elems(N) + 1);
+}
+static int64_t hyb_tmp_bytes(int64_t n) { return 4 * (2 * n + 1 + panel_scan_tmp_elems(n)); }
+
+int64_t dia_convert_bytes(int64_t n, int64_t ncols, int64_t ndiag, int value_bytes) {
+    const int64_t pitch = ceil_div(n, 64) * 64;
+    return dia_tmp_bytes(n + ncols - 1) + 4 * n + 4 * ndiag + ndiag * pitch * value_bytes;
+}
+
+// K <= 3 nnz / n (convert_to_hyb), and no more long rows than rows
+int64_t hyb_convert_bytes(int64_t n, int64_t nnz, int value_bytes) {
+    const int64_t pitch = ceil_div(n, 64) * 64, K = n > 0 ? 3 * nnz / n : 0;
+    return K * pitch * (4 + value_bytes) + 4 * n + hyb_tmp_bytes(n);
+}
+
 ck_status convert_to_dia(ck_matrix &M, hipStream_t s) {
     const int64_t n = M.n, pitch = ceil_div(n, 64) * 64;
     int64_t nd = 0;
@@ -434,8 +452,7 @@ ck_status convert_to_dia(ck_matrix &M, hipStream_t s) {
     double *rep = nullptr;
     const int64_t N = n + M.ncols - 1;   // offsets -(n-1) .. ncols-1
     if (n > 0 && M.nnz > 0) {
-        const int64_t ints = 2 * N + 1 + panel_scan_tmp_elems(N);
-        CK_TRY(tmp.get((size_t)(8 * N + (ints + 1) * (int64_t)sizeof(int))));
+        CK_TRY(tmp.get((size_t)dia_tmp_bytes(N)));
         CK_TRY(mask.get((size_t)(4 * n)));
         rep = (double *)tmp.p;
         flags = (int *)(rep + N);
@@ -557,8 +574,7 @@ ck_status convert_to_hyb(ck_matrix &M, hipStream_t s) {
     CK_TRY(launch_to_ell(M, K, pitch, M.hyb_col, M.hyb_val, M.hyb_val32, s));
     if (nt > 0) {
         Tmp tmp(M, s);
-        const int64_t scan_tmp = panel_scan_tmp_elems(n);
-        CK_TRY(tmp.get((size_t)(2 * n + 1 + scan_tmp) * sizeof(int)));
+        CK_TRY(tmp.get((size_t)hyb_tmp_bytes(n)));
         int *flag = (int *)tmp.p, *pos = flag + n;
         hipLaunchKernelGGL(hyb_long_flags, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, (int)K,
                            M.rp, flag);

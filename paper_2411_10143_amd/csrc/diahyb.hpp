@@ -9,6 +9,10 @@ namespace ck {
 // Enqueued on s; both block on s once to read a count back.
 ck_status convert_to_dia(ck_matrix &M, hipStream_t s);
 ck_status convert_to_hyb(ck_matrix &M, hipStream_t s);
+// Device memory the conversions hold at most, their scratch included, for values
+// of value_bytes (the FP32 copy counted).
+int64_t dia_convert_bytes(int64_t n, int64_t ncols, int64_t ndiag, int value_bytes);
+int64_t hyb_convert_bytes(int64_t n, int64_t nnz, int value_bytes);
 
 // Bytes a row's diagonal mask takes in the constant form.
 inline int64_t dia_mask_bytes(int64_t nd) { return nd <= 8 ? 1 : 4; }

@@ -502,6 +502,19 @@ int64_t panel_tmp_ints(int64_t N) {
     return N + std::max<int64_t>(kSpread * kSpreadInts, panel_scan_tmp_elems(N));
 }
 
+int64_t panel_convert_bytes(int64_t n, int64_t ncols, int64_t nnz, int value_bytes) {
+    const int64_t P = panel_count_for(ncols, 8), N = P * n;
+    const int64_t all = nnz * (4 + value_bytes) + 4 * panel_tmp_ints(N);
+    // dense panel rows: their pointers and the plan
+    const int64_t dense = 4 * (N + 1) + 4 * merge_plan_ints(N, nnz);
+    // row list: its arrays beside the dense pointers and the scan (panel_make_rows),
+    // then beside the plan alone
+    const int64_t NE = std::min(3 * N / 4, nnz);
+    const int64_t list = 4 * NE + 4 * (NE + 1) + 4 * P * (ceil_div(n, 256) + 1);
+    const int64_t make = 4 * (N + 1) + 4 * (N + 1 + panel_scan_tmp_elems(N));
+    return all + std::max(dense, list + std::max(make, 4 * merge_plan_ints(NE, nnz)));
+}
+
 int64_t panel_scan_tmp_elems(int64_t N) {
     const int64_t b1 = ceil_div(N + 1, 2048);
     const int64_t b2 = ceil_div(b1, 2048);

@@ -10,6 +10,9 @@ namespace ck {
 int panel_count_for(int64_t ncols, int value_bytes);
 int64_t panel_scan_tmp_elems(int64_t N);
 int64_t panel_tmp_ints(int64_t N);   // N counts, then their counters or the scan's scratch
+// Device memory a conversion to panels holds at most, its scratch included, for
+// values of value_bytes (the FP32 copy counted).
+int64_t panel_convert_bytes(int64_t n, int64_t ncols, int64_t nnz, int value_bytes);
 // The panel count of M's CSR-panel copy: panel_count_for(ncols, 8), or 4
 // (see panel.hip).  tmp: panel_tmp_ints(panel_count_for(
 // ncols, 8) * n) ints of scratch; on return tmp[0 .. P n) holds the chosen P's per-row panel counts,

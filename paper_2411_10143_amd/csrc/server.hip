@@ -149,28 +149,26 @@ int64_t csr_bytes(const ck_server &S, const MatEntry &e) {
     return 4 * (e.n + 1) + (S.o.precision == CK_PREC_MIXED ? 16 : 12) * e.nnz;
 }
 
-// Bytes a conversion to c adds to the handle (upper estimates from the
-// features; 0 for a configuration that needs no copy or is refused), plus
-// the conversion's own temporaries.
-int64_t converted_bytes(const ck_features &F, const ck_config &c, bool fp32) {
+// Bytes a conversion of M to c holds at most, its temporaries included (also
+// those of a conversion that counts the diagonals and is then refused).
+int64_t converted_bytes(const ck_matrix &M, const ck_features &F, const ck_config &c, bool fp32) {
     const int64_t n = F.nrows, nnz = F.nnz;
     const int64_t pitch = ceil_div(std::max<int64_t>(n, 1), 64) * 64;
-    const int64_t vb = fp32 ? 12 : 8;          // value bytes per slot (FP64 + FP32 copy)
-    const int64_t tmp = 8 * (n + F.ncols) + 4096;
+    const int vb = fp32 ? 12 : 8;          // value bytes per slot (FP64 + FP32 copy)
     if (c.format == CK_FMT_ELL)
-        return F.max_r * pitch > 8 * nnz ? 0 : F.max_r * pitch * (4 + vb) + tmp;
+        return F.max_r * pitch > 8 * nnz ? 0 : F.max_r * pitch * (4 + vb);
     if (c.format == CK_FMT_COO)
-        return 4 * nnz + tmp;
+        return 4 * nnz;
     if (c.format == CK_FMT_DIA)
-        return F.ndiag * pitch > 8 * nnz ? 0 : F.ndiag * pitch * vb + 4 * F.ndiag + tmp;
-    if (c.format == CK_FMT_HYB)   // width K <= 3 nnz / n
-        return (3 * nnz + pitch) * (4 + vb) + 4 * n + tmp;
+        return dia_convert_bytes(n, F.ncols, F.ndiag * pitch > 8 * nnz ? 0 : F.ndiag, vb);
+    if (c.format == CK_FMT_HYB)
+        return hyb_convert_bytes(n, nnz, vb);
     if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_PANEL) {
-        const int64_t P = panel_count_for(F.ncols, 8);
-        return 4 * (P * n + 1) + nnz * (4 + vb) + 8 * (P * n + 1) + tmp;
+        const int P = slices_of(n, F.ncols, nnz, M.max_row, M.span);
+        return P > 0 ? slices_bytes(n, nnz, P, fp32) : panel_convert_bytes(n, F.ncols, nnz, vb);
     }
     if (c.format == CK_FMT_CSR && c.algorithm == CK_ALG_MERGE)
-        return 4 * merge_plan_ints(n, nnz) + tmp;
+        return 4 * merge_plan_ints(n, nnz);
     return 0;
 }
 
@@ -280,7 +278,7 @@ ck_status ensure_resident(ck_server &S, MatEntry &e) {
             e.symmetric = F.is_symmetric != 0;
             if (spmv_select(&F, nullptr, &e.cfg) != CK_OK)
                 e.cfg = default_config(e.n, e.nnz);
-            e.conv_bytes = converted_bytes(F, e.cfg, fp32);
+            e.conv_bytes = converted_bytes(*e.h, F, e.cfg, fp32);
         } else {   // no features: the default kernel, and GMRES (no symmetry known)
             e.symmetric = false;
             e.cfg = default_config(e.n, e.nnz);
