@@ -404,7 +404,7 @@ ck_status ck_export_coo_rows(ck_handle h, int32_t *d_row, hipStream_t s);
  * of FP64 x per panel, or 4 when x fits four slices of 2.5 MB, the longest
  * row is at most 4x ceil(nnz/nrows) and more than 3/4 of the 4*nrows panel
  * rows hold entries.  A copy by slices of x (see spmv_convert) is cut finer;
- * its panels are counted by this call.  CK_E_INVALID without a CSR-panel copy. */
+ * these are the panels it takes the place of.  CK_E_INVALID without a CSR-panel copy. */
 ck_status ck_panel_layout(ck_handle h, int32_t *panels, int64_t *width, int64_t *stored_rows);
 
 /* ck_dot -- deterministic two-stage FP64 dot product of two device vectors

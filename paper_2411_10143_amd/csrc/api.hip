@@ -302,22 +302,6 @@ static bool readable(const T *p, int64_t count, int device) {
            (uintptr_t)p % sizeof(T) == 0 && at <= size && (size - at) / sizeof(T) >= (size_t)count;
 }
 
-// The panels that M's entries would make (CSR-panel's rule), counted on the null stream.
-static ck_status panel_shape(ck_matrix &M, int32_t *panels, int64_t *width, int64_t *rows) {
-    int *tmp = nullptr;
-    int P = 0;
-    int64_t filled = 0;
-    CK_TRY(mat_alloc(M, &tmp, panel_tmp_ints((int64_t)panel_count_for(M.ncols, 8) * M.n), nullptr));
-    const ck_status st = panel_choose_count(M, tmp, nullptr, &P, &filled);
-    (void)hipStreamSynchronize(nullptr);
-    mat_free(M, tmp);
-    CK_TRY(st);
-    *panels = P;
-    *width = ceil_div(std::max<int64_t>(M.ncols, 1), P);
-    *rows = 4 * filled > 3 * (P * M.n) ? P * M.n : filled;
-    return CK_OK;
-}
-
 extern "C" {
 
 const char *ck_last_error(void) { return g_last_error.c_str(); }
@@ -760,8 +744,6 @@ ck_status ck_panel_layout(ck_handle h, int32_t *panels, int64_t *width, int64_t 
         return fail(CK_E_INVALID, "NULL argument");
     if (!h->has_panel.load())
         return fail(CK_E_INVALID, "matrix has no CSR-panel copy");
-    if (h->slice_val != nullptr)   // cut finer than its panels, which are counted here
-        return panel_shape(*h, panels, width, stored_rows);
     *panels = h->panel_P;
     *width = h->panel_W;
     *stored_rows = h->panel_rows;

@@ -479,6 +479,23 @@ static ck_status count_panels(const ck_matrix &M, int P, int64_t W, int *cnt, in
     return CK_OK;
 }
 
+// Whether four panels are tried, and whether `filled` of `rows` panel rows make them dense.
+static bool may_take_four(const ck_matrix &M) {
+    return panel_count_for(M.ncols, 8) == 8 && M.ncols * 8 <= 4 * kSliceP4 &&
+           M.max_row <= 4 * ceil_div(M.nnz, M.n);
+}
+static bool dense_rows(int64_t filled, int64_t rows) { return 4 * filled > 3 * rows; }
+
+bool panel_layout_of(ck_matrix &M, int P, int64_t filled) {
+    const bool dense = dense_rows(filled, P * M.n);
+    if (P == 4 && !(may_take_four(M) && dense))
+        return false;
+    M.panel_P = P;
+    M.panel_W = ceil_div(std::max<int64_t>(M.ncols, 1), P);
+    M.panel_rows = dense ? P * M.n : filled;
+    return true;
+}
+
 ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
                              int64_t *filled) {
     const int P8 = panel_count_for(M.ncols, 8);
@@ -487,10 +504,10 @@ ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P
     *filled = 0;
     if (M.n == 0)
         return CK_OK;
-    if (P8 == 8 && M.ncols * 8 <= 4 * kSliceP4 && M.max_row <= 4 * ceil_div(M.nnz, M.n)) {
+    if (may_take_four(M)) {
         const int64_t W4 = ceil_div(std::max<int64_t>(M.ncols, 1), 4);
         CK_TRY(count_panels(M, 4, W4, tmp, filled, s));
-        if (4 * *filled > 3 * (4 * M.n)) {   // the P = 4 layout would be dense
+        if (dense_rows(*filled, 4 * M.n)) {
             *P_out = 4;
             return CK_OK;
         }
@@ -563,7 +580,7 @@ ck_status launch_to_panel(const ck_matrix &M, int P, int64_t W, int *cnt, int *t
 ck_status panel_make_rows(ck_matrix &M, int *cnt, int64_t filled, hipStream_t s) {
     const int64_t n = M.n, N = (int64_t)M.panel_P * n, NE = filled;
     M.panel_rows = N;
-    if (4 * NE > 3 * N || N == 0)   // dense rows are cheaper
+    if (dense_rows(NE, N) || N == 0)   // dense rows are cheaper
         return CK_OK;
     int *pos = nullptr;
     CK_TRY(mat_alloc(M, &pos, N + 1 + panel_scan_tmp_elems(N), s));

@@ -19,6 +19,9 @@ int64_t panel_convert_bytes(int64_t n, int64_t ncols, int64_t nnz, int value_byt
 // *filled of them nonzero.
 ck_status panel_choose_count(const ck_matrix &M, int *tmp, hipStream_t s, int *P_out,
                              int64_t *filled);
+// Sets M's panel count, width and rows to those a CSR-panel copy in P panels would
+// have, `filled` of whose rows hold entries; false for P = 4 if it would not be made.
+bool panel_layout_of(ck_matrix &M, int P, int64_t filled);
 // Exclusive scan of N ints into N + 1 outputs (out[N] = total); tmp holds
 // panel_scan_tmp_elems(N) ints.
 ck_status launch_scan_exclusive(int64_t N, const int *in, int *out, int *tmp, hipStream_t s);

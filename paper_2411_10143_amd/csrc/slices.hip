@@ -14,7 +14,7 @@
 //
 // Measured (before: merge path, the best there was): n = 180,000 36.8 -> 24.6 us, FP32
 // 34.1 -> 17.0; n = 100,000 22.1 -> 17.6, FP32 20.6 -> 12.7; n = 300,000 57.8 -> 44.4,
-// FP32 53.4 -> 28.7.  The conversion: 54 us, 72 us (n = 180,000), 114 us (300,000).
+// FP32 53.4 -> 28.7.  The conversion (with the panels' count, 11 us): 66 us, 84 us (n = 180,000), 120 us (300,000).
 // Bounds now: the entries (10 bytes, FP32 6) and the partial sums, written and read,
 // 2/3 of it; the rest is the launch of the sum and the first loads' latency.
 // Where every workgroup went through all slices instead, so that no partial sums were
@@ -27,6 +27,8 @@
 // 1.5M: 13.0, 10.9).  Uneven rows leave workgroups waiting for others (power-law n =
 // 100,000: 20.9, 45 us), and rows whose columns lie close together gather from L1.
 #include <algorithm>
+#include <numeric>
+#include <vector>
 
 #include "matrix.hpp"
 #include "panel.hpp"
@@ -73,13 +75,46 @@ __device__ __forceinline__ void visit_rows(int n, int W, const int *__restrict__
     }
 }
 
+// filled[block] = the block's sum of the rows' set bits in `panels`, held by all
+// eight lanes of a row together.
+__device__ __forceinline__ void store_filled(unsigned panels, int *__restrict__ filled) {
+    constexpr int L = kConvThreads / 64;
+    __shared__ int part[kConvThreads / 64];
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1)
+        panels |= __shfl_xor(panels, off, L);
+    const int sum = ck::wave_sum(threadIdx.x % L == 0 ? __popc(panels) : 0);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int w = 0; w < kConvThreads / 64; ++w)
+            t += part[w];
+        filled[blockIdx.x] = t;
+    }
+}
+
+// filled[g] = the rows' panels of group g that hold entries, x cut in eight.
+__global__ __launch_bounds__(kConvThreads) void slices_eight(int n, int W8,
+                                                    const int *__restrict__ rp,
+                                                    const int *__restrict__ col,
+                                                    int *__restrict__ filled) {
+    unsigned panels = 0;
+    visit_rows(n, W8, rp, col, nullptr,
+               [&](int, int, int p, int, double) { panels |= 1u << p; });
+    store_filled(panels, filled);
+}
+
 // ends[s*n + i] = entries in slice s of the rows of i's 64 up to i; total[s*G + g] =
-// of all the rows of group g.  Also the zeros that end the entries' arrays.
-__global__ __launch_bounds__(kConvThreads) void slices_count(int n, int P, int W, int G,
+// of all the rows of group g, filled[g] = their panels that hold entries, x cut in
+// four (of W4 columns).  Also the zeros that end the entries' arrays.
+__global__ __launch_bounds__(kConvThreads) void slices_count(int n, int W4, int P, int W, int G,
                                                     const int *__restrict__ rp,
                                                     const int *__restrict__ col,
                                                     unsigned short *__restrict__ ends,
                                                     int *__restrict__ total,
+                                                    int *__restrict__ filled,
                                                     unsigned short *__restrict__ scol_end,
                                                     double *__restrict__ sval_end,
                                                     float *__restrict__ sval32_end) {
@@ -87,6 +122,8 @@ __global__ __launch_bounds__(kConvThreads) void slices_count(int n, int P, int W
     const int lane = threadIdx.x & 63;
     for (int t = threadIdx.x; t < 64 * (kSlices + 1); t += kConvThreads)
         (&s_cnt[0][0])[t] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        filled[G] = 0;
     if (blockIdx.x == 0 && threadIdx.x < kSlicePass) {
         scol_end[threadIdx.x] = 0;
         sval_end[threadIdx.x] = 0;
@@ -94,9 +131,13 @@ __global__ __launch_bounds__(kConvThreads) void slices_count(int n, int P, int W
             sval32_end[threadIdx.x] = 0;
     }
     __syncthreads();
-    visit_rows(n, W, rp, col, nullptr,
-               [&](int row, int, int s, int, double) { atomicAdd(&s_cnt[row][s], 1); });
-    __syncthreads();
+    unsigned panels = 0;   // of the thread's row
+    visit_rows(n, W, rp, col, nullptr, [&](int row, int, int s, int c, double) {
+        atomicAdd(&s_cnt[row][s], 1);
+        c += s * W;
+        panels |= c < 2 * W4 ? (c < W4 ? 1u : 2u) : (c < 3 * W4 ? 4u : 8u);
+    });
+    store_filled(panels, filled);   // its barrier orders the counts too
     const int64_t i = (int64_t)blockIdx.x * 64 + lane;
     for (int s = threadIdx.x >> 6; s < P; s += kConvThreads / 64) {
         const int scan = ck::wave_scan(s_cnt[lane][s]);
@@ -118,7 +159,15 @@ __global__ __launch_bounds__(kConvThreads) void slices_fill(
     int n, int P, int W, int G, const int *__restrict__ rp, const int *__restrict__ col,
     const double *__restrict__ val, const unsigned short *__restrict__ ends,
     const int *__restrict__ base, unsigned short *__restrict__ scol, double *__restrict__ sval,
-    float *__restrict__ sval32) {
+    float *__restrict__ sval32, int *__restrict__ filled) {
+    if (blockIdx.x == 0) {   // one workgroup adds up the groups' filled panels on the way
+        int sum = 0;
+        for (int g = threadIdx.x; g < G; g += kConvThreads)
+            sum += filled[g];
+        sum = ck::wave_sum(sum);
+        if ((threadIdx.x & 63) == 0)
+            atomicAdd(&filled[G], sum);
+    }
     __shared__ double s_val[kStage];
     __shared__ unsigned short s_col[kStage];
     // destination of the row's entries minus their place in the CSR arrays
@@ -299,9 +348,10 @@ int slices_of(int64_t n, int64_t ncols, int64_t nnz, int64_t max_row, int64_t sp
     return (int)P;
 }
 
-// The slices' arrays in one block, each 256-byte aligned.
+// The slices' arrays in one block, each 256-byte aligned, and the conversion's counts of
+// filled panels: a group's each, and their sum.
 struct SliceMem {
-    int64_t ends, val32, col, base, bytes;   // after the FP64 values
+    int64_t ends, val32, col, base, filled, bytes;   // after the FP64 values
 };
 static SliceMem slice_mem(int64_t n, int64_t nnz, int P, bool fp32) {
     auto up = [](int64_t b) { return ceil_div(b, 256) * 256; };
@@ -311,7 +361,8 @@ static SliceMem slice_mem(int64_t n, int64_t nnz, int P, bool fp32) {
     m.col = m.val32 + (fp32 ? up(4 * entries) : 0);
     m.ends = m.col + up(2 * entries);
     m.base = m.ends + up(2 * P * n);
-    m.bytes = m.base + 4 * (P * ceil_div(n, 64) + 1);
+    m.filled = m.base + up(4 * (P * ceil_div(n, 64) + 1));
+    m.bytes = m.filled + 4 * (ceil_div(n, 64) + 1);
     return m;
 }
 int64_t slices_bytes(int64_t n, int64_t nnz, int P, bool fp32) {
@@ -336,22 +387,38 @@ ck_status build_slices(ck_matrix &M, int P, hipStream_t s) {
     M.slice_ends = (unsigned short *)(mem + m.ends);
     M.slice_base = (int *)(mem + m.base);
     // the groups' totals and the scan's scratch lie where the values come after them
-    int *total = (int *)mem;
+    int *total = (int *)mem, *filled = (int *)(mem + m.filled);
     const int n = (int)M.n, W = (int)slice_width(M, P);
-    hipLaunchKernelGGL(slices_count, dim3(G), dim3(kConvThreads), 0, s, n, P, W, (int)G, M.rp,
-                       M.col, M.slice_ends, total, M.slice_col + M.nnz, M.slice_val + M.nnz,
+    hipLaunchKernelGGL(slices_count, dim3(G), dim3(kConvThreads), 0, s, n,
+                       (int)ceil_div(M.ncols, 4), P, W, (int)G, M.rp, M.col, M.slice_ends, total,
+                       filled, M.slice_col + M.nnz, M.slice_val + M.nnz,
                        M.val32 ? M.slice_val32 + M.nnz : nullptr);
     ck_status st = launch_scan_exclusive(N, total, M.slice_base, total + N, s);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(G), dim3(kConvThreads), 0, s, n, P, W, (int)G, M.rp, M.col,
                            M.val, M.slice_ends, M.slice_base, M.slice_col, M.slice_val,
-                           M.slice_val32);
+                           M.slice_val32, filled);
     };
     if (st == CK_OK)
         M.val32 ? go(slices_fill<true>) : go(slices_fill<false>);
     if (hipGetLastError() != hipSuccess && st == CK_OK)
         st = fail(CK_E_HIP, "conversion to slices failed");
-    return st;
+    CK_TRY(st);
+    // the panels that CSR-panel would make of M, for ck_panel_layout: four where the
+    // rows fill them, else eight, counted only then
+    int four = 0;
+    CK_HIP(hipMemcpyAsync(&four, filled + G, sizeof four, hipMemcpyDeviceToHost, s));
+    CK_HIP(hipStreamSynchronize(s));
+    if (panel_layout_of(M, 4, (unsigned)four))
+        return CK_OK;
+    std::vector<int> eight(G);
+    hipLaunchKernelGGL(slices_eight, dim3(G), dim3(kConvThreads), 0, s, n,
+                       (int)ceil_div(M.ncols, 8), M.rp, M.col, filled);
+    CK_HIP(hipGetLastError());
+    CK_HIP(hipMemcpyAsync(eight.data(), filled, G * sizeof(int), hipMemcpyDeviceToHost, s));
+    CK_HIP(hipStreamSynchronize(s));
+    panel_layout_of(M, 8, std::accumulate(eight.begin(), eight.end(), int64_t(0)));
+    return CK_OK;
 }
 
 void free_slices(ck_matrix &M) {
