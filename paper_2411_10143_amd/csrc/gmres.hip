@@ -270,7 +270,7 @@ __global__ __launch_bounds__(ck::kGmThreads) void gm_pass2(int64_t n, int64_t G,
     // it left.  Reported here, where the store to the host's memory is hidden
     // behind the sweep.
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        ck::report(progress, st->relres, seq,
+        ck::report(progress, st->relres, seq, seq - 1 - (unsigned)st->iter,
                    st->final_state != ck::RUN ? ck::kReportDone
                    : st->halt ? ck::kReportStopped : ck::kReportRun);
     // A halted solve runs no rows (and leaves zero partials, which no later

@@ -5,6 +5,7 @@
 
 #include "cgstate.hpp"
 #include "common.hpp"
+#include "progress.hpp"
 
 namespace ck {
 
@@ -54,19 +55,11 @@ struct GmDev {
 
 constexpr int FULL = 4;         // cycle_stop value: m steps done
 
-// ---- progress reports --------------------------------------------------------
-// One 8-byte word in pinned host memory per solve, stored by one thread of an
-// iteration kernel: the relative residual (float bits, high half), the number
-// of the iteration as the host counts them (24 bits) and its outcome.  The
-// host reads it to stay a few iterations ahead of the device and to stop
-// issuing once the device has stopped; nothing is copied or waited for.
-enum : unsigned { kReportRun = 0, kReportStopped = 1, kReportDone = 2 };
+// One report (progress.hpp).
 __device__ __forceinline__ void report(unsigned long long *word, double relres, unsigned seq,
-                                       unsigned outcome) {
-    const unsigned long long v =
-        ((unsigned long long)__float_as_uint((float)relres) << 32) | ((seq & 0xffffffu) << 8) |
-        outcome;
-    __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                                       unsigned skipped, unsigned outcome) {
+    __hip_atomic_store(word, report_word((float)relres, seq, skipped, outcome), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- two-stage reductions ----------------------------------------------------

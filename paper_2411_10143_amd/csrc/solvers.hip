@@ -76,30 +76,15 @@ struct Pinned {
             CK_HIP(hipHostMalloc((void **)&buf, 4096, hipHostMallocDefault));
         return CK_OK;
     }
-    // the progress word (solvers.hpp), cleared before a run's first kernel
+    // the progress word (progress.hpp), cleared before a run's first kernel
     unsigned long long *progress() { return (unsigned long long *)buf; }
 };
 thread_local Pinned tl_pinned;
 
 // The latest progress report of a run.
-struct Report {
-    unsigned seq = 0, outcome = kReportRun;
-    double relres = 0;
-};
 Report read_report(const unsigned long long *word) {
-    const unsigned long long v = __atomic_load_n(word, __ATOMIC_RELAXED);
-    Report r;
-    const unsigned hi = (unsigned)(v >> 32);
-    float f;
-    std::memcpy(&f, &hi, sizeof f);
-    r.relres = f;
-    r.seq = (unsigned)(v >> 8) & 0xffffffu;
-    r.outcome = (unsigned)v & 0xffu;
-    return r;
+    return unpack_report(__atomic_load_n(word, __ATOMIC_RELAXED));
 }
-
-// a >= b for report numbers, which count modulo 2^24
-bool seq_reached(unsigned a, unsigned b) { return ((a - b) & 0xffffffu) < 0x800000u; }
 
 // Waits for the report of iteration `target` or a later one, of a stop after
 // iteration `since`, or of the run's end.  Every iteration has a kernel that
@@ -526,6 +511,7 @@ ck_status cg_core(SolveCtx &c, T *x, T *r, T *p, T *q, T *partials, CgDev<T> *de
     const int *state_ptr = &dev->state;
     const int iter0 = iter_total, budget = max_iter - iter_total;
     int issued = 0;
+    RunCount count;
     *pin.progress() = 0;   // the last run's kernels have finished
     while (true) {
         c.poll(iter0 + issued);
@@ -549,14 +535,16 @@ ck_status cg_core(SolveCtx &c, T *x, T *r, T *p, T *q, T *partials, CgDev<T> *de
         const int target = issued >= budget ? issued : issued - ahead;
         if (target > 0)
             CK_TRY(wait_report(pin.progress(), target, 0, c.s, &rep));
-        if (c.exec)
-            c.exec->progress(iter0 + (int)rep.seq, rep.relres, tol);
+        if (c.exec && rep.outcome == kReportRun)   // iteration rep.seq has run too
+            c.exec->progress(iter0 + count.before(rep, issued) + 1, rep.relres, tol);
         if (rep.outcome != kReportRun || issued >= budget)
             break;
     }
     CK_HIP(hipMemcpyAsync(pin.buf + 2048, dev, sizeof h, hipMemcpyDeviceToHost, c.s));
     CK_HIP(hipStreamSynchronize(c.s));
     std::memcpy(&h, pin.buf + 2048, sizeof h);
+    if (c.exec)
+        c.exec->progress(h.iter, h.relres, tol);
     iter_total = h.iter;
     state_out = h.state;
     return CK_OK;
@@ -720,6 +708,7 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
     const int ahead = std::min(4, std::max(1, c.o.check_every > 0 ? c.o.check_every : 8));
     int issued = 0;   // counted for the reports: skipped steps count too
     bool ended = false, likely_last = false;
+    RunCount count;
     *pin.progress() = 0;
     ck_status out = CK_OK;
     while (true) {
@@ -748,8 +737,9 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
             Report rep = read_report(pin.progress());
             if (issued - ahead > 0)
                 CK_TRY(wait_report(pin.progress(), issued - ahead, first, c.s, &rep));
-            if (c.exec && sizeof(T) == 8)   // the report precedes its step
-                c.exec->progress((int)rep.seq - 1, rep.relres, c.o.tol);
+            const int ran = count.before(rep, issued);   // the report precedes its step
+            if (c.exec && sizeof(T) == 8)
+                c.exec->progress(ran, rep.relres, c.o.tol);
             ended = rep.outcome == kReportDone;
             likely_last = rep.outcome == kReportStopped && seq_reached(rep.seq, first + 1);
             if (ended || likely_last)

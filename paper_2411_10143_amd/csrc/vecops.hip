@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
     if (!cg->go) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             ck::cg_store_no_step(cg);
-            ck::report(progress, cg->relres, seq, ck::kReportDone);
+            ck::report(progress, cg->relres, seq, 0, ck::kReportDone);
         }
         return;
     }
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void cg_rho_update_xp(int64_t n, int64_t G,
                 cg->state = ck::CONVERGED;
             else if (iter >= cg->max_iter)
                 cg->state = ck::BUDGET;
-            ck::report(progress, relres, seq,
+            ck::report(progress, relres, seq, 0,
                        converged || iter >= cg->max_iter ? ck::kReportDone : ck::kReportRun);
         }
     }
