@@ -356,7 +356,10 @@ ck_status cg_solve(ck_handle h, const double *d_b, double *d_x, const ck_solve_o
  * solver of the paper's evaluation, Section IV).  Each cycle starts from the
  * true residual; Arnoldi uses classical Gram-Schmidt applied twice; the
  * Givens least-squares update runs on the device.  MIXED precision: each
- * FP64 refinement step runs one FP32 GMRES(m) cycle on r/||r||. */
+ * FP64 refinement step runs one FP32 GMRES(m) cycle on r/||r||.  Small systems
+ * in short cycles (m or n at most 16, FP64 6) with a CSR-vector configuration and
+ * no async run in one launch of the request loop's batched kernel where that is
+ * faster, their inner products as those of cg_solve. */
 ck_status gmres_solve(ck_handle h, const double *d_b, double *d_x, const ck_solve_opts *opts,
                       ck_solve_result *res, hipStream_t s);
 

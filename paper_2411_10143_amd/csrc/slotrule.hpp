@@ -1,5 +1,5 @@
 // Which form a small system's inner products take in a one-workgroup solve,
-// and which single CG solves run in one workgroup at all.  Host arithmetic on
+// and which single solves run in one workgroup at all.  Host arithmetic on
 // sizes alone, so that a matrix always takes the same form.
 //
 // A workgroup's product is bound by the instructions it issues, or by its
@@ -54,6 +54,26 @@ inline bool cg_in_one_workgroup(int64_t n, int64_t nnz, int64_t max_row, int lan
                                      : slot_lanes_ns(n, nnz, max_row, lanes, threads, fp32);
     const int64_t steps = (max_row + lanes - 1) / lanes;
     return 4500 + product < (fp32 ? 15500 + 130 * steps : 11500 + 150 * steps);
+}
+
+// The same for GMRES(m) (at most n steps a cycle).  A cycle's start and end take the
+// multi-workgroup kernels a dozen launches, so one workgroup is ahead by about
+// 11,000 / m ns a step in FP64, 12,000 / m + 2,000 in mixed precision, before its
+// products: the inner one and, once a cycle, the FP64 residual's.  Longer cycles lose
+// it in the basis sweeps.  us a step (one workgroup, multi-workgroup, one workgroup
+// before the vectors were on the chip): mixed, 4 rows, m = 30 18.8, 25.2, 21.0; 100 rows of
+// three, m = 1 11.7, 26.7, 20.4, m = 10 11.1, 14.4, 16.1, m = 20 14.8, 15.2, 18.5; 2,000
+// rows of 9, m = 2 21.7, 23.6, 41.3; FP64, 100 rows of three, m = 1 14.4, 26.1, 24.3,
+// m = 5 14.4, 16.4, 19.2, m = 10 17.0, 15.9, 20.2; 4,000 rows of 9, m = 1 64.7, 33.3, 119.
+inline bool gmres_in_one_workgroup(int64_t n, int64_t nnz, int64_t max_row, int m, int lanes,
+                                   bool one_lane, int threads, bool fp32) {
+    const int64_t steps = std::min<int64_t>(m, std::max<int64_t>(n, 1));
+    if (steps > (fp32 ? 16 : 6))
+        return false;
+    const int64_t product = one_lane ? slot_copy_ns(nnz, max_row, fp32)
+                                     : slot_lanes_ns(n, nnz, max_row, lanes, threads, fp32);
+    const int64_t residual = slot_lanes_ns(n, nnz, max_row, lanes, threads, false);
+    return product + residual / steps <= (fp32 ? 12000 / steps + 2000 : 11000 / steps);
 }
 
 }  // namespace ck

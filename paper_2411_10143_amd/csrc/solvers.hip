@@ -775,9 +775,7 @@ enum class Solver { CG, GMRES };
 // vectors leave its LDS, and in FP64 the multi-workgroup kernels overtake it even on
 // rows of two or three entries (n = 6,144 9.0 us an iteration against 12.6, n = 8,100
 // 13.0 and 12.4; mixed n = 8,192 11.9 and 19.8).  Below, entries and the longest row
-// decide (slotrule.hpp).  GMRES never runs in one: its steps are three launches of 15
-// to 19 us together (FP64 18 to 23) at 8 to 2,000 rows, where one workgroup took 20 to
-// 52 (26 to 75).
+// decide (slotrule.hpp).
 constexpr int64_t kSmallMixed = kSlotRows, kSmallFp64 = 6144;
 
 // FP64 CG of a system of at most kWgCgMaxN rows in one single-workgroup launch
@@ -806,9 +804,9 @@ ck_status wg_cg_solve(SolveCtx &c, const double *b, double *x) {
                 h.relres);
 }
 
-// A CG solve on the request loop's kernel; one_lane: its inner products take one lane
-// per row, else the configuration's.
-ck_status small_solve(SolveCtx &c, const double *b, double *x, bool one_lane) {
+// A solve on the request loop's kernel; one_lane: its inner products take one lane per
+// row, else the configuration's.
+ck_status small_solve(SolveCtx &c, const double *b, double *x, int kind, int m, bool one_lane) {
     ck_matrix &M = c.M;
     const bool fp32 = c.o.precision == CK_PREC_MIXED;
     const int64_t ld = ceil_div(M.n, 64) * 64;
@@ -821,7 +819,7 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool one_lane) {
     CK_TRY(ws.get(&slot, 1));
     CK_TRY(ws.get(&stat, 1));
     CK_TRY(ws.get(&active, 1));
-    CK_TRY(ws.get(&work, bslot_work_elems(B_CG, M.n, 0) * (fp32 ? 4 : 8)));
+    CK_TRY(ws.get(&work, bslot_work_elems(kind, M.n, m) * (fp32 ? 4 : 8)));
     CK_TRY(ws.get(&r64, ld));
     // the copy is an option: without it the CSR arrays give the same bits
     const bool copy = one_lane && build_slot_copy(M, fp32, c.s) == CK_OK;
@@ -829,7 +827,8 @@ ck_status small_solve(SolveCtx &c, const double *b, double *x, bool one_lane) {
     h->inner_lanes = one_lane ? 1 : c.cfg.lanes;
     if (copy)
         h->sell = slot_copy_at(M.slot_mem[fp32], M.n, M.nnz, M.max_row, fp32 ? 4 : 8);
-    h->kind = B_CG;
+    h->kind = kind;
+    h->m = m;
     h->n = (int)M.n;
     h->lanes = c.cfg.lanes;
     h->rp = M.rp;
@@ -965,10 +964,19 @@ ck_status solve(ck_handle hnd, const double *b, double *x, const ck_solve_opts *
                        (!opts->use_config && !opts->known_start &&
                         opts->async == CK_EXEC_DEFAULT &&
                         slot_one_lane(M.n, M.nnz, M.max_row, c.cfg.lanes, kWideThreads, fp32)));
-    if (which == Solver::CG && vector_cfg && !run_async &&
-        M.n <= (fp32 ? kSmallMixed : kSmallFp64) &&
-        cg_in_one_workgroup(M.n, M.nnz, M.max_row, c.cfg.lanes, one_lane, kWideThreads, fp32)) {
-        const ck_status st = small_solve(c, b, x, one_lane);
+    const int m = opts->restart > 0 ? opts->restart : 30;
+    const bool small =
+        vector_cfg && !run_async &&
+        (which == Solver::CG
+             ? M.n <= (fp32 ? kSmallMixed : kSmallFp64) &&
+                   cg_in_one_workgroup(M.n, M.nnz, M.max_row, c.cfg.lanes, one_lane, kWideThreads,
+                                       fp32)
+             : M.n <= kSlotRows && m <= kBMaxM &&
+                   gmres_in_one_workgroup(M.n, M.nnz, M.max_row, m, c.cfg.lanes, one_lane,
+                                          kWideThreads, fp32));
+    if (small) {
+        const ck_status st =
+            small_solve(c, b, x, which == Solver::CG ? B_CG : B_GMRES, m, one_lane);
         res->final_config = c.cfg;
         res->status = st;
         res->t_total_us = us_since(t0);

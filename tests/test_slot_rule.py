@@ -15,12 +15,15 @@ DRIVER = r"""
 #include "slotrule.hpp"
 int main() {
     long long n, nnz, max_row;
-    int lanes, threads, fp32;
-    while (scanf("%lld %lld %lld %d %d %d", &n, &nnz, &max_row, &lanes, &threads, &fp32) == 6) {
+    int lanes, threads, fp32, m;
+    while (scanf("%lld %lld %lld %d %d %d %d", &n, &nnz, &max_row, &lanes, &threads, &fp32,
+                 &m) == 7) {
         const bool one = ck::slot_one_lane(n, nnz, max_row, lanes, threads, fp32);
-        printf("%d %d %d\n", one,
-               ck::cg_in_one_workgroup(n, nnz, max_row, lanes, one, threads, fp32),
-               ck::cg_in_one_workgroup(n, nnz, max_row, lanes, lanes == 1, threads, fp32));
+        auto inside = [&](bool o) {   // m = 0: CG
+            return m == 0 ? ck::cg_in_one_workgroup(n, nnz, max_row, lanes, o, threads, fp32)
+                          : ck::gmres_in_one_workgroup(n, nnz, max_row, m, lanes, o, threads, fp32);
+        };
+        printf("%d %d %d\n", one, inside(one), inside(lanes == 1));
     }
     return 0;
 }
@@ -70,7 +73,7 @@ def rule(tmp_path_factory):
 
 
 def test_choices_against_measured_times(rule):
-    got = rule([(n, nnz, mr, L, 1024, fp32) for n, nnz, mr, L, fp32, *_ in MEASURED])
+    got = rule([(n, nnz, mr, L, 1024, fp32, 0) for n, nnz, mr, L, fp32, *_ in MEASURED])
     assert len(got) == len(MEASURED)
     for case, (one, inside, inside_lanes) in zip(MEASURED, got):
         copy, lanes, multi = case[5:]
@@ -80,10 +83,35 @@ def test_choices_against_measured_times(rule):
         assert (lanes if inside_lanes else multi) <= 1.5 * min(lanes, multi), case
 
 
+# n, nnz, longest row, lanes, fp32, m -> us a GMRES step in one workgroup, on the
+# multi-workgroup kernels, and before the vectors were on the chip
+GMRES = [
+    (4, 14, 4, 1, 0, 30, 28.0, 36.1, 26.8), (4, 14, 4, 1, 1, 10, 11.1, 30.4, 15.6),
+    (30, 88, 3, 2, 1, 1, 11.4, 26.1, 20.1), (30, 144, 30, 4, 1, 5, 11.6, 17.0, 16.1),
+    (100, 298, 3, 2, 0, 1, 14.4, 26.1, 24.3), (100, 298, 3, 2, 0, 10, 17.0, 15.9, 20.2),
+    (100, 298, 3, 2, 1, 10, 11.1, 14.4, 16.1), (100, 298, 3, 2, 1, 30, 18.7, 16.3, 21.1),
+    (200, 9010, 60, 32, 1, 1, 20.1, 33.6, 26.5), (200, 9010, 60, 32, 1, 2, 15.0, 22.2, 20.7),
+    (1000, 2998, 3, 2, 1, 2, 11.4, 23.0, 21.4), (1000, 2998, 3, 2, 1, 5, 10.8, 17.8, 18.8),
+    (1000, 8964, 19, 8, 1, 1, 21.8, 29.8, 33.3), (2000, 17964, 20, 8, 0, 2, 27.4, 24.7, 55.4),
+    (2000, 100652, 75, 32, 1, 1, 88.8, 36.3, 144.2), (4000, 35964, 19, 8, 0, 1, 64.7, 33.3, 119.0),
+    (4000, 202776, 75, 32, 1, 10, 48.9, 17.9, 145.1), (400, 1994, 400, 4, 1, 1, 66.2, 46.8, 106.3),
+    (4000, 19994, 4000, 4, 0, 5, 449.9, 175.5, 627.7),
+]
+
+
+def test_gmres_choices(rule):
+    got = rule([(n, nnz, mr, L, 1024, fp32, m) for n, nnz, mr, L, fp32, m, *_ in GMRES])
+    assert len(got) == len(GMRES)
+    for case, (_, inside, _) in zip(GMRES, got):
+        slot, multi, before = case[6:]
+        took = slot if inside else multi
+        assert took <= 1.25 * min(slot, multi) and took <= 1.05 * before, case
+
+
 def test_extremes(rule):
-    got = rule([(8192, 8192 * 8192, 8192, 64, 1024, 0), (1, 1, 1, 1, 1024, 0),
-                (1, 1, 1, 2, 256, 1), (5, 0, 0, 2, 1024, 0),
-                (8000, 39994, 8000, 16, 1024, 0), (8000, 39994, 8000, 64, 1024, 1)])
+    got = rule([(8192, 8192 * 8192, 8192, 64, 1024, 0, 0), (1, 1, 1, 1, 1024, 0, 0),
+                (1, 1, 1, 2, 256, 1, 0), (5, 0, 0, 2, 1024, 0, 0),
+                (8000, 39994, 8000, 16, 1024, 0, 0), (8000, 39994, 8000, 64, 1024, 1, 0)])
     assert got[0][1:] == (0, 0)              # a dense matrix: never in one workgroup
     assert got[1] == (1, 1, 1)
     assert got[2][1:] == (1, 1) and got[3][1:] == (1, 1)
