@@ -57,10 +57,13 @@ __global__ __launch_bounds__(256) void dia_mark(int64_t n, const int *__restrict
     }
 }
 
-// The constant form's row masks, and *varies = 1 if an entry differs (in its
-// bits) from its diagonal's rep or there are more than 32 diagonals; blocks
-// that start after that do nothing.  Eight lanes per row.
-__global__ __launch_bounds__(256) void dia_masks(int64_t n, int64_t N, const int *__restrict__ rp,
+// The constant form's masks of the first `rows` rows, and *varies = 1 if an entry
+// of them differs (in its bits) from its diagonal's rep or there are more than 32
+// diagonals; blocks stop once it is set.  Eight lanes per row, grid-stride: with a
+// block for every 32 rows, ending the blocks of a large matrix whose first rows had
+// settled it took 20 us.
+__global__ __launch_bounds__(256) void dia_masks(int64_t rows, int64_t n, int64_t N,
+                                                 const int *__restrict__ rp,
                                                  const int *__restrict__ col,
                                                  const double *__restrict__ val,
                                                  const int *__restrict__ pos,
@@ -68,36 +71,42 @@ __global__ __launch_bounds__(256) void dia_masks(int64_t n, int64_t N, const int
                                                  void *__restrict__ mask, int *varies) {
     constexpr int L = 8;
     const int lane = threadIdx.x & (L - 1);
-    const int64_t i = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
     const int nd = pos[N];
     if (nd > 32) {
-        if (i == 0 && lane == 0)
+        if (blockIdx.x == 0 && threadIdx.x == 0)
             *varies = 1;
         return;
     }
-    if (__hip_atomic_load(varies, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
-        return;
-    unsigned m = 0;
-    bool differs = false;
-    if (i < n) {
-        const int k1 = rp[i + 1];
-        for (int k = rp[i] + lane; k < k1; k += L) {
-            const int64_t t = (int64_t)col[k] - i + n - 1;
-            m |= 1u << pos[t];
-            differs |= __double_as_longlong(val[k]) != __double_as_longlong(rep[t]);
+    for (int64_t i0 = (int64_t)blockIdx.x * (256 / L); i0 < rows;
+         i0 += (int64_t)gridDim.x * (256 / L)) {
+        if (__hip_atomic_load(varies, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+            return;   // no barrier follows
+        const int64_t i = i0 + threadIdx.x / L;
+        unsigned m = 0;
+        bool differs = false;
+        if (i < rows) {
+            const int k1 = rp[i + 1];
+            for (int k = rp[i] + lane; k < k1; k += L) {
+                const int64_t t = (int64_t)col[k] - i + n - 1;
+                m |= 1u << pos[t];
+                differs |= __double_as_longlong(val[k]) != __double_as_longlong(rep[t]);
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < L; off <<= 1)
+            m |= __shfl_xor(m, off, L);
+        if (i < rows && lane == 0) {
+            if (nd <= 8)
+                ((unsigned char *)mask)[i] = (unsigned char)m;
+            else
+                ((unsigned *)mask)[i] = m;
+        }
+        if (__any(differs)) {
+            if ((threadIdx.x & 63) == 0)
+                __hip_atomic_store(varies, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
         }
     }
-#pragma unroll
-    for (int off = 1; off < L; off <<= 1)
-        m |= __shfl_xor(m, off, L);
-    if (i < n && lane == 0) {
-        if (nd <= 8)
-            ((unsigned char *)mask)[i] = (unsigned char)m;
-        else
-            ((unsigned *)mask)[i] = m;
-    }
-    if (__any(differs) && (threadIdx.x & 63) == 0)
-        atomicOr(varies, 1);
 }
 
 // coef[pos[t]] = rep[t] for every flagged t
@@ -454,24 +463,27 @@ ck_status convert_to_dia(ck_matrix &M, hipStream_t s) {
     if (n > 0 && M.nnz > 0) {
         CK_TRY(tmp.get((size_t)dia_tmp_bytes(N)));
         CK_TRY(mask.get((size_t)(4 * n)));
+        // the count (pos[N]) and `varies` are read back together, `varies` and the flags
+        // cleared together
         rep = (double *)tmp.p;
-        flags = (int *)(rep + N);
-        pos = flags + N;
-        int *varies = pos + N + 1 + panel_scan_tmp_elems(N);
-        CK_TRY(launch_fill<int>(N, flags, 0, s));
-        CK_TRY(launch_fill<int>(1, varies, 0, s));
+        pos = (int *)(rep + N);
+        int *varies = pos + N + 1;
+        flags = varies + 1;
+        int *scan = flags + N;
+        CK_TRY(launch_fill<int>(N + 1, varies, 0, s));
         hipLaunchKernelGGL(dia_mark, dim3(ceil_div(n, 256 / 8)), dim3(256), 0, s, n, M.rp, M.col,
                            M.val, flags, rep);
-        CK_TRY(launch_scan_exclusive(N, flags, pos, pos + N + 1, s));
-        // the first rows alone settle most matrices with varying values: the
-        // blocks of the second launch then end at once
-        for (const int64_t blocks : {(int64_t)1, ceil_div(n, 256 / 8)})
-            hipLaunchKernelGGL(dia_masks, dim3(blocks), dim3(256), 0, s, n, N, M.rp, M.col, M.val,
-                               pos, rep, mask.p, varies);
-        int total = 0, var = 1;
-        CK_HIP(hipMemcpyAsync(&total, pos + N, sizeof total, hipMemcpyDeviceToHost, s));
-        CK_HIP(hipMemcpyAsync(&var, varies, sizeof var, hipMemcpyDeviceToHost, s));
+        CK_TRY(launch_scan_exclusive(N, flags, pos, scan, s));
+        // the first rows alone settle most matrices with varying values: they go first,
+        // and the blocks of the second launch end at once
+        for (const int64_t rows : {std::min<int64_t>(n, 256 / 8), n})
+            hipLaunchKernelGGL(dia_masks, dim3(std::min<int64_t>(ceil_div(rows, 256 / 8), 4096)),
+                               dim3(256), 0, s, rows, n, N, M.rp, M.col, M.val, pos, rep, mask.p,
+                               varies);
+        int back[2] = {0, 1};
+        CK_HIP(hipMemcpyAsync(back, pos + N, sizeof back, hipMemcpyDeviceToHost, s));
         CK_HIP(hipStreamSynchronize(s));
+        const int total = back[0], var = back[1];
         nd = total;
         constant = var == 0;
     }
