@@ -717,12 +717,16 @@ ck_status gmres_run(SolveCtx &c, const double *b, double *x) {
         CK_TRY(spmv<double>(c, -1.0, x, 1.0, r64, final_ptr));
         CK_TRY(launch_gm_cycle_start<T>(M.n, r64, V, f.partials, st, c.s));
         if (likely_last) {   // the last cycle stopped early: has this start ended the solve?
-            CK_HIP(hipMemcpyAsync(pin.buf + 64, final_ptr, sizeof(int), hipMemcpyDeviceToHost,
-                                  c.s));
+            constexpr size_t from = offsetof(GmDev<T>, relres), to = offsetof(GmDev<T>, final_state);
+            CK_HIP(hipMemcpyAsync(pin.buf + 64, (const char *)st + from, to + sizeof(int) - from,
+                                  hipMemcpyDeviceToHost, c.s));
             CK_HIP(hipStreamSynchronize(c.s));
+            double rr;
             int fs;
-            std::memcpy(&fs, pin.buf + 64, sizeof fs);
-            if (fs != RUN)
+            std::memcpy(&rr, pin.buf + 64, sizeof rr);
+            std::memcpy(&fs, pin.buf + 64 + to - from, sizeof fs);
+            // no cycle mends a residual that is not finite; each would stop at once
+            if (fs != RUN || !std::isfinite(rr))
                 break;
             likely_last = false;
         }
