@@ -408,8 +408,8 @@ __device__ __forceinline__ void stage_products(int j0, int nents, const int *__r
 // built by the conversion), so a thread needs no search and no row pointers,
 // its eight products are read together, and its place in the rows is a
 // prefix sum of bit counts; without a plan (a product before any conversion)
-// two threads search the workgroup's coordinates and every thread searches
-// its own start in LDS, with the same items per thread and so the same bits.
+// two threads search the workgroup's coordinates and the bits are made in LDS
+// from the row pointers: the same items per thread, and so the same result.
 // Rows cut by thread boundaries are completed in LDS, rows cut by workgroup
 // boundaries by carry_fixup; the finished rows leave LDS in row order.
 //
@@ -431,7 +431,7 @@ __device__ __forceinline__ void merge_rows(int n, int nnz, int64_t G, const int 
     __shared__ int s_crow[256];
     __shared__ T s_cval[256];
     __shared__ T s_prod[ITEMS + ITEMS / 8];   // the products, then the row sums
-    __shared__ int s_rend[PLAN ? 1 : ITEMS + 1];
+    __shared__ unsigned s_bits[PLAN ? 1 : 64];
     __shared__ int s_wave[4];
     __shared__ int2 s_coord[2];
     const int64_t b = ck::xcd_block(G);
@@ -447,51 +447,35 @@ __device__ __forceinline__ void merge_rows(int n, int nnz, int64_t G, const int 
     } else {
         if (tid < 2)
             s_coord[tid] = merge_start(n, nnz, rp, b + tid);
+        if (tid < 64)
+            s_bits[tid] = 0;
         __syncthreads();
         c0 = s_coord[0];
         c1 = s_coord[1];
     }
     const int i0 = c0.x, nends = c1.x - c0.x, nents = c1.y - c0.y;
     const int items = nends + nents;
-    if constexpr (!PLAN)
-        for (int t = tid; t <= nends; t += 256)
-            s_rend[t] = i0 + t < n ? rp[i0 + t + 1] - c0.y : nents;
+    if constexpr (!PLAN)   // as merge_bits
+        for (int t = tid; t < nends; t += 256) {
+            const int at = rp[i0 + t + 1] - c0.y + t;
+            atomicOr(&s_bits[at >> 5], 1u << (at & 31));
+        }
     stage_products<T>(c0.y, nents, col, val, x, s_prod);
-    const int dl = tid * kMergeIPT;   // this thread's first item
-    int a;                            // row ends before it
-    if constexpr (PLAN) {
-        const int pc = __popc(mask);
-        const int sc = ck::wave_scan(pc);
-        if ((tid & 63) == 63)
-            s_wave[tid >> 6] = sc;
+    if constexpr (!PLAN) {
         __syncthreads();
-        a = sc - pc;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#pragma unroll
-        for (int w = 0; w < 3; ++w)
-            a += w < wave ? s_wave[w] : 0;
-    } else {
-        __syncthreads();
-        int lo = max(0, dl - nents), hi = min(dl, nends);
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (s_rend[mid] <= dl - mid - 1)
-                lo = mid + 1;
-            else
-                hi = mid;
-        }
-        a = lo;
-        int e = dl - lo;
-#pragma unroll
-        for (int d = 0, r = lo; d < kMergeIPT; ++d) {
-            if (r < nends && s_rend[r] <= e) {
-                mask |= 1u << d;
-                ++r;
-            } else {
-                ++e;
-            }
-        }
+        mask = ((const unsigned char *)s_bits)[tid];
     }
+    const int dl = tid * kMergeIPT;   // this thread's first item
+    const int pc = __popc(mask);
+    const int sc = ck::wave_scan(pc);
+    if ((tid & 63) == 63)
+        s_wave[tid >> 6] = sc;
+    __syncthreads();
+    int a = sc - pc;                  // row ends before it
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+        a += w < wave ? s_wave[w] : 0;
     T v[kMergeIPT];   // item d: its product, or the sum of the row it ends
 #pragma unroll
     for (int d = 0; d < kMergeIPT; ++d) {
@@ -815,7 +799,7 @@ ck_status launch_merge_plan(int64_t rows, int64_t nnz, const int32_t *rp, int32_
     hipLaunchKernelGGL(merge_partition, dim3(ceil_div(G + 1, 256)), dim3(256), 0, s, (int)rows,
                        (int)nnz, G, rp, part);
     if (G > 0)
-        hipLaunchKernelGGL(merge_bits, dim3(std::min<int64_t>(G, 16384)), dim3(256), 0, s, G, rp,
+        hipLaunchKernelGGL(merge_bits, dim3(std::min<int64_t>(G, 4096)), dim3(256), 0, s, G, rp,
                            part, (unsigned *)(plan + 2 * (G + 1)));
     CK_HIP(hipGetLastError());
     return CK_OK;
