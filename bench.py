@@ -840,8 +840,8 @@ def solver_summary(args):
     lat, r, x = _timed_solves(ck, ck.cg_solve, Mx, b, 100, 5, tol=1e-10, config=cfg)
     assert oracle.relres(A, b.cpu().numpy(), x.cpu().numpy()) <= 1e-10
     row["default_csr_vector"] = {**_lat(lat), "iterations": r["iterations"],
-                                 "kernel": f"batched_chunk, {ck.CONFIG_NAMES[ck.config_id(cfg)]} "
-                                           "product, whole solve in one launch"}
+                                 "kernel": f"{ck.CONFIG_NAMES[ck.config_id(cfg)]} in every product "
+                                           "(use_config), multi-workgroup kernels"}
     if not args.no_cpu_baseline:
         bh = b.cpu().numpy()
         for par in (True, False):

@@ -427,7 +427,8 @@ ck_status ck_config_from_id(int32_t id, ck_config *out);
  * DIA's kernel is specialised for the matrix's diagonal count: its name ends
  * in ", ND>", ND being 3, 5, 7, 9, 13, 15, 19 or 27, or 0 for any other
  * count, and is spmv_dia_const when every diagonal's values are equal.
- * CSR-panel's is spmv_slices after a copy by slices of x.  Writes a
+ * CSR-panel's is spmv_slices after a copy by slices of x.  CSR-merge's ends in
+ * "true>", and in "false>" in products before the conversion.  Writes a
  * NUL-terminated string of at most cap bytes. */
 ck_status ck_kernel_name(const ck_config *cfg, int32_t fp32, char *buf, size_t cap);
 

@@ -12,8 +12,9 @@
 //   update: x += beta * d  (FP64)
 // With FP64 inner vectors the same loop is plain CG (inner target
 // tol ||b||/beta, then the true-residual check) or plain restarted GMRES(m);
-// the solvers use it, with 1024 threads, for systems too small to fill the
-// GPU, where one workgroup running the whole solve beats a launch per step.
+// single solves use it, with 1024 threads, for systems too small to fill the
+// GPU, where one workgroup running the whole solve beats a launch per step
+// (slotrule.hpp).
 // Every reduction stays inside the workgroup in a fixed order, so a slot's
 // bits do not depend on which other slots share the launch.
 #include <algorithm>
@@ -962,7 +963,8 @@ __device__ __forceinline__ void run_slot(ck::BSlot *slots, ck::BStat *stat, int 
 // step is a chain of L2 round trips, so more threads shorten it (n = 7,000,
 // FP32 CG: 103 us a step with 256 threads and the vectors in memory, 8 us
 // now), while a system of a thousand rows gains nothing from more than 256
-// and leaves the rest of the compute unit to other slots.  The width follows
+// and, where no slot of the launch is wider, leaves the rest of the compute
+// unit to other slots (the wide kernel's LDS fills it).  The width follows
 // from n alone, so a slot's bits do not depend on the launch it is in.
 template <typename T, int BS>
 __global__ __launch_bounds__(BS) void batched_chunk(ck::BSlot *slots, ck::BStat *stat,

@@ -11,7 +11,8 @@ enum : int { B_CG = 0, B_GMRES = 1 };
 enum : int { B_OUTER = 0, B_INNER = 1, B_UPDATE = 2, B_DONE = 3 };
 
 // Slot copy of a small matrix (at most kSlotRows rows), read by the inner
-// products: sliced ELLPACK with the rows sorted by length, longest first (ties
+// products: sliced ELLPACK (Monakov, Lokhmotov and Avetisyan, 2010) with the rows
+// sorted by length as in SELL-C-sigma (Kreutzer et al., 2014), longest first (ties
 // by row), 64 to a slice, one lane per row.  Slice s holds slots base[s] ..
 // base[s + 1] - 1, slot-major (64 lanes of entry 0, of entry 1, ...), K_s = its
 // first row's length; columns are 16 bits, padding has column n (a zero kept

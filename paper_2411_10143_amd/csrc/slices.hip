@@ -14,7 +14,8 @@
 //
 // Measured (before: merge path, the best there was): n = 180,000 36.8 -> 24.6 us, FP32
 // 34.1 -> 17.0; n = 100,000 22.1 -> 17.6, FP32 20.6 -> 12.7; n = 300,000 57.8 -> 44.4,
-// FP32 53.4 -> 28.7.  The conversion (with the panels' count, 11 us): 66 us, 84 us (n = 180,000), 120 us (300,000).
+// FP32 53.4 -> 28.7.  The conversion, 11 us of it the panels' count: n = 100,000 66 us,
+// 180,000 84, 300,000 120.
 // Bounds now: the entries (10 bytes, FP32 6) and the partial sums, written and read,
 // 2/3 of it; the rest is the launch of the sum and the first loads' latency.
 // Where every workgroup went through all slices instead, so that no partial sums were
